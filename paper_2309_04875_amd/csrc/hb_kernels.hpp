@@ -194,9 +194,6 @@ struct TileTraits {
     using S = Shape<W>;
     static constexpr int L = S::L;
     static constexpr bool kSupported = (L >= 2);                // every width below 33
-    // the group lane publishes party 1's sign bit of a field next to party 0's; one-bit fields have no room for
-    // that, but their 32 fields leave the upper half of the word free
-    static constexpr int kSign1 = (W == 1) ? 32 : 1;
     static constexpr int kGroups = tile_groups(W);              // groups per wavefront
     static constexpr int kTile = tile_elements(W);              // elements per wavefront
     static constexpr int kPairs = (kTile / 2 + kWave - 1) / kWave;   // element pairs per lane (the last may be idle)
@@ -211,6 +208,113 @@ struct TileTraits {
     // LDS bytes per wavefront for the slices
     static constexpr int kSliceBytes = kPacked ? 2 * kWave * 8 : kTile * (int)sizeof(Entry);
 };
+
+// ---- what a group lane publishes for the owners of its elements -------------------------------------------------
+// DReLU / ReLU: the opened bit z and the dealer's bit r of every element (B2aBits), formed for all L fields at once.
+// Where a pair of fields is an LDS item (kPacked), z of field j sits at bit jW and r at bit jW + 1 of ONE word, so an
+// owner reads its pair's item and takes four bits at constant places; other widths publish {z at bit jW, r at bit 2j}
+// in two words, which an owner shifts once per pair.  Publishing the sign shares and the dealer word as they were, for
+// every owner to decode with its own shifts, took about ten more instructions per element.
+// Sign shares: {party 0, party 1}, field j at bit jW.
+template <int W, int MODE>
+struct Verdict {
+    using T = TileTraits<W>;
+    static constexpr bool kOneWord = T::kPacked && op_of(MODE) != kSign;
+    using Word = typename std::conditional<kOneWord, uint64_t, U64x2>::type;
+
+    // bit 2j -> bit jW, for the packed widths
+    static __device__ __forceinline__ uint32_t spread_half(uint32_t v)
+    {
+        if constexpr (W == 32) {
+            return v & 1u;
+        } else if constexpr (W == 4) {
+            v = (v & 0x55u) | ((v & 0x5500u) << 8);
+            v = (v | (v << 4)) & 0x05050505u;
+            return (v | (v << 2)) & 0x11111111u;
+        } else {
+            // every bit moves by a multiple of W - 2: one multiply makes all the moves, and what else it produces
+            // stays off the places that are kept (sums of two bits carry into the next place only)
+            constexpr uint32_t kMoves = (W == 16) ? 0x4001u : 0x41041u, kIn = (W == 16) ? 0x5u : 0x55u;
+            constexpr uint32_t kOut = (W == 16) ? 0x10001u : 0x1010101u;
+            return ((v & kIn) * kMoves) & kOut;
+        }
+    }
+    static __device__ __forceinline__ Word make(Pair sum, uint64_t wb)
+    {
+        using S = Shape<W>;
+        if constexpr (op_of(MODE) == kSign) {
+            return U64x2{(sum.p0 >> (W - 1)) & S::ones(), (sum.p1 >> (W - 1)) & S::ones()};
+        } else {
+            const uint64_t sx = (sum.p0 ^ sum.p1) >> (W - 1);      // bit jW: sign_0 ^ sign_1
+            const uint64_t rx = wb ^ (wb >> 1);                    // bit 2j: r
+            if constexpr (kOneWord) {
+                constexpr int kHalfFields = 32 / W;
+                const uint64_t r = ((uint64_t)spread_half((uint32_t)(rx >> (2 * kHalfFields))) << 32) | spread_half((uint32_t)rx);
+                return bitop3<kTtAndXor>(S::ones(), sx, r) | (r << 1);
+            } else {
+                return U64x2{sx, rx};                              // z of field j: bit jW of sx ^ bit 2j of rx
+            }
+        }
+    }
+    // The two elements of pair `pr` (first one: element `e` = 2 pr of the tile).
+    static __device__ __forceinline__ void pick(const unsigned char *lds, int pr, int e, B2aBits (&t)[2])
+    {
+        if constexpr (kOneWord) {
+            const typename T::Item it = reinterpret_cast<const typename T::Item *>(lds)[pr];
+            constexpr int kSecond = W % 32;                // place of the second field in `hi`
+            const uint32_t lo = (uint32_t)it, hi = W == 32 ? (uint32_t)((uint64_t)it >> 32) : lo;
+            t[0] = B2aBits{minus_bit(lo, 0), __builtin_amdgcn_ubfe(lo, 1, 1)};
+            t[1] = B2aBits{minus_bit(hi, kSecond), __builtin_amdgcn_ubfe(hi, kSecond + 1, 1)};
+        } else {
+            constexpr int L = T::L;
+            const U64x2 *verdict = reinterpret_cast<const U64x2 *>(lds);
+            const int grp = e / L, j = e - grp * L;
+            const U64x2 v = verdict[grp];
+            const uint64_t sx = v.a >> (j * W);
+            const uint32_t rx = (uint32_t)(v.b >> (2 * j));
+            t[0].r = rx & 1u;
+            t[0].m = minus_bit((uint32_t)sx ^ rx, 0);
+            // both elements of the pair sit in one group unless L is odd and the pair straddles two
+            uint32_t s1 = (uint32_t)(sx >> W), r1 = rx >> 2;
+            if constexpr (L % 2 != 0) {
+                const bool split = (j == L - 1);
+                const U64x2 v1 = verdict[split ? grp + 1 : grp];
+                if (split) {
+                    s1 = (uint32_t)v1.a;
+                    r1 = (uint32_t)v1.b;
+                }
+            }
+            t[1].r = r1 & 1u;
+            t[1].m = minus_bit(s1 ^ r1, 0);
+        }
+    }
+    static __device__ __forceinline__ void pick_signs(const unsigned char *lds, int e, Pair (&sign)[2])
+    {
+        constexpr int L = T::L;
+        const U64x2 *verdict = reinterpret_cast<const U64x2 *>(lds);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int grp = (e + h) / L, j = (e + h) - grp * L;
+            const U64x2 v = verdict[grp];
+            sign[h] = Pair{(v.a >> (j * W)) & 1u, (v.b >> (j * W)) & 1u};
+        }
+    }
+};
+
+// The owner's part for one pair: what `io` stores for elements e, e + 1 of the tile.
+template <int W, int MODE>
+__device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr, int e, U64x2 xa, U64x2 xb, uint64_t zA, Pair (&r)[2])
+{
+    using V = Verdict<W, MODE>;
+    if constexpr (op_of(MODE) == kSign) {
+        V::pick_signs(verdict, e, r);
+    } else {
+        B2aBits t[2];
+        V::pick(verdict, pr, e, t);
+        r[0] = op_of(MODE) == kDrelu ? b2a_drelu(t[0], zA) : b2a_mul(t[0], Pair{xa.a, xb.a}, zA);
+        r[1] = op_of(MODE) == kDrelu ? b2a_drelu(t[1], zA + 6 * kGamma) : b2a_mul(t[1], Pair{xa.b, xb.b}, zA + 6 * kGamma);
+    }
+}
 
 // ---- where a tile's element pairs come from and where the results go ----------------------------------------
 // Shares in, shares out: the library's normal boundary.
@@ -312,7 +416,7 @@ struct FloatIO {
 // whole tile lies inside the tensor, so no access needs a bounds check (every tile but a tensor's last).
 template <int W, int MODE, bool FULL, class IO>
 __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                               uint64_t tile, int lane, unsigned char *slice_lds, U64x2 *verdict)
+                                               uint64_t tile, int lane, unsigned char *slice_lds, unsigned char *verdict)
 {
     using T = TileTraits<W>;
     using S = Shape<W>;
@@ -366,12 +470,9 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         const uint64_t g = tile * T::kGroups + lane;
         const uint64_t zg = seedB + (g * (uint64_t)S::words_per_group(shared_of(MODE)) + 1) * kGamma;
         const Pair sum = a2b_sum<W, shared_of(MODE)>(u0, u1, zg);
-        // sign of field j: party 0 at bit jW, party 1 at bit jW + kSign1
-        const uint64_t ones = S::ones();
-        const uint64_t sg = ((sum.p0 >> (W - 1)) & ones) | (((sum.p1 >> (W - 1)) & ones) << T::kSign1);
         uint64_t wb = 0;
         if (op_of(MODE) != kSign) wb = mix64(zg + (uint64_t)S::b2a_word(shared_of(MODE)) * kGamma);
-        verdict[lane] = U64x2{sg, wb};
+        reinterpret_cast<typename Verdict<W, MODE>::Word *>(verdict)[lane] = Verdict<W, MODE>::make(sum, wb);
     }
     wave_sync();
 
@@ -379,31 +480,10 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
     const uint64_t zA0 = seedA + (6 * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;   // A[6i] of the lane's first element
 #pragma unroll
     for (int c = 0; c < T::kPairs; ++c) {
-        const int e = 2 * (c * kWave + lane);
+        const int pr = c * kWave + lane, e = 2 * pr;
         if (e < T::kTile) {
             Pair r[2];
-            const int grp0 = e / L, j0 = e - grp0 * L;
-            const U64x2 v0 = verdict[grp0];
-            // both elements of the pair sit in one group unless L is odd and the pair straddles two
-            const bool split = (L % 2 != 0) && (j0 == L - 1);
-            const U64x2 v1 = split ? verdict[grp0 + 1] : v0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const U64x2 v = h ? v1 : v0;
-                const int j = h ? (split ? 0 : j0 + 1) : j0;
-                // only two bits of each shifted word are used
-                const uint64_t sg = v.a >> (j * W);
-                const Pair sign{sg & 1u, (sg >> T::kSign1) & 1u};
-                if (op_of(MODE) == kSign) {
-                    r[h] = sign;
-                } else {
-                    const uint32_t rh = (uint32_t)(v.b >> (2 * j));
-                    const Pair rho{rh & 1u, (rh >> 1) & 1u};
-                    const uint64_t zA = zA0 + (uint64_t)(6 * (2 * c * kWave + h)) * kGamma;
-                    const Pair D = b2a_drelu(sign, rho, zA);
-                    r[h] = (op_of(MODE) == kDrelu) ? D : beaver_mul(Pair{h ? xa[c].b : xa[c].a, h ? xb[c].b : xb[c].a}, D, zA);
-                }
-            }
+            finish_pair<W, MODE>(verdict, pr, e, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
@@ -412,7 +492,7 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
 // `tile` must be uniform over the wavefront (callers derive it from wave_index()).
 template <int W, int MODE, class IO>
 __device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                          uint64_t tile, int lane, unsigned char *slice_lds, U64x2 *verdict)
+                                          uint64_t tile, int lane, unsigned char *slice_lds, unsigned char *verdict)
 {
     if ((tile + 1) * TileTraits<W>::kTile <= n)
         tile_body_impl<W, MODE, true>(io, n, k, seedB, seedA, tile, lane, slice_lds, verdict);
@@ -434,7 +514,7 @@ tile_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t 
 {
     using T = TileTraits<W>;
     __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ U64x2 verdict_all[kWavesPerBlock][kWave];     // per group: {sign shares, B2A dealer word}
+    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, MODE>::Word)];
     const int lane = threadIdx.x % kWave, wv = wave_index();
     const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
     if (tile * T::kTile >= n) return;        // whole wavefront beyond the tensor (uniform per wave)
@@ -465,7 +545,7 @@ tile_batch_kernel(const BatchArgs args)
 {
     using T = TileTraits<W>;
     __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ U64x2 verdict_all[kWavesPerBlock][kWave];
+    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, MODE>::Word)];
     const int lane = threadIdx.x % kWave, wv = wave_index();
     const uint64_t gt = (uint64_t)blockIdx.x * kWavesPerBlock + wv;          // wave-tile number over the whole batch
     if (gt >= args.tile_end[args.count - 1]) return;
@@ -510,7 +590,7 @@ constexpr int small_tile_elements(int w) { return 16 * tile_lanes_per_word(w); }
 template <int W, int MODE, bool FULL>
 __device__ __forceinline__ void small_tile_body_impl(const ShareIO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                      uint64_t tile, int lane, unsigned char *slice_lds, uint64_t *words_lds,
-                                                     U64x2 *verdict)
+                                                     unsigned char *verdict)
 {
     using T = TileTraits<W>;
     using Q = SmallTraits<W>;
@@ -575,34 +655,17 @@ __device__ __forceinline__ void small_tile_body_impl(const ShareIO &io, uint64_t
         }
     }
     const Pair sum = a2b_sum_words<W>(u0, u1, gw);
-    const uint64_t ones = S::ones();
-    const uint64_t sg = ((sum.p0 >> (W - 1)) & ones) | (((sum.p1 >> (W - 1)) & ones) << T::kSign1);
-    if (sub == 0) verdict[grp] = U64x2{sg, gw[Q::kWords - 1]};
+    if (sub == 0) reinterpret_cast<typename Verdict<W, MODE>::Word *>(verdict)[grp] = Verdict<W, MODE>::make(sum, gw[Q::kWords - 1]);
     wave_sync();
 
     // ---- owners: pick up the verdict of each element's group, finish, store -------------------------------
     const uint64_t zA0 = seedA + (6 * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
 #pragma unroll
     for (int c = 0; c < Q::kPairs; ++c) {
-        const int e = 2 * (c * kWave + lane);
+        const int pr = c * kWave + lane, e = 2 * pr;
         if (e < Q::kTile) {
             Pair r[2];
-            const int grp0 = e / L, j0 = e - grp0 * L;
-            const U64x2 v0 = verdict[grp0];
-            const bool split = (L % 2 != 0) && (j0 == L - 1);
-            const U64x2 v1 = split ? verdict[grp0 + 1] : v0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const U64x2 v = h ? v1 : v0;
-                const int j = h ? (split ? 0 : j0 + 1) : j0;
-                const uint64_t sgj = v.a >> (j * W);
-                const Pair sign{sgj & 1u, (sgj >> T::kSign1) & 1u};
-                const uint32_t rh = (uint32_t)(v.b >> (2 * j));
-                const Pair rho{rh & 1u, (rh >> 1) & 1u};
-                const uint64_t zA = zA0 + (uint64_t)(6 * (2 * c * kWave + h)) * kGamma;
-                const Pair D = b2a_drelu(sign, rho, zA);
-                r[h] = (op_of(MODE) == kDrelu) ? D : beaver_mul(Pair{h ? xa[c].b : xa[c].a, h ? xb[c].b : xb[c].a}, D, zA);
-            }
+            finish_pair<W, MODE>(verdict, pr, e, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
@@ -617,7 +680,7 @@ small_batch_kernel(const BatchArgs args)
     using Q = SmallTraits<W>;
     __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][Q::kSliceBytes];
     __shared__ __attribute__((aligned(16))) uint64_t words_all[kWavesPerBlock][Q::kGroups * Q::kStride];
-    __shared__ U64x2 verdict_all[kWavesPerBlock][Q::kGroups + 1];
+    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][Q::kGroups * sizeof(typename Verdict<W, MODE>::Word)];
     const int lane = threadIdx.x % kWave, wv = wave_index();
     const uint64_t gt = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
     if (gt >= args.tile_end[args.count - 1]) return;
@@ -658,7 +721,7 @@ tile_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seed
 {
     using T = TileTraits<W>;
     __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ U64x2 verdict_all[kWavesPerBlock][kWave];
+    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, kRelu>::Word)];
     const int lane = threadIdx.x % kWave, wv = wave_index();
     const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
     if (tile * T::kTile >= n) return;

@@ -140,52 +140,60 @@ __device__ __forceinline__ Shares<P> mp_a2b_sum(const uint64_t (&u)[P], uint64_t
 
 // Everything after the circuit for one element.  sign / rho: bit q = party q's XOR share of the sign / of the
 // dealer bit.  zA = generator state of the element's first arithmetic word.  MODE: kDrelu or kRelu.
+// As for two parties (b2a_shares): with c_q = ~r^A_q and q = r^A_{P-1} - 1 = c_0 + ... + c_{P-2} + (P - 2) + r,
+//   DReLU_0 = (c_0 ^ m) + 2 (1 - z),  DReLU_q = (c_q ^ m) + (1 - z),  DReLU_{P-1} = ~(q ^ m) + z.
 template <int P, int MODE>
 __device__ __forceinline__ Shares<P> mp_finish(uint32_t sign, uint32_t rho, const Shares<P> &x, uint64_t zA)
 {
-    const uint64_t z = (uint64_t)(__popc(sign ^ rho) & 1);    // opened bit
-    const uint64_t r = (uint64_t)(__popc(rho) & 1);           // known to the dealer only
-    uint64_t rA[P], rsum = 0;
+    const uint32_t r = (uint32_t)__popc(rho) & 1u;            // known to the dealer only
+    const int32_t m = minus_bit((uint32_t)__popc(sign ^ rho), 0);    // -z, the opened bit
+    const uint64_t mm = (uint64_t)(int64_t)m;
+    uint64_t f[P], csum = 0;
 #pragma unroll
     for (int q = 0; q < P - 1; ++q) {
-        rA[q] = mix64(zA + (uint64_t)q * kGamma);
-        rsum += rA[q];
+        const uint64_t c = ~mix64(zA + (uint64_t)q * kGamma);
+        csum += c;
+        f[q] = held(c ^ mm);
     }
-    rA[P - 1] = r - rsum;
-    Shares<P> D;
+    f[P - 1] = held(~((csum + (r + (uint32_t)(P - 2))) ^ mm));
+    if (MODE == kDrelu) {
+        const uint32_t n = (uint32_t)(m + 1), z = (uint32_t)-m;
+        Shares<P> D;
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-        const uint64_t pub = (q == 0) ? 1 : 0;
-        const uint64_t beta = z ? (pub - rA[q]) : rA[q];       // sign = z + r - 2zr, party 0 adds the public z
-        D.v[q] = pub - beta;
+        for (int q = 0; q < P; ++q) D.v[q] = f[q] + (q == 0 ? 2 * n : q == P - 1 ? z : n);
+        return D;
     }
-    if (MODE == kDrelu) return D;
 
+    uint64_t drelu = f[0];                                    // sum of the DReLU_q
+#pragma unroll
+    for (int q = 1; q < P; ++q) drelu += f[q];
+    drelu = held(drelu + (uint32_t)(P + (P - 1) * m));
     const uint64_t zM = zA + (uint64_t)(P - 1) * kGamma;
     uint64_t a[P], b[P], c[P];
-    uint64_t as = 0, bs = 0, cs = 0, xs = 0, del = 0;
+    uint64_t as = 0, b_others = 0, cs = 0, xs = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
         a[q] = mix64(zM + (uint64_t)q * kGamma);
         b[q] = mix64(zM + (uint64_t)(P + q) * kGamma);
         as += a[q];
-        bs += b[q];
+        if (q > 0) b_others += b[q];
         xs += x.v[q];
-        del += D.v[q] - b[q];                // opened: each party's message D_q - b_q, summed
     }
 #pragma unroll
     for (int q = 0; q < P - 1; ++q) {
         c[q] = mix64(zM + (uint64_t)(2 * P + q) * kGamma);
         cs += c[q];
     }
-    const uint64_t eps = xs - as;            // opened: sum over the parties of x_q - a_q
+    const uint64_t eps = xs - as;                             // opened: sum over the parties of x_q - a_q
+    const uint64_t b0_del = held(drelu - b_others);           // b_0 + del
+    const uint64_t del = b0_del - b[0];                       // opened: sum of D_q - b_q
     Shares<P> out;
     // party 0 takes the public term: c_0 + eps * b_0 + del * a_0 + eps * del
-    out.v[0] = sum_of_products(c[0], eps, b[0] + del, del, a[0]);
+    out.v[0] = sum_of_products(c[0], eps, b0_del, del, a[0]);
 #pragma unroll
     for (int q = 1; q < P - 1; ++q) out.v[q] = sum_of_products(c[q], eps, b[q], del, a[q]);
     // the last party's c completes the triple: c_{P-1} = a * b - (c_0 + ... + c_{P-2})
-    out.v[P - 1] = sum_of_products(0 - cs, as, bs, eps, b[P - 1], del, a[P - 1]);
+    out.v[P - 1] = sum_of_products(0 - cs, as, b[0] + b_others, eps, b[P - 1], del, a[P - 1]);
     return out;
 }
 

@@ -228,18 +228,47 @@ __device__ __forceinline__ Pair a2b_sum_words(uint64_t u0, uint64_t u1, const ui
     return Pair{Sum.p0 ^ ((G.p0 << 1) & keep1), Sum.p1 ^ ((G.p1 << 1) & keep1)};
 }
 
-// B2A of the sign bit and 1 - sign, for one element.  sign/rho: XOR shares of the sign and of the
-// dealer bit r.  zA: generator state of the element's first arithmetic word A[6i].
-__device__ __forceinline__ Pair b2a_drelu(Pair sign, Pair rho, uint64_t zA)
+// What an element keeps of its group's verdict: the opened bit z = sign_0 ^ rho_0 ^ sign_1 ^ rho_1 of the B2A, as
+// m = -z (0 or all ones), and the dealer's bit r = rho_0 ^ rho_1 (0 or 1).
+struct B2aBits {
+    int32_t m;
+    uint32_t r;
+};
+
+// Keeps the compiler from reasoning about a value (a carry chain it would narrow, a sum it would cancel); no instruction.
+__device__ __forceinline__ uint64_t held(uint64_t v)
 {
-    const uint64_t z = (sign.p0 ^ rho.p0) ^ (sign.p1 ^ rho.p1);   // opened bit
-    const uint64_t r = rho.p0 ^ rho.p1;                           // known to the dealer only
-    const uint64_t rA0 = mix64(zA);
-    const uint64_t rA1 = r - rA0;
-    // sign = z ^ r = z + r - 2zr; party 0 adds the public z
-    const uint64_t beta0 = z ? (1 - rA0) : rA0;
-    const uint64_t beta1 = z ? (0 - rA1) : rA1;
-    return Pair{1 - beta0, 0 - beta1};
+    asm("" : "+v"(v));
+    return v;
+}
+
+// bit `at` of v as B2aBits::m
+__device__ __forceinline__ int32_t minus_bit(uint32_t v, int at) { return (int32_t)__builtin_amdgcn_sbfe((int)v, at, 1); }
+
+// B2A of the sign bit and 1 - sign, for one element.  zA: generator state of the element's first arithmetic word
+// A[6i] = r^A_0; r^A_1 = r - r^A_0.  sign = z ^ r = z + r - 2zr and party 0 adds the public z, so
+//   DReLU_0 = 1 - beta_0 = z ? r^A_0 : 1 - r^A_0,   DReLU_1 = -beta_1 = z ? r^A_1 : -r^A_1.
+// A vector instruction costs four SIMD cycles whatever it does, a 64-bit add is one, a subtract, a select or an xor
+// two.  -v = ~v + 1 turns the conditional negations into xors with m; with c = ~r^A_0 (the complement is free: the
+// generator's last xor becomes an xnor) and q = r^A_1 - 1 = c + r,
+//   DReLU_0 = (c ^ m) + 2 (1 - z),   DReLU_1 = ~(q ^ m) + z.
+// With the verdict published as (z, r) pairs the w = 8 ReLU tile is 1986 vector instructions per wavefront where selects
+// and subtracts on separately shifted sign shares and dealer bits took 2060: 285,212,672 elements in 2.175 ms against
+// 2.227, the simulator's 4,194,304 in 34.7 us against 35.6.
+struct B2aShares {
+    uint64_t f0, f1;    // DReLU_0 less 2 (1 - z), DReLU_1 less z
+};
+__device__ __forceinline__ B2aShares b2a_shares(B2aBits t, uint64_t zA)
+{
+    const uint64_t c = ~mix64(zA);
+    const uint64_t q = c + t.r;
+    const uint64_t m = (uint64_t)(int64_t)t.m;
+    return B2aShares{held(c ^ m), held(~(q ^ m))};
+}
+__device__ __forceinline__ Pair b2a_drelu(B2aBits t, uint64_t zA)
+{
+    const B2aShares f = b2a_shares(t, zA);
+    return Pair{f.f0 + (uint32_t)(2 * (t.m + 1)), f.f1 + (uint32_t)-t.m};
 }
 
 // ---- products on Z_2^64 out of 32-bit halves --------------------------------------------------------------------
@@ -247,11 +276,6 @@ __device__ __forceinline__ Pair b2a_drelu(Pair sign, Pair rho, uint64_t zA)
 // multiplies, so a sum of products costs one instruction per 32 x 32 product plus one final add when the cross
 // products are accumulated in a 64-bit register of their own, of which only the low half is used.  held() keeps
 // that register whole: without it the compiler narrows the chain to 32-bit multiplies followed by separate adds.
-__device__ __forceinline__ uint64_t held(uint64_t v)
-{
-    asm("" : "+v"(v));
-    return v;
-}
 __device__ __forceinline__ uint64_t lo32(uint64_t v) { return (uint32_t)v; }
 __device__ __forceinline__ uint64_t hi32(uint64_t v) { return v >> 32; }
 // low + 2^32 * cross, touching only the high half of `low`
@@ -285,9 +309,10 @@ __device__ __forceinline__ uint64_t sum_of_products(uint64_t acc, uint64_t x, ui
     return add_to_high(held(low), cross);
 }
 
-// Beaver multiply x * D on Z_2^64 for one element; the triple is A[6i+1 .. 6i+5].
-__device__ __forceinline__ Pair beaver_mul(Pair x, Pair D, uint64_t zA)
+// Beaver multiply x * DReLU on Z_2^64 for one element; the triple is A[6i+1 .. 6i+5].
+__device__ __forceinline__ Pair b2a_mul(B2aBits t, Pair x, uint64_t zA)
 {
+    const B2aShares f = b2a_shares(t, zA);
     const uint64_t a0 = mix64(zA + 1 * kGamma);
     const uint64_t a1 = mix64(zA + 2 * kGamma);
     const uint64_t b0 = mix64(zA + 3 * kGamma);
@@ -295,10 +320,12 @@ __device__ __forceinline__ Pair beaver_mul(Pair x, Pair D, uint64_t zA)
     const uint64_t c0 = mix64(zA + 5 * kGamma);
     const uint64_t a = a0 + a1, b = b0 + b1;                      // the dealer's triple (a, b, a * b)
     const uint64_t eps = (x.p0 + x.p1) - a;                       // opened: (x_0 - a_0) + (x_1 - a_1)
-    const uint64_t del = (D.p0 - b0) + (D.p1 - b1);               // opened: each party's message, summed
+    // opened: (DReLU_0 - b_0) + (DReLU_1 - b_1), taken as ((DReLU_0 + DReLU_1) - b_1) - b_0: party 0 needs b_0 + del
+    const uint64_t b0_del = held((f.f0 + f.f1) + (uint32_t)(t.m + 2)) - b1;
+    const uint64_t del = held(b0_del) - b0;
     Pair out;
     // party 0: c_0 + eps * b_0 + del * a_0 + eps * del
-    out.p0 = sum_of_products(c0, eps, b0 + del, del, a0);
+    out.p0 = sum_of_products(c0, eps, b0_del, del, a0);
     // party 1: c_1 + eps * b_1 + del * a_1, the dealer having completed c_1 = a * b - c_0
     out.p1 = sum_of_products(0 - c0, a, b, eps, b1, del, a1);
     return out;
@@ -316,12 +343,10 @@ template <int W, int MODE>
 __device__ __forceinline__ Pair finish_element(Pair sum, uint64_t wb, int j, Pair x, uint64_t zA)
 {
     const int sb = j * W + W - 1;
-    const Pair sign{(sum.p0 >> sb) & 1, (sum.p1 >> sb) & 1};
-    if (op_of(MODE) == kSign) return sign;
-    const Pair rho{(wb >> (2 * j)) & 1, (wb >> (2 * j + 1)) & 1};
-    const Pair D = b2a_drelu(sign, rho, zA);
-    if (op_of(MODE) == kDrelu) return D;
-    return beaver_mul(x, D, zA);
+    if (op_of(MODE) == kSign) return Pair{(sum.p0 >> sb) & 1, (sum.p1 >> sb) & 1};
+    const uint32_t r = (uint32_t)((wb ^ (wb >> 1)) >> (2 * j)) & 1u;
+    const B2aBits t{minus_bit((uint32_t)((sum.p0 ^ sum.p1) >> sb) ^ r, 0), r};
+    return op_of(MODE) == kDrelu ? b2a_drelu(t, zA) : b2a_mul(t, x, zA);
 }
 
 }  // namespace hb
