@@ -58,21 +58,13 @@ def kernel_name(w, op="relu", batched=False):
 
 
 def party_path_bytes(n, k, m):
-    """Bytes the party-faithful path must move for one ReLU: what each of its kernels reads and writes once
-    (shares, per-group state words, wire words, per-element DReLU shares, results), both parties."""
+    """Bytes the party-faithful path must move for one ReLU: shares read, result shares and both parties' wires written."""
     w = m - k
     L = min(64 // w, 32)
     R = 0 if w == 1 else (w - 1).bit_length()
     G = (n + L - 1) // L
-    b2a = (n + 63) // 64
-    words = 2 * n + 2 * G * (2 + 2)                                   # slice: read shares; write S, P, two wire words
-    for r in range(R):                                               # round: read state + both wires' previous message;
-        words += 2 * G * ((1 + 4 if r == 0 else 2 + 8) + 2 + 4)      #        write G, P and four wire words
-    words += 2 * G * (2 + (4 if R else 4) + 1)                       # sign: read S, G, the last G-update opening; write Z
-    words += 2 * (G + b2a)                                           # B2A: read Z, write packed bits
-    words += 2 * (n + 2 * b2a + n + 2 * n)                           # multiply send: read share, B2A words; write D, 2 wire words
-    words += 2 * (4 * n + n)                                         # result: read both wires' multiply words, write result
-    return 8 * words
+    wire_words = 2 * G + 4 * G * R + (n + 63) // 64 + 2 * n
+    return 32 * n + 16 * wire_words
 
 
 def _time_launches(fn, torch, warm_ms=120.0, meas_ms=150.0, max_reps=4000):

@@ -172,13 +172,13 @@ HB_API int hb_relu_mp(const int64_t *const *shares, int parties, size_t n, int k
 HB_API uint64_t hb_opened_bits_mp(int relu, int parties, int k, int m, size_t n);   /* 0 for invalid arguments */
 
 /*
- * Party-faithful ReLU: the same protocol and dealer material as hb_relu, but every opening goes through
+ * Party-faithful ReLU: the same protocol and dealer material as hb_relu, but every opening is a message, put in
  * memory the way it would go over the link between two GPUs (Sec. 2.2: each AND, the B2A and the multiply
  * open masked values; Sec. 4.2: the w-bit fields are packed into 64-bit words before each communication).
  * Each party is evaluated by its own threads, owns its state and writes the words it sends to its "wire";
- * a party reads the other wire only for completed rounds (one kernel launch per communication round:
- * slice + gate 0, R prefix rounds, sign, B2A bits, multiply openings, result).  out0 / out1 are
- * bit-for-bit the shares hb_relu returns.
+ * of the other party it learns those words alone, one communication round after the other (slice + gate 0,
+ * R prefix rounds, B2A bits, multiply openings; one kernel launch).  out0 / out1 are bit-for-bit the shares
+ * hb_relu returns.
  *
  * Wire of party p, 64-bit words: [2G: gate 0][4G per round, R rounds][ceil(n/64): B2A][2n: multiply], G =
  * ceil(n / L) groups of L = min(floor(64/w), 32) elements; in a group word field j sits at bit j*w; word

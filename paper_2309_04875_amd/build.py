@@ -30,6 +30,7 @@ HIPCC_FLAGS = [
 MODES = (0, 1, 2, 3, 4)                                 # DReLU, ReLU, sign shares; DReLU, ReLU on the shared-mask layout
 WIDTH_RANGES = ((1, 16), (17, 32), (33, 48), (49, 64))
 MP_PARTIES = (3, 4)                                     # multi-party kernels (two parties: the kernels above)
+PARTY_WIDTH_RANGES = ((1, 4), (5, 8), (9, 16), (17, 32), (33, 48), (49, 64))   # party-faithful kernels
 MP_WIDTH_RANGES = ((1, 8), (9, 16), (17, 32), (33, 48), (49, 64))
 
 
@@ -63,6 +64,9 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
                 units.append((os.path.join(CSRC, "hb_mp_part.hip"),
                               os.path.join(work, "mp_p%d_w%d.o" % (parties, lo)),
                               [("HB_PART_PARTIES", parties), ("HB_PART_LO", lo), ("HB_PART_HI", hi)]))
+        for lo, hi in PARTY_WIDTH_RANGES:
+            units.append((os.path.join(CSRC, "hb_party_part.hip"), os.path.join(work, "party_w%d.o" % lo),
+                          [("HB_PART_LO", lo), ("HB_PART_HI", hi)]))
         with ThreadPoolExecutor(max_workers=jobs) as pool:
             for out in pool.map(_compile, [probes] + units):
                 if verbose and out.strip():

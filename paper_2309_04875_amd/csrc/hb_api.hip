@@ -323,10 +323,11 @@ int run_mp(int op, const int64_t *const *shares, int parties, size_t n, int k, i
     return HB_OK;
 }
 
-// Workspace of the party-faithful path: [wire 0][wire 1][state 0][state 1], every region 256-byte aligned.
-// state p = S, P, G, Z (one word per group each) and D (one word per element).
+// Workspace of the party-faithful path: [wire 0][wire 1][reserve 0][reserve 1], every region 256-byte aligned.  The
+// kernel uses the wires; the reserves (four words per group and one per element for each party) keep the size that
+// callers and HB_PARTY_STATIC_BYTES were told when circuit state lived in memory.
 struct PartyLayout {
-    uint64_t groups, wire_words, wire_off[2], state_off[2], total_bytes;
+    uint64_t groups, wire_words, off_b2a, wire_off[2], total_bytes;
 };
 
 PartyLayout party_layout(size_t n, int k, int m, int dealer = HB_DEALER_PER_GATE)
@@ -337,14 +338,13 @@ PartyLayout party_layout(size_t n, int k, int m, int dealer = HB_DEALER_PER_GATE
     const uint64_t per_round = dealer == HB_DEALER_SHARED_MASK ? 3 : 4;
     PartyLayout lay = {};
     lay.groups = ((uint64_t)n + L - 1) / L;
-    lay.wire_words = 2 * lay.groups + per_round * lay.groups * R + ((uint64_t)n + 63) / 64 + 2 * (uint64_t)n;
+    lay.off_b2a = 2 * lay.groups + per_round * lay.groups * R;
+    lay.wire_words = lay.off_b2a + ((uint64_t)n + 63) / 64 + 2 * (uint64_t)n;
     auto up = [](uint64_t b) { return (b + 255) & ~255ull; };
-    const uint64_t wire_bytes = up(8 * lay.wire_words), state_bytes = up(8 * (4 * lay.groups + (uint64_t)n));
+    const uint64_t wire_bytes = up(8 * lay.wire_words), reserve_bytes = up(8 * (4 * lay.groups + (uint64_t)n));
     lay.wire_off[0] = 0;
     lay.wire_off[1] = wire_bytes;
-    lay.state_off[0] = 2 * wire_bytes;
-    lay.state_off[1] = 2 * wire_bytes + state_bytes;
-    lay.total_bytes = 2 * wire_bytes + 2 * state_bytes;
+    lay.total_bytes = 2 * wire_bytes + 2 * reserve_bytes;
     return lay;
 }
 
@@ -454,29 +454,6 @@ int run_party(const int64_t *share0, const int64_t *share1, size_t n, int k, int
     if (wire_bytes) *wire_bytes = 8 * lay.wire_words;
     if (n == 0) return HB_OK;
 
-    const int w = m - k;
-    hb::PartyShape s = {};
-    s.w = w;
-    s.R = rounds_of(w);
-    s.L = (64 / w) > 32 ? 32 : 64 / w;
-    s.k = k;
-    s.shared = dealer == HB_DEALER_SHARED_MASK;
-    s.per_round = s.shared ? 3 : 4;
-    s.words_per_group = (uint64_t)(s.shared ? 5 + 8 * s.R + 1 : 5 * (1 + 2 * s.R) + 1);
-    s.field = (w == 64) ? ~0ull : ((1ull << w) - 1);
-    auto repeat = [&](uint64_t f) {
-        uint64_t r = 0;
-        for (int j = 0; j < s.L; ++j) r |= f << (j * w);
-        return r;
-    };
-    s.ones = repeat(1);
-    s.live = repeat(s.field);
-    for (int r = 0; r < 6; ++r) {
-        const int sh = 1 << r;
-        s.keep[r] = (sh >= w) ? 0 : repeat((s.field << sh) & s.field);
-    }
-    s.keep1 = (1 >= w) ? 0 : repeat((s.field << 1) & s.field);
-
     hb::PartyCtx c = {};
     char *base = (char *)workspace;
     c.x[0] = (const uint64_t *)share0;
@@ -487,30 +464,13 @@ int run_party(const int64_t *share0, const int64_t *share1, size_t n, int k, int
     c.groups = lay.groups;
     c.seedB = hb::stream_word(seed, 0);
     c.seedA = hb::stream_word(seed, 1);
-    for (int p = 0; p < 2; ++p) {
-        c.wire[p] = (uint64_t *)(base + lay.wire_off[p]);
-        uint64_t *state = (uint64_t *)(base + lay.state_off[p]);
-        c.S[p] = state;
-        c.P[p] = state + lay.groups;
-        c.G[p] = state + 2 * lay.groups;
-        c.Z[p] = state + 3 * lay.groups;
-        c.D[p] = state + 4 * lay.groups;
-    }
-    c.off_b2a = 2 * lay.groups + (uint64_t)s.per_round * lay.groups * (uint64_t)s.R;
-    c.off_mul = c.off_b2a + (n + 63) / 64;
-
-    auto grid_for = [](uint64_t threads) { return dim3((unsigned)((threads + hb::kPartyBlock - 1) / hb::kPartyBlock), 2); };
-    if ((lay.groups + hb::kPartyBlock - 1) / hb::kPartyBlock > 0x7fffffffull || (n + hb::kPartyBlock - 1) / hb::kPartyBlock > 0x7fffffffull)
-        return HB_EINVAL;
-    hipStream_t q = (hipStream_t)stream;
-    const dim3 blk(hb::kPartyBlock);
-    hipLaunchKernelGGL(hb::party_slice_kernel, grid_for(lay.groups), blk, 0, q, c, s);
-    for (int r = 0; r < s.R; ++r) hipLaunchKernelGGL(hb::party_round_kernel, grid_for(lay.groups), blk, 0, q, c, s, r);
-    hipLaunchKernelGGL(hb::party_sign_kernel, grid_for(lay.groups), blk, 0, q, c, s);
-    hipLaunchKernelGGL(hb::party_b2a_kernel, grid_for((n + 63) / 64), blk, 0, q, c, s);
-    hipLaunchKernelGGL(hb::party_mul_send_kernel, grid_for(n), blk, 0, q, c, s);
-    hipLaunchKernelGGL(hb::party_mul_finish_kernel, grid_for(n), blk, 0, q, c, s);
-    const hipError_t e = hipGetLastError();
+    c.k = k;
+    for (int p = 0; p < 2; ++p) c.wire[p] = (uint64_t *)(base + lay.wire_off[p]);
+    c.off_b2a = lay.off_b2a;
+    c.off_mul = lay.off_b2a + (n + 63) / 64;
+    const hb::PartyLauncher f = hb::launcher_table().party[dealer == HB_DEALER_SHARED_MASK][m - k - 1];
+    if (f == nullptr) return fail_hip(hipErrorInvalidDeviceFunction, "no kernel was built for this slice width");
+    const hipError_t e = f(c, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return HB_OK;
 }

@@ -25,12 +25,17 @@ using SimLauncher = hipError_t (*)(const float *x, uint64_t n, int k, uint64_t s
 using MpLauncher = hipError_t (*)(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                   hipStream_t stream);
 
+// The party-faithful ReLU.
+struct PartyCtx;
+using PartyLauncher = hipError_t (*)(const PartyCtx &c, hipStream_t stream);
+
 struct LauncherTable {
     GroupLauncher f[kModes][64];       // [mode][w - 1]
     BatchLauncher batch[kModes][64];   // null where the width has no tile kernel
     BatchLauncher small[kModes][64];   // small wave-tiles (tile_end counts small tiles); null where there is none
     SimLauncher sim[64];               // null where the width has no tile kernel
     MpLauncher mp[kMaxParties - 2][2][64];   // [parties - 3][kDrelu | kRelu][w - 1]
+    PartyLauncher party[2][64];        // [shared-mask layout][w - 1]
 };
 
 LauncherTable &launcher_table();
