@@ -738,33 +738,26 @@ int hb_eco_scan(const int64_t *share0, const int64_t *share1, size_t n, uint64_t
         const Range c = range_of(counts, 64);
         if (!disjoint(c, range_of(share0, n)) || !disjoint(c, range_of(share1, n))) return HB_EINVAL;
     }
-    hipLaunchKernelGGL(hb::eco_zero_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, (unsigned long long *)counts);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail_hip(e, "kernel launch");
-    if (n == 0) return HB_OK;
-    // aim at about 1024 wavefronts (one block per CU: the per-wave epilogue and the 64 atomics per block are
-    // fixed costs, and 4 waves per CU with 64 loads in flight each already stream at 4.4 TB/s);
-    // a lane takes `chunks` carry-save trees of 64 elements
-    const uint64_t target_waves = 1024;
-    uint64_t per_lane = ((uint64_t)n + target_waves * 64 - 1) / (target_waves * 64);
-    uint64_t chunks = (per_lane + hb::kEcoChunk - 1) / hb::kEcoChunk;
-    if (chunks < 1) chunks = 1;
-    if (chunks > (uint64_t)hb::kEcoMaxPerLane / hb::kEcoChunk) chunks = hb::kEcoMaxPerLane / hb::kEcoChunk;
-    const uint64_t per_wave = (uint64_t)hb::kWave * hb::kEcoChunk * chunks;
-    const uint64_t waves = ((uint64_t)n + per_wave - 1) / per_wave;
-    const uint64_t blocks = (waves + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-    if (blocks > 0x7fffffffull) return HB_EINVAL;
-    int live = 1;
-    while ((1ull << live) <= chunks * hb::kEcoChunk) ++live;      // planes that can be non-zero
-    if (all_aligned16(ptrs, 2)) {
-        hipLaunchKernelGGL((hb::eco_scan_kernel<true>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, (hipStream_t)stream,
-                           (const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, (int)chunks, live,
-                           (unsigned long long *)counts);
-    } else {
-        hipLaunchKernelGGL((hb::eco_scan_kernel<false>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, (hipStream_t)stream,
-                           (const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, (int)chunks, live,
-                           (unsigned long long *)counts);
+    // One workgroup per compute unit (kEcoWaves x 256 wavefronts), fewer where a wavefront would get less than one tree of rows,
+    // more where a lane's counter would overflow.
+    const uint64_t rows = ((uint64_t)n + hb::kEcoRow - 1) / hb::kEcoRow;
+    uint64_t blocks = (rows + hb::kEcoRows * hb::kEcoWaves - 1) / (hb::kEcoRows * hb::kEcoWaves);
+    if (blocks > 256) blocks = 256;
+    const uint64_t least = (rows + hb::kEcoMaxRows * hb::kEcoWaves - 1) / (hb::kEcoMaxRows * hb::kEcoWaves);
+    if (blocks < least) blocks = least;
+    hipError_t e;
+    if (blocks != 1) {                  // a single workgroup stores its counts
+        hipLaunchKernelGGL(hb::eco_zero_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, (unsigned long long *)counts);
+        e = hipGetLastError();
+        if (e != hipSuccess) return fail_hip(e, "kernel launch");
     }
+    if (n == 0) return HB_OK;
+    const uint64_t per_lane = 2 * ((rows + blocks * hb::kEcoWaves - 1) / (blocks * hb::kEcoWaves));
+    int live = 1;
+    while ((1ull << live) <= per_lane) ++live;      // planes that can be non-zero
+    hipLaunchKernelGGL(hb::eco_scan_kernel, dim3((unsigned)blocks), dim3(hb::kEcoBlock), 0, (hipStream_t)stream,
+                       (const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, rows, live,
+                       (unsigned long long *)counts);
     e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return HB_OK;
