@@ -378,7 +378,7 @@ def main():
             plan = hb.hb_plan_create([(a, b, c, d, kk, mm, ROOT_SEED)], True)
             ms = _time_launches(plan.run, torch, 30.0, 60.0)
             add_config("cfg1 flat 65,536, (%d,%d)" % (kk, mm), sp.n, [mm - kk], "one hb_plan_run (1 launch)", ms,
-                       hb.hb_opened_bits(True, kk, mm, 1), kernel_name(mm - kk) if mm - kk > 32 else "hb::small_batch_kernel<%d, relu>" % (mm - kk))
+                       hb.hb_opened_bits(True, kk, mm, 1), kernel_name(mm - kk, batched=True))
             ms = _time_launches(lambda: hb.hb_relu(a, b, kk, mm, ROOT_SEED, c, d), torch, 30.0, 60.0)
             extra["flat_65536_w%d_us_plain_hb_relu_call" % (mm - kk)] = ms * 1e3
             hb.hb_plan_destroy(plan)
@@ -392,7 +392,7 @@ def main():
         plan = hb.hb_plan_create(small_batch, True)
         ms = _time_launches(plan.run, torch, 30.0, 60.0)
         add_config("cfg2 resnet18 32x32 one image, per-tensor (k,m)", n_small, [8], "one hb_plan_run (1 launch)", ms, bits_small,
-                   "hb::small_batch_kernel<8, relu>")
+                   kernel_name(8, batched=True))
         ms = _time_launches(lambda: hb.hb_relu_batch(small_batch), torch, 30.0, 60.0)
         extra["one_image_set_us_plain_batched_call"] = ms * 1e3
         ms = _time_launches(lambda: [hb.hb_relu(a, b, kk, mm, sd, c, d) for (a, b, c, d, kk, mm, sd) in small], torch, 30.0, 60.0)

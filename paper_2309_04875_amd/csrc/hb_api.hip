@@ -166,18 +166,6 @@ hipError_t enqueue(const LaunchItem &it, hipStream_t stream)
     return it.single(d.x0, d.x1, d.n, d.k, d.seedB, d.seedA, d.o0, d.o1, it.vec16, stream);
 }
 
-// Launches with fewer large wave-tiles than this take the small wave-tile kernels (where the width has them): below
-// about one wavefront per SIMD a launch lasts as long as one wavefront's instruction stream, which they shorten.
-// HB_SMALL_TILE_LIMIT in the environment (read once) overrides the limit; 0 switches the small tiles off.
-uint64_t small_tile_limit()
-{
-    static const uint64_t limit = [] {
-        const char *v = std::getenv("HB_SMALL_TILE_LIMIT");
-        return v != nullptr ? (uint64_t)std::strtoull(v, nullptr, 10) : (uint64_t)1536;
-    }();
-    return limit;
-}
-
 void fill_tensor(hb::BatchTensor &d, const hb_tensor &t)
 {
     d.x0 = (const uint64_t *)t.share0;
@@ -222,25 +210,34 @@ int plan_launches(int mode, const hb_tensor *tensors, size_t count, std::vector<
                 same.push_back(j);
             }
         }
-        const uint64_t per_big = (uint64_t)hb::tile_elements(w);
-        uint64_t big_tiles = 0;
-        for (size_t j : same) big_tiles += (tensors[j].n + per_big - 1) / per_big;
-        const hb::BatchLauncher small = hb::launcher_table().small[mode][w - 1];
-        const bool use_small = small != nullptr && big_tiles < small_tile_limit();
-        const uint64_t per_tile = use_small ? (uint64_t)hb::small_tile_elements(w) : per_big;
+        const uint64_t per_tile = (uint64_t)hb::tile_elements(w);
         LaunchItem it;
-        it.tiles = use_small ? small : big;
+        auto start = [&] {
+            it.tiles = big;
+            it.args = hb::BatchArgs{};
+            for (uint32_t &e : it.args.tile_end) e = hb::kNoTile;
+        };
+        auto finish = [&] {
+            it.args.whole_blocks = hb::tile_grid(it.args.tiles, w).whole_blocks;
+            items.push_back(it);
+        };
+        start();
         for (size_t j : same) {
-            if (it.args.count == hb::kBatchMax) {
-                items.push_back(it);
-                it.args = hb::BatchArgs{};
-            }
             const hb_tensor &t = tensors[j];
-            fill_tensor(it.args.t[it.args.count], t);
-            it.args.tile_end[it.args.count] = (it.args.count ? it.args.tile_end[it.args.count - 1] : 0) + (t.n + per_tile - 1) / per_tile;
+            const uint64_t tiles = (t.n + per_tile - 1) / per_tile;
+            if (tiles >= hb::kNoTile) return fail_hip(hipErrorInvalidConfiguration, "more wave-tiles than a grid holds");
+            if (it.args.count == hb::kBatchMax || it.args.tiles + tiles >= hb::kNoTile) {
+                finish();
+                start();
+            }
+            hb::BatchTensor &d = it.args.t[it.args.count];
+            fill_tensor(d, t);
+            d.first_tile = it.args.tiles;
+            if (it.args.count > 0) it.args.tile_end[it.args.count - 1] = it.args.tiles;
+            it.args.tiles += (uint32_t)tiles;
             ++it.args.count;
         }
-        items.push_back(it);
+        finish();
     }
     return HB_OK;
 }
@@ -259,24 +256,11 @@ int run(int mode, const int64_t *share0, const int64_t *share1, size_t n, int k,
     }
     if (n > 0) {
         const uint64_t seedB = hb::stream_word(seed, 0), seedA = hb::stream_word(seed, 1);
-        const uint64_t per_big = (uint64_t)hb::tile_elements(w);
-        const hb::BatchLauncher small = hb::force_group_kernel() ? nullptr : hb::launcher_table().small[mode][w - 1];
-        hipError_t e;
-        if (small != nullptr && (n + per_big - 1) / per_big < small_tile_limit()) {
-            hb::BatchArgs args = {};
-            const hb_tensor t = {share0, share1, out0, out1, n, k, m, seed};
-            fill_tensor(args.t[0], t);
-            const uint64_t per_tile = (uint64_t)hb::small_tile_elements(w);
-            args.tile_end[0] = (n + per_tile - 1) / per_tile;
-            args.count = 1;
-            e = small(args, (hipStream_t)stream);
-        } else {
-            const void *ptrs[4] = {share0, share1, out0, out1};
-            const hb::GroupLauncher f = hb::launcher_table().f[mode][w - 1];
-            if (f == nullptr) return fail_hip(hipErrorInvalidDeviceFunction, "no kernel was built for this slice width");
-            e = f((const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, k, seedB, seedA, (uint64_t *)out0,
-                  (uint64_t *)out1, all_aligned16(ptrs, 4), (hipStream_t)stream);
-        }
+        const void *ptrs[4] = {share0, share1, out0, out1};
+        const hb::GroupLauncher f = hb::launcher_table().f[mode][w - 1];
+        if (f == nullptr) return fail_hip(hipErrorInvalidDeviceFunction, "no kernel was built for this slice width");
+        const hipError_t e = f((const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, k, seedB, seedA,
+                               (uint64_t *)out0, (uint64_t *)out1, all_aligned16(ptrs, 4), (hipStream_t)stream);
         if (e != hipSuccess) return fail_hip(e, "kernel launch");
     }
     if (opened_bits) *opened_bits = bits;
@@ -482,6 +466,34 @@ LauncherTable &launcher_table()
 {
     static LauncherTable table = {};
     return table;
+}
+
+// A tile that runs alone on a SIMD takes as long as a full round of tiles, one per SIMD.  Launches of fewer than
+// small_tile_limit() tiles share every tile out by quarters; longer ones share out what is left after their last full round
+// where that is at most kSplitMost tiles, which then takes the time of one or two quarters instead of a tile's.
+// Measured, quarters against whole tiles: w = 8, 512 tiles 5.3 / 7.0 us, 900 6.9 / 7.1, 1088 (64 left) 7.5 / 9.9,
+// 1536 (512 left) 9.0 / 10.4, 4150 (54 left) 17.2 / 19.8; w = 10, 512 tiles 5.8 / 6.9, 900 7.9 / 7.2, 2100 (52 left) 10.8 / 13.4.
+// Three quarters' time (1700 tiles by quarters: 10.1 / 10.3) no longer pays.
+constexpr uint64_t kSimds = 1024, kSplitMost = 512;
+
+// HB_SMALL_TILE_LIMIT in the environment (read once) overrides the limit; 0 switches the quarters off.
+uint64_t small_tile_limit()
+{
+    static const uint64_t limit = [] {
+        const char *v = std::getenv("HB_SMALL_TILE_LIMIT");
+        return v != nullptr ? (uint64_t)std::strtoull(v, nullptr, 10) : (uint64_t)900;
+    }();
+    return limit;
+}
+
+TileGrid tile_grid(uint64_t tiles, int w)
+{
+    const uint64_t limit = small_tile_limit(), left = tiles % kSimds;
+    uint64_t split = 0;
+    if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= kSplitMost ? left : 0;
+    const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
+    if (blocks > 0x7fffffffull) return TileGrid{0, 0, false};
+    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0};
 }
 
 bool force_group_kernel()

@@ -188,6 +188,7 @@ __device__ __forceinline__ void wave_sync()
 constexpr int tile_lanes_per_word(int w) { return 64 / w > 32 ? 32 : 64 / w; }
 constexpr int tile_groups(int w) { return tile_lanes_per_word(w) > 16 ? 32 : 64; }
 constexpr int tile_elements(int w) { return tile_groups(w) * tile_lanes_per_word(w); }
+constexpr bool quarters_supported(int w) { return w >= 4 && w <= 32; }      // a tile of 64 groups splits into quarters of 16
 
 template <int W>
 struct TileTraits {
@@ -203,24 +204,80 @@ struct TileTraits {
     using Item = typename std::conditional<(W == 4), uint8_t,
                  typename std::conditional<(W == 8), uint16_t,
                  typename std::conditional<(W == 16), uint32_t, uint64_t>::type>::type>::type;
-    static constexpr int kHalf = (W <= 16) ? 16 : 32;           // bits per party inside an unpacked LDS entry
+};
+
+// Where the owners of GROUPS groups leave the slices of their elements for the group lanes, one of three ways:
+//   packed widths        the pair's two fields of a party as an item of that group's word of that party
+//   L even, 2W <= 32     one 64-bit entry per pair, party 0's two fields in the lower half and party 1's in the upper,
+//                        which a group lane puts in place with one shift (an entry per element took twice the reads and
+//                        three times the instructions)
+//   other widths         one entry per element, both parties' fields in it
+template <int W, int GROUPS>
+struct Slices {
+    using T = TileTraits<W>;
+    using S = Shape<W>;
+    static constexpr int L = T::L;
+    static constexpr bool kPairEntries = !T::kPacked && L % 2 == 0 && 2 * W <= 32;
+    static constexpr int kHalf = (W <= 16) ? 16 : 32;           // bits per party inside an element's entry
     using Entry = typename std::conditional<(W <= 16), uint32_t, uint64_t>::type;
-    // LDS bytes per wavefront for the slices
-    static constexpr int kSliceBytes = kPacked ? 2 * kWave * 8 : kTile * (int)sizeof(Entry);
+    static constexpr int kBytes = T::kPacked ? 2 * GROUPS * 8 : (GROUPS * L * (int)sizeof(Entry) + 15) / 16 * 16;
+
+    static __device__ __forceinline__ uint64_t field(uint64_t x, int k) { return (x >> k) & S::kField; }
+    static __device__ __forceinline__ void deposit(unsigned char *lds, int pr, U64x2 xa, U64x2 xb, int k)
+    {
+        if constexpr (T::kPacked) {
+            using Item = typename T::Item;
+            reinterpret_cast<Item *>(lds)[pr] = (Item)(field(xa.a, k) | (field(xa.b, k) << (W % 64)));
+            reinterpret_cast<Item *>(lds + GROUPS * 8)[pr] = (Item)(field(xb.a, k) | (field(xb.b, k) << (W % 64)));
+        } else if constexpr (kPairEntries) {
+            const uint32_t a = (uint32_t)field(xa.a, k) | ((uint32_t)field(xa.b, k) << (W % 32));
+            const uint32_t b = (uint32_t)field(xb.a, k) | ((uint32_t)field(xb.b, k) << (W % 32));
+            reinterpret_cast<uint64_t *>(lds)[pr] = ((uint64_t)b << 32) | a;
+        } else {
+            Entry *slices = reinterpret_cast<Entry *>(lds);
+            slices[2 * pr] = (Entry)field(xa.a, k) | ((Entry)field(xb.a, k) << kHalf);
+            slices[2 * pr + 1] = (Entry)field(xa.b, k) | ((Entry)field(xb.b, k) << kHalf);
+        }
+    }
+    static __device__ __forceinline__ Pair collect(const unsigned char *lds, int grp)
+    {
+        Pair u{0, 0};
+        if constexpr (T::kPacked) {
+            u.p0 = reinterpret_cast<const uint64_t *>(lds)[grp];
+            u.p1 = reinterpret_cast<const uint64_t *>(lds + GROUPS * 8)[grp];
+        } else if constexpr (kPairEntries) {
+            const uint64_t *pairs = reinterpret_cast<const uint64_t *>(lds) + grp * (L / 2);
+#pragma unroll
+            for (int i = 0; i < L / 2; ++i) {
+                u.p0 |= lo_word(pairs[i]) << (2 * W * i);
+                u.p1 |= (pairs[i] >> 32) << (2 * W * i);
+            }
+        } else {
+            const Entry *slices = reinterpret_cast<const Entry *>(lds) + grp * L;
+#pragma unroll
+            for (int j = 0; j < L; ++j) {
+                const Entry en = slices[j];
+                u.p0 |= (uint64_t)(en & (Entry)S::kField) << (j * W);
+                u.p1 |= (uint64_t)(en >> kHalf) << (j * W);
+            }
+        }
+        return u;
+    }
+    static __device__ __forceinline__ uint64_t lo_word(uint64_t v) { return (uint32_t)v; }
 };
 
 // ---- what a group lane publishes for the owners of its elements -------------------------------------------------
-// DReLU / ReLU: the opened bit z and the dealer's bit r of every element (B2aBits), formed for all L fields at once.
-// Where a pair of fields is an LDS item (kPacked), z of field j sits at bit jW and r at bit jW + 1 of ONE word, so an
-// owner reads its pair's item and takes four bits at constant places; other widths publish {z at bit jW, r at bit 2j}
-// in two words, which an owner shifts once per pair.  Publishing the sign shares and the dealer word as they were, for
-// every owner to decode with its own shifts, took about ten more instructions per element.
-// Sign shares: {party 0, party 1}, field j at bit jW.
+// Two bits per element: the opened bit z and the dealer's bit r (B2aBits), or the two parties' sign shares.  Where a pair
+// of fields is an LDS item (kPacked) they sit at bits jW and jW + 1 of one word per group, other widths publish a byte
+// per element.  Either way an owner reads its pair's item at its pair's index and takes four bits at constant places.
+// (Publishing two words per group, for every owner to find its group and shift by its field's place, took 14 more vector
+// instructions per pair in the widths that are not packed.)
 template <int W, int MODE>
 struct Verdict {
     using T = TileTraits<W>;
-    static constexpr bool kOneWord = T::kPacked && op_of(MODE) != kSign;
-    using Word = typename std::conditional<kOneWord, uint64_t, U64x2>::type;
+    using S = Shape<W>;
+    static constexpr bool kSigns = op_of(MODE) == kSign;
+    static constexpr int bytes(int groups) { return T::kPacked ? 8 * groups : (groups * T::L + 15) / 16 * 16; }
 
     // bit 2j -> bit jW, for the packed widths
     static __device__ __forceinline__ uint32_t spread_half(uint32_t v)
@@ -239,78 +296,81 @@ struct Verdict {
             return ((v & kIn) * kMoves) & kOut;
         }
     }
-    static __device__ __forceinline__ Word make(Pair sum, uint64_t wb)
+    template <class Word>
+    static __device__ __forceinline__ Word spread(uint64_t v)
     {
-        using S = Shape<W>;
-        if constexpr (op_of(MODE) == kSign) {
-            return U64x2{(sum.p0 >> (W - 1)) & S::ones(), (sum.p1 >> (W - 1)) & S::ones()};
-        } else {
-            const uint64_t sx = (sum.p0 ^ sum.p1) >> (W - 1);      // bit jW: sign_0 ^ sign_1
-            const uint64_t rx = wb ^ (wb >> 1);                    // bit 2j: r
-            if constexpr (kOneWord) {
-                constexpr int kHalfFields = 32 / W;
-                const uint64_t r = ((uint64_t)spread_half((uint32_t)(rx >> (2 * kHalfFields))) << 32) | spread_half((uint32_t)rx);
-                return bitop3<kTtAndXor>(S::ones(), sx, r) | (r << 1);
+        if constexpr (sizeof(Word) == 4) return spread_half((uint32_t)v);
+        else return ((uint64_t)spread_half((uint32_t)(v >> (2 * (32 / W)))) << 32) | spread_half((uint32_t)v);
+    }
+    static __device__ __forceinline__ uint32_t bit_at(uint64_t v, int at)
+    {
+        return at < 32 ? __builtin_amdgcn_ubfe((uint32_t)v, at, 1) : __builtin_amdgcn_ubfe((uint32_t)(v >> 32), at - 32, 1);
+    }
+    // The FIELDS fields of one word of the circuit's sum; `slot`: number of the word in the tile.  wb: the group's B2A
+    // word with the bits of the first of these fields at 0 and 1.
+    template <class Word, int FIELDS>
+    static __device__ __forceinline__ void publish(unsigned char *lds, int slot, WordPair<Word> sum, uint64_t wb)
+    {
+        const Word s0 = sum.p0 >> (W - 1), s1 = sum.p1 >> (W - 1), sx = (sum.p0 ^ sum.p1) >> (W - 1);     // field j: bit jW
+        const uint64_t rx = wb ^ (wb >> 1);                                                              // bit 2j: r
+        if constexpr (T::kPacked) {
+            constexpr Word ones = (Word)S::ones();
+            Word v;
+            if constexpr (kSigns) {
+                v = (s0 & ones) | ((s1 & ones) << 1);
             } else {
-                return U64x2{sx, rx};                              // z of field j: bit jW of sx ^ bit 2j of rx
+                const Word r = spread<Word>(rx);
+                v = bitop3<kTtAndXor>(ones, sx, r) | (r << 1);
             }
-        }
-    }
-    // The two elements of pair `pr` (first one: element `e` = 2 pr of the tile).
-    static __device__ __forceinline__ void pick(const unsigned char *lds, int pr, int e, B2aBits (&t)[2])
-    {
-        if constexpr (kOneWord) {
-            const typename T::Item it = reinterpret_cast<const typename T::Item *>(lds)[pr];
-            constexpr int kSecond = W % 32;                // place of the second field in `hi`
-            const uint32_t lo = (uint32_t)it, hi = W == 32 ? (uint32_t)((uint64_t)it >> 32) : lo;
-            t[0] = B2aBits{minus_bit(lo, 0), __builtin_amdgcn_ubfe(lo, 1, 1)};
-            t[1] = B2aBits{minus_bit(hi, kSecond), __builtin_amdgcn_ubfe(hi, kSecond + 1, 1)};
+            reinterpret_cast<Word *>(lds)[slot] = v;
         } else {
-            constexpr int L = T::L;
-            const U64x2 *verdict = reinterpret_cast<const U64x2 *>(lds);
-            const int grp = e / L, j = e - grp * L;
-            const U64x2 v = verdict[grp];
-            const uint64_t sx = v.a >> (j * W);
-            const uint32_t rx = (uint32_t)(v.b >> (2 * j));
-            t[0].r = rx & 1u;
-            t[0].m = minus_bit((uint32_t)sx ^ rx, 0);
-            // both elements of the pair sit in one group unless L is odd and the pair straddles two
-            uint32_t s1 = (uint32_t)(sx >> W), r1 = rx >> 2;
-            if constexpr (L % 2 != 0) {
-                const bool split = (j == L - 1);
-                const U64x2 v1 = verdict[split ? grp + 1 : grp];
-                if (split) {
-                    s1 = (uint32_t)v1.a;
-                    r1 = (uint32_t)v1.b;
-                }
+            const uint64_t r = rx & 0x5555555555555555ull, rr = r | (r << 1);
+#pragma unroll
+            for (int j = 0; j < FIELDS; ++j) {
+                // bits above the two are never looked at
+                const uint32_t v = kSigns ? bit_at(s0, j * W) | (bit_at(s1, j * W) << 1) : bit_at(sx, j * W) ^ (uint32_t)(rr >> (2 * j));
+                lds[slot * FIELDS + j] = (unsigned char)v;
             }
-            t[1].r = r1 & 1u;
-            t[1].m = minus_bit(s1 ^ r1, 0);
         }
     }
-    static __device__ __forceinline__ void pick_signs(const unsigned char *lds, int e, Pair (&sign)[2])
+    // What pair `pr` of the tile reads: its first element's bits at 0 and 1 of `lo`, its second's at kSecond of `hi`.
+    static constexpr int kSecond = T::kPacked ? W % 32 : 8;
+    static __device__ __forceinline__ void read(const unsigned char *lds, int pr, uint32_t &lo, uint32_t &hi)
     {
-        constexpr int L = T::L;
-        const U64x2 *verdict = reinterpret_cast<const U64x2 *>(lds);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int grp = (e + h) / L, j = (e + h) - grp * L;
-            const U64x2 v = verdict[grp];
-            sign[h] = Pair{(v.a >> (j * W)) & 1u, (v.b >> (j * W)) & 1u};
+        if constexpr (T::kPacked) {
+            const typename T::Item it = reinterpret_cast<const typename T::Item *>(lds)[pr];
+            lo = (uint32_t)it;
+            hi = W == 32 ? (uint32_t)((uint64_t)it >> 32) : lo;
+        } else {
+            lo = hi = reinterpret_cast<const uint16_t *>(lds)[pr];
         }
+    }
+    static __device__ __forceinline__ void pick(const unsigned char *lds, int pr, B2aBits (&t)[2])
+    {
+        uint32_t lo, hi;
+        read(lds, pr, lo, hi);
+        t[0] = B2aBits{minus_bit(lo, 0), __builtin_amdgcn_ubfe(lo, 1, 1)};
+        t[1] = B2aBits{minus_bit(hi, kSecond), __builtin_amdgcn_ubfe(hi, kSecond + 1, 1)};
+    }
+    static __device__ __forceinline__ void pick_signs(const unsigned char *lds, int pr, Pair (&sign)[2])
+    {
+        uint32_t lo, hi;
+        read(lds, pr, lo, hi);
+        sign[0] = Pair{__builtin_amdgcn_ubfe(lo, 0, 1), __builtin_amdgcn_ubfe(lo, 1, 1)};
+        sign[1] = Pair{__builtin_amdgcn_ubfe(hi, kSecond, 1), __builtin_amdgcn_ubfe(hi, kSecond + 1, 1)};
     }
 };
 
 // The owner's part for one pair: what `io` stores for elements e, e + 1 of the tile.
 template <int W, int MODE>
-__device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr, int e, U64x2 xa, U64x2 xb, uint64_t zA, Pair (&r)[2])
+__device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr, U64x2 xa, U64x2 xb, uint64_t zA, Pair (&r)[2])
 {
     using V = Verdict<W, MODE>;
     if constexpr (op_of(MODE) == kSign) {
-        V::pick_signs(verdict, e, r);
+        V::pick_signs(verdict, pr, r);
     } else {
         B2aBits t[2];
-        V::pick(verdict, pr, e, t);
+        V::pick(verdict, pr, t);
         r[0] = op_of(MODE) == kDrelu ? b2a_drelu(t[0], zA) : b2a_mul(t[0], Pair{xa.a, xb.a}, zA);
         r[1] = op_of(MODE) == kDrelu ? b2a_drelu(t[1], zA + 6 * kGamma) : b2a_mul(t[1], Pair{xa.b, xb.b}, zA + 6 * kGamma);
     }
@@ -412,17 +472,18 @@ struct FloatIO {
     }
 };
 
-// Work of one wavefront on wave-tile `tile` of one tensor.  slice_lds / verdict: this wave's LDS.  FULL: the
-// whole tile lies inside the tensor, so no access needs a bounds check (every tile but a tensor's last).
+// Work of one wavefront on wave-tile `tile` of one tensor.  lds: this wave's LDS.  FULL: the whole tile lies inside the
+// tensor, so no access needs a bounds check (every tile but a tensor's last).
 template <int W, int MODE, bool FULL, class IO>
 __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                               uint64_t tile, int lane, unsigned char *slice_lds, unsigned char *verdict)
+                                               uint64_t tile, int lane, unsigned char *lds)
 {
     using T = TileTraits<W>;
     using S = Shape<W>;
-    constexpr int L = T::L;
+    using Sl = Slices<W, T::kGroups>;
     static_assert(T::kSupported, "tile kernel needs W <= 32");
     const uint64_t tile0 = tile * T::kTile;
+    unsigned char *verdict = lds + Sl::kBytes;
 
     // ---- owners: load, slice, deposit -------------------------------------------------------
     U64x2 xa[T::kPairs], xb[T::kPairs];
@@ -434,45 +495,20 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         xb[c] = U64x2{0, 0};
         if (e < T::kTile) {
             io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
-            if constexpr (T::kPacked) {
-                // the pair's two fields of party 0 / party 1, already at their place relative to the pair
-                using Item = typename T::Item;
-                Item *w0 = reinterpret_cast<Item *>(slice_lds);
-                Item *w1 = reinterpret_cast<Item *>(slice_lds + kWave * 8);
-                w0[pr] = (Item)(((xa[c].a >> k) & S::kField) | (((xa[c].b >> k) & S::kField) << (W % 64)));
-                w1[pr] = (Item)(((xb[c].a >> k) & S::kField) | (((xb[c].b >> k) & S::kField) << (W % 64)));
-            } else {
-                using Entry = typename T::Entry;
-                Entry *slices = reinterpret_cast<Entry *>(slice_lds);
-                slices[e] = (Entry)((xa[c].a >> k) & S::kField) | ((Entry)((xb[c].a >> k) & S::kField) << T::kHalf);
-                slices[e + 1] = (Entry)((xa[c].b >> k) & S::kField) | ((Entry)((xb[c].b >> k) & S::kField) << T::kHalf);
-            }
+            Sl::deposit(lds, pr, xa[c], xb[c], k);
         }
     }
     wave_sync();
 
     // ---- group lanes: collect fields, run the circuit, publish the verdict ----------------------
     if (T::kGroups == kWave || lane < T::kGroups) {
-        uint64_t u0 = 0, u1 = 0;
-        if constexpr (T::kPacked) {
-            u0 = reinterpret_cast<const uint64_t *>(slice_lds)[lane];
-            u1 = reinterpret_cast<const uint64_t *>(slice_lds + kWave * 8)[lane];
-        } else {
-            using Entry = typename T::Entry;
-            const Entry *slices = reinterpret_cast<const Entry *>(slice_lds);
-#pragma unroll
-            for (int j = 0; j < L; ++j) {
-                const Entry en = slices[lane * L + j];
-                u0 |= (uint64_t)(en & (Entry)S::kField) << (j * W);
-                u1 |= (uint64_t)(en >> T::kHalf) << (j * W);
-            }
-        }
+        const Pair u = Sl::collect(lds, lane);
         const uint64_t g = tile * T::kGroups + lane;
         const uint64_t zg = seedB + (g * (uint64_t)S::words_per_group(shared_of(MODE)) + 1) * kGamma;
-        const Pair sum = a2b_sum<W, shared_of(MODE)>(u0, u1, zg);
+        const Pair sum = a2b_sum<W, shared_of(MODE)>(u.p0, u.p1, zg);
         uint64_t wb = 0;
         if (op_of(MODE) != kSign) wb = mix64(zg + (uint64_t)S::b2a_word(shared_of(MODE)) * kGamma);
-        reinterpret_cast<typename Verdict<W, MODE>::Word *>(verdict)[lane] = Verdict<W, MODE>::make(sum, wb);
+        Verdict<W, MODE>::template publish<uint64_t, T::L>(verdict, lane, sum, wb);
     }
     wave_sync();
 
@@ -483,179 +519,125 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         const int pr = c * kWave + lane, e = 2 * pr;
         if (e < T::kTile) {
             Pair r[2];
-            finish_pair<W, MODE>(verdict, pr, e, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
+            finish_pair<W, MODE>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
 }
 
-// `tile` must be uniform over the wavefront (callers derive it from wave_index()).
-template <int W, int MODE, class IO>
-__device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                          uint64_t tile, int lane, unsigned char *slice_lds, unsigned char *verdict)
-{
-    if ((tile + 1) * TileTraits<W>::kTile <= n)
-        tile_body_impl<W, MODE, true>(io, n, k, seedB, seedA, tile, lane, slice_lds, verdict);
-    else
-        tile_body_impl<W, MODE, false>(io, n, k, seedB, seedA, tile, lane, slice_lds, verdict);
-}
-
-// The wavefront's number inside its workgroup, as a scalar: everything derived from it (tile number, tensor
-// descriptor, base addresses) then stays in scalar registers.
-__device__ __forceinline__ int wave_index()
-{
-    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-}
-
+// ---- a quarter of a tile per wavefront ----------------------------------------------------------------------------
+// A launch with few tiles lasts as long as one wavefront's instruction stream (about 2000 vector instructions at w = 8,
+// most of it dealer words), and so does the last round of any launch.  Here the four wavefronts of a workgroup share one
+// tile, 16 groups each.  The four lanes of a group draw every fourth dealer word of the group each and hand them to one
+// another through LDS; where the fields of a word split into two halves (L even) lanes then evaluate the gate logic on
+// one half, 32 bits, which halves it.  Owners finish one element pair per lane (at w = 8) instead of four.  Same dealer
+// indices, same results; about a third of the tile's instructions per wavefront, 1.25 times the tile's in all, so this
+// form takes only what cannot fill the chip (tile_grid).  4 <= w <= 32.
 template <int W, int MODE>
-__global__ void __launch_bounds__(kBlock)
-tile_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t *o0,
-            uint64_t *o1)
-{
-    using T = TileTraits<W>;
-    __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, MODE>::Word)];
-    const int lane = threadIdx.x % kWave, wv = wave_index();
-    const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
-    if (tile * T::kTile >= n) return;        // whole wavefront beyond the tensor (uniform per wave)
-    tile_body<W, MODE>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, tile, lane, slices_all[wv], verdict_all[wv]);
-}
-
-// Several tensors of one slice width in a single launch.  The descriptors travel in the kernel
-// argument block; wave-tiles of all tensors are numbered consecutively and tile_end[t] is the number
-// of wave-tiles in tensors 0..t.
-constexpr int kBatchMax = 24;
-
-struct BatchTensor {
-    const uint64_t *x0, *x1;
-    uint64_t *o0, *o1;
-    uint64_t n, seedB, seedA;
-    int k, pad;
-};
-
-struct BatchArgs {
-    int count, pad;
-    uint64_t tile_end[kBatchMax];
-    BatchTensor t[kBatchMax];
-};
-
-template <int W, int MODE>
-__global__ void __launch_bounds__(kBlock)
-tile_batch_kernel(const BatchArgs args)
-{
-    using T = TileTraits<W>;
-    __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, MODE>::Word)];
-    const int lane = threadIdx.x % kWave, wv = wave_index();
-    const uint64_t gt = (uint64_t)blockIdx.x * kWavesPerBlock + wv;          // wave-tile number over the whole batch
-    if (gt >= args.tile_end[args.count - 1]) return;
-    int ti = 0;
-    while (gt >= args.tile_end[ti]) ++ti;                                     // uniform per wave, at most kBatchMax steps
-    const uint64_t tile = gt - (ti ? args.tile_end[ti - 1] : 0);
-    const BatchTensor &d = args.t[ti];
-    tile_body<W, MODE>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, tile, lane, slices_all[wv], verdict_all[wv]);
-}
-
-// ------------------------------------------------------------------------------------------------
-// Small wave-tile (short tensors): 16 groups per wavefront and four lanes per group.
-//
-// When a launch has fewer wave-tiles than the chip has SIMDs, its duration is one wavefront's serial instruction
-// stream (about 2000 vector instructions at w = 8), most of it dealer words.  Here a wavefront takes a quarter of
-// the elements and the four lanes of a group split the group's dealer words between them (every fourth word
-// each), hand them to one another through LDS, and all evaluate the (short) gate logic; owners then finish one
-// element pair per lane (at w = 8) instead of four.  Same dealer indices, same results; about a third of the
-// serial work per wavefront, about 1.25 times the total work, so this form is used only for launches that
-// cannot fill the chip.  Standard dealer layout, DReLU and ReLU, 4 <= w <= 32.
-// ------------------------------------------------------------------------------------------------
-template <int W>
-struct SmallTraits {
+struct QuarterTraits {
     using S = Shape<W>;
     using T = TileTraits<W>;
     static constexpr int L = S::L;
-    static constexpr bool kSupported = T::kSupported && (W >= 4);
+    static constexpr bool kSupported = quarters_supported(W);
+    static constexpr bool kShared = shared_of(MODE);
     static constexpr int kSplit = 4;                            // lanes per group
     static constexpr int kGroups = kWave / kSplit;              // groups per wavefront
     static constexpr int kTile = kGroups * L;                   // elements per wavefront
     static constexpr int kPairs = (kTile / 2 + kWave - 1) / kWave;
-    static constexpr int kWords = 10 * S::R + 1;                // evaluated dealer words of a group: 2R gates + B2A
+    static constexpr bool kHalves = (L % 2 == 0);
+    using Word = typename std::conditional<kHalves, uint32_t, uint64_t>::type;
+    static constexpr int kFields = kHalves ? L / 2 : L;         // fields of a Word
+    // evaluated dealer words of a group: those of all gates but the last P-update, then the B2A word
+    static constexpr int kGateWords = S::b2a_word(kShared) - (kShared ? 3 : 5);
+    static constexpr bool kHasB2a = op_of(MODE) != kSign;
+    static constexpr int kWords = kGateWords + (kHasB2a ? 1 : 0);
     static constexpr int kWordsPerLane = (kWords + kSplit - 1) / kSplit;
-    // words of LDS per group: a multiple of 32 words plus 2, so that the 16 groups' 16-byte reads of one word
-    // fall into 16 different sets of four banks (and the stride stays a 16-byte multiple)
-    static constexpr int kStride = ((kWords + 31) / 32) * 32 + 2;
-    static constexpr int kSliceBytes = T::kPacked ? 2 * kGroups * 8 : kTile * (int)sizeof(typename T::Entry);
+    // A group's row in LDS, in 32-bit units: the lower halves of its words, then the upper ones (whole words where fields
+    // do not split).  An odd multiple of four, so that the 16-byte reads of 16 rows fall into different sets of banks.
+    static constexpr int kPad = (kWords + 3) / 4 * 4;
+    static constexpr int kRow = 2 * kPad + 4;
+    using Sl = Slices<W, kGroups>;
+    static constexpr int kWordsAt = Sl::kBytes, kVerdictAt = kWordsAt + kGroups * kRow * 4;
+    static constexpr int kLdsBytes = kVerdictAt + Verdict<W, MODE>::bytes(kGroups);
 };
 
-constexpr int small_tile_elements(int w) { return 16 * tile_lanes_per_word(w); }
-
-template <int W, int MODE, bool FULL>
-__device__ __forceinline__ void small_tile_body_impl(const ShareIO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                                     uint64_t tile, int lane, unsigned char *slice_lds, uint64_t *words_lds,
-                                                     unsigned char *verdict)
+// Bits at .. at + 31 of v, 0 <= at <= 32, where `at` differs between lanes.  Not a 64-bit shift: with its amount in the last
+// vector register of the wavefront's allocation v_lshrrev_b64 has shifted by something else now and then (seen with the
+// amount in v63 of 64), and the compiler does not keep it from there.
+__device__ __forceinline__ uint32_t word_at(uint64_t v, int at)
 {
-    using T = TileTraits<W>;
-    using Q = SmallTraits<W>;
-    using S = Shape<W>;
-    constexpr int L = Q::L;
-    static_assert(Q::kSupported && !shared_of(MODE) && op_of(MODE) != kSign, "small tiles: standard layout, DReLU / ReLU");
-    const uint64_t tile0 = tile * Q::kTile;
+    const uint32_t low = __builtin_amdgcn_alignbit((uint32_t)(v >> 32), (uint32_t)v, (uint32_t)at);
+    return at >= 32 ? (uint32_t)(v >> 32) : low;
+}
 
-    // ---- owners: load, slice, deposit (as in the large tile, with 16 group words per party) ----------------
+template <int W, int MODE, bool FULL, class IO>
+__device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
+                                                  uint64_t quarter, int lane, unsigned char *lds)
+{
+    using Q = QuarterTraits<W, MODE>;
+    using S = Shape<W>;
+    using Sl = typename Q::Sl;
+    using Word = typename Q::Word;
+    const uint64_t tile0 = quarter * Q::kTile;
+    unsigned char *verdict = lds + Q::kVerdictAt;
+
+    // ---- owners: load ------------------------------------------------------------------------------------
     U64x2 xa[Q::kPairs], xb[Q::kPairs];
 #pragma unroll
     for (int c = 0; c < Q::kPairs; ++c) {
-        const int pr = c * kWave + lane;
-        const int e = 2 * pr;
+        const int e = 2 * (c * kWave + lane);
         xa[c] = U64x2{0, 0};
         xb[c] = U64x2{0, 0};
-        if (e < Q::kTile) {
-            io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
-            if constexpr (T::kPacked) {
-                using Item = typename T::Item;
-                Item *w0 = reinterpret_cast<Item *>(slice_lds);
-                Item *w1 = reinterpret_cast<Item *>(slice_lds + Q::kGroups * 8);
-                w0[pr] = (Item)(((xa[c].a >> k) & S::kField) | (((xa[c].b >> k) & S::kField) << (W % 64)));
-                w1[pr] = (Item)(((xb[c].a >> k) & S::kField) | (((xb[c].b >> k) & S::kField) << (W % 64)));
+        if (e < Q::kTile) io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
+    }
+
+    // ---- every lane, while the loads are under way: its share of the group's dealer words ------------------
+    const int grp = lane / Q::kSplit, sub = lane % Q::kSplit, half = sub % 2;
+    const uint64_t g = quarter * Q::kGroups + grp;
+    const uint64_t zs = seedB + (g * (uint64_t)S::words_per_group(Q::kShared) + 1 + (uint64_t)sub) * kGamma;
+    uint32_t *row = reinterpret_cast<uint32_t *>(lds + Q::kWordsAt) + grp * Q::kRow;
+#pragma unroll
+    for (int t = 0; t < Q::kWordsPerLane; ++t) {
+        const int j = t * Q::kSplit + sub;                      // word j of the group; the last one drawn is the B2A word
+        if (Q::kWords % Q::kSplit == 0 || t + 1 < Q::kWordsPerLane || j < Q::kWords) {
+            uint64_t z = zs + (uint64_t)(t * Q::kSplit) * kGamma;
+            int upper = Q::kFields * W;                         // place of the upper half's first field
+            if (Q::kHasB2a && t + 1 == Q::kWordsPerLane && j == Q::kWords - 1) {
+                z += (uint64_t)(S::b2a_word(Q::kShared) - Q::kGateWords) * kGamma;
+                upper = 2 * Q::kFields;
+            }
+            const uint64_t v = mix64(z);
+            if constexpr (Q::kHalves) {
+                row[j] = (uint32_t)v;
+                row[Q::kPad + j] = word_at(v, upper);
             } else {
-                using Entry = typename T::Entry;
-                Entry *slices = reinterpret_cast<Entry *>(slice_lds);
-                slices[e] = (Entry)((xa[c].a >> k) & S::kField) | ((Entry)((xb[c].a >> k) & S::kField) << T::kHalf);
-                slices[e + 1] = (Entry)((xa[c].b >> k) & S::kField) | ((Entry)((xb[c].b >> k) & S::kField) << T::kHalf);
+                reinterpret_cast<uint64_t *>(row)[j] = v;
             }
         }
     }
 
-    // ---- every lane: its share of the group's dealer words -------------------------------------------------
-    const int grp = lane / Q::kSplit, sub = lane % Q::kSplit;
-    const uint64_t g = tile * Q::kGroups + grp;
-    const uint64_t zg = seedB + (g * (uint64_t)S::words_per_group(false) + 1) * kGamma;
-    uint64_t *gw = words_lds + grp * Q::kStride;
+    // ---- owners: slice, deposit ---------------------------------------------------------------------------
 #pragma unroll
-    for (int t = 0; t < Q::kWordsPerLane; ++t) {
-        const int j = t * Q::kSplit + sub;                      // j-th evaluated word: stream index j, the B2A word last
-        if (Q::kWords % Q::kSplit == 0 || t + 1 < Q::kWordsPerLane || j < Q::kWords) {
-            const unsigned idx = (j == Q::kWords - 1) ? (unsigned)S::b2a_word(false) : (unsigned)j;
-            gw[j] = mix64(zg + (uint64_t)idx * kGamma);
-        }
+    for (int c = 0; c < Q::kPairs; ++c) {
+        const int pr = c * kWave + lane;
+        if (2 * pr < Q::kTile) Sl::deposit(lds, pr, xa[c], xb[c], k);
     }
     wave_sync();
 
-    // ---- every lane: collect the fields of its group, run the gate logic on the exchanged words ------------
-    uint64_t u0 = 0, u1 = 0;
-    if constexpr (T::kPacked) {
-        u0 = reinterpret_cast<const uint64_t *>(slice_lds)[grp];
-        u1 = reinterpret_cast<const uint64_t *>(slice_lds + Q::kGroups * 8)[grp];
-    } else {
-        using Entry = typename T::Entry;
-        const Entry *slices = reinterpret_cast<const Entry *>(slice_lds);
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-            const Entry en = slices[grp * L + j];
-            u0 |= (uint64_t)(en & (Entry)S::kField) << (j * W);
-            u1 |= (uint64_t)(en >> T::kHalf) << (j * W);
+    // ---- every lane: the gate logic of its group, or of its half of the fields ------------------------------
+    {
+        const Pair u = Sl::collect(lds, grp);
+        const Word *words = reinterpret_cast<const Word *>(row + (Q::kHalves ? half * Q::kPad : 0));
+        WordPair<Word> v{(Word)u.p0, (Word)u.p1};
+        if constexpr (Q::kHalves) {
+            const int shift = half * (Q::kFields * W);
+            v = WordPair<Word>{word_at(u.p0, shift), word_at(u.p1, shift)};
         }
+        const WordPair<Word> sum = a2b_sum_words<W, Q::kShared, Word>(v.p0, v.p1, words);
+        const uint64_t wb = Q::kHasB2a ? words[Q::kWords - 1] : 0;
+        if (sub < (Q::kHalves ? 2 : 1))
+            Verdict<W, MODE>::template publish<Word, Q::kFields>(verdict, Q::kHalves ? 2 * grp + half : grp, sum, wb);
     }
-    const Pair sum = a2b_sum_words<W>(u0, u1, gw);
-    if (sub == 0) reinterpret_cast<typename Verdict<W, MODE>::Word *>(verdict)[grp] = Verdict<W, MODE>::make(sum, gw[Q::kWords - 1]);
     wave_sync();
 
     // ---- owners: pick up the verdict of each element's group, finish, store -------------------------------
@@ -665,35 +647,123 @@ __device__ __forceinline__ void small_tile_body_impl(const ShareIO &io, uint64_t
         const int pr = c * kWave + lane, e = 2 * pr;
         if (e < Q::kTile) {
             Pair r[2];
-            finish_pair<W, MODE>(verdict, pr, e, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
+            finish_pair<W, MODE>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
 }
 
-// Several tensors of one slice width on small wave-tiles; tile_end counts small tiles.
+// LDS of a workgroup.  It is allocated at launch, so that a launch without quarters, whose rows of dealer words are the
+// larger part, keeps room for more workgroups per compute unit.
+template <int W, int MODE>
+constexpr int whole_lds_bytes()
+{
+    return Slices<W, tile_groups(W)>::kBytes + Verdict<W, MODE>::bytes(tile_groups(W));      // of a wavefront
+}
+template <int W, int MODE>
+constexpr unsigned tile_lds_bytes(bool quarters)
+{
+    int most = whole_lds_bytes<W, MODE>();
+    if constexpr (quarters_supported(W)) {
+        if (quarters && QuarterTraits<W, MODE>::kLdsBytes > most) most = QuarterTraits<W, MODE>::kLdsBytes;
+    }
+    return (unsigned)(kWavesPerBlock * most);
+}
+
+// The wavefront's number inside its workgroup, as a scalar: everything derived from it (tile number, tensor
+// descriptor, base addresses) then stays in scalar registers.
+__device__ __forceinline__ int wave_index()
+{
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+}
+
+// Which part of a launch a wavefront takes: workgroups 0 .. whole_blocks - 1 take four tiles each, the others one tile each.
+struct TileWork {
+    uint64_t tile;
+    int quarter;        // -1: the whole tile
+};
+template <int W>
+__device__ __forceinline__ TileWork tile_work(uint32_t whole_blocks, int wv)
+{
+    const uint32_t b = blockIdx.x;
+    const bool split = quarters_supported(W) && b >= whole_blocks;
+    return TileWork{split ? (uint64_t)whole_blocks * (kWavesPerBlock - 1) + b : (uint64_t)b * kWavesPerBlock + wv, split ? wv : -1};
+}
+
+// t.tile must be uniform over the wavefront; the tile lies inside the tensor at least in part.
+template <int W, int MODE, class IO>
+__device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA, TileWork t, int lane, int wv,
+                                          unsigned char *tile_lds)
+{
+    if constexpr (quarters_supported(W)) {
+        if (t.quarter >= 0) {
+            using Q = QuarterTraits<W, MODE>;
+            const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
+            unsigned char *lds = tile_lds + wv * Q::kLdsBytes;
+            if ((quarter + 1) * Q::kTile <= n)
+                quarter_body_impl<W, MODE, true>(io, n, k, seedB, seedA, quarter, lane, lds);
+            else if (quarter * Q::kTile < n)
+                quarter_body_impl<W, MODE, false>(io, n, k, seedB, seedA, quarter, lane, lds);
+            return;
+        }
+    }
+    unsigned char *lds = tile_lds + wv * whole_lds_bytes<W, MODE>();
+    if ((t.tile + 1) * TileTraits<W>::kTile <= n)
+        tile_body_impl<W, MODE, true>(io, n, k, seedB, seedA, t.tile, lane, lds);
+    else
+        tile_body_impl<W, MODE, false>(io, n, k, seedB, seedA, t.tile, lane, lds);
+}
+
 template <int W, int MODE>
 __global__ void __launch_bounds__(kBlock)
-small_batch_kernel(const BatchArgs args)
+tile_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t *o0,
+            uint64_t *o1, uint32_t whole_blocks)
 {
-    using T = TileTraits<W>;
-    using Q = SmallTraits<W>;
-    __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][Q::kSliceBytes];
-    __shared__ __attribute__((aligned(16))) uint64_t words_all[kWavesPerBlock][Q::kGroups * Q::kStride];
-    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][Q::kGroups * sizeof(typename Verdict<W, MODE>::Word)];
+    extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const uint64_t gt = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
-    if (gt >= args.tile_end[args.count - 1]) return;
+    const TileWork t = tile_work<W>(whole_blocks, wv);
+    if (t.tile * TileTraits<W>::kTile >= n) return;        // whole wavefront beyond the tensor (uniform per wave)
+    tile_body<W, MODE>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, t, lane, wv, tile_lds);
+}
+
+// Several tensors of one slice width in a single launch.  The descriptors travel in the kernel
+// argument block; wave-tiles of all tensors are numbered consecutively and tile_end[t] is the number
+// of wave-tiles in tensors 0..t, kNoTile from the last tensor on: a tile's tensor is then the number of entries that do not
+// exceed the tile's number, which takes one load of the whole table instead of a chain of loads, one tensor after the other.
+constexpr int kBatchMax = 24;
+constexpr uint32_t kNoTile = 0x7fffffffu;
+
+struct BatchTensor {
+    const uint64_t *x0, *x1;
+    uint64_t *o0, *o1;
+    uint64_t n, seedB, seedA;
+    int k;
+    uint32_t first_tile;
+};
+
+struct BatchArgs {
+    uint32_t whole_blocks;             // tile_grid of all tensors' tiles
+    uint32_t tiles;                    // of all tensors
+    uint32_t tile_end[kBatchMax];
+    BatchTensor t[kBatchMax];
+    int count;
+};
+
+template <int W, int MODE>
+__global__ void __launch_bounds__(kBlock)
+tile_batch_kernel(const BatchArgs args)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
+    const int lane = threadIdx.x % kWave, wv = wave_index();
+    TileWork t = tile_work<W>(args.whole_blocks, wv);                          // tile number over the whole batch
+    const uint32_t gt = (uint32_t)t.tile;                                      // below 2^31 + 4
+    if (gt >= args.tiles) return;
     int ti = 0;
-    while (gt >= args.tile_end[ti]) ++ti;
-    const uint64_t tile = gt - (ti ? args.tile_end[ti - 1] : 0);
-    const BatchTensor &d = args.t[ti];
-    const ShareIO io{d.x0, d.x1, d.o0, d.o1};
-    if ((tile + 1) * Q::kTile <= d.n)
-        small_tile_body_impl<W, MODE, true>(io, d.n, d.k, d.seedB, d.seedA, tile, lane, slices_all[wv], words_all[wv], verdict_all[wv]);
-    else
-        small_tile_body_impl<W, MODE, false>(io, d.n, d.k, d.seedB, d.seedA, tile, lane, slices_all[wv], words_all[wv], verdict_all[wv]);
-    (void)sizeof(T);
+#pragma unroll
+    for (int i = 0; i < kBatchMax; ++i) ti += (int)((args.tile_end[i] - 1 - gt) >> 31);   // scalar: the borrow, not a comparison
+    const BatchTensor &d = args.t[__builtin_amdgcn_readfirstlane(ti)];
+    t.tile = gt - d.first_tile;
+    tile_body<W, MODE>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, t, lane, wv, tile_lds);
 }
 
 // The simulator kernel: ReLU on plaintext floats through the whole protocol, 8 bytes of traffic per element.
@@ -717,15 +787,13 @@ wide_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seed
 
 template <int W>
 __global__ void __launch_bounds__(kBlock)
-tile_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t seedS, float *y)
+tile_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t seedS, float *y, uint32_t whole_blocks)
 {
-    using T = TileTraits<W>;
-    __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][T::kSliceBytes];
-    __shared__ __attribute__((aligned(16))) unsigned char verdict_all[kWavesPerBlock][kWave * sizeof(typename Verdict<W, kRelu>::Word)];
+    extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
-    if (tile * T::kTile >= n) return;
-    tile_body<W, kRelu>(FloatIO{x, y, seedS}, n, k, seedB, seedA, tile, lane, slices_all[wv], verdict_all[wv]);
+    const TileWork t = tile_work<W>(whole_blocks, wv);
+    if (t.tile * TileTraits<W>::kTile >= n) return;
+    tile_body<W, kRelu>(FloatIO{x, y, seedS}, n, k, seedB, seedA, t, lane, wv, tile_lds);
 }
 
 }  // namespace hb

@@ -32,13 +32,20 @@ using PartyLauncher = hipError_t (*)(const PartyCtx &c, hipStream_t stream);
 struct LauncherTable {
     GroupLauncher f[kModes][64];       // [mode][w - 1]
     BatchLauncher batch[kModes][64];   // null where the width has no tile kernel
-    BatchLauncher small[kModes][64];   // small wave-tiles (tile_end counts small tiles); null where there is none
     SimLauncher sim[64];               // null where the width has no tile kernel
     MpLauncher mp[kMaxParties - 2][2][64];   // [parties - 3][kDrelu | kRelu][w - 1]
     PartyLauncher party[2][64];        // [shared-mask layout][w - 1]
 };
 
 LauncherTable &launcher_table();
+
+// Grid of a launch of wave-tiles: `whole_blocks` workgroups of four tiles, then a workgroup for each of the tiles that
+// are shared out by quarters.
+struct TileGrid {
+    uint32_t whole_blocks, blocks;       // blocks 0: more than a grid holds
+    bool quarters;                       // blocks > whole_blocks
+};
+TileGrid tile_grid(uint64_t tiles, int w);
 
 // Debug knob: HB_KERNEL=group in the environment (read once) sends every width to the thread-per-group kernel.
 bool force_group_kernel();

@@ -19,11 +19,10 @@ hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int 
     if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     if constexpr (hb::TileTraits<W>::kSupported) {
         if (!hb::force_group_kernel()) {
-            const uint64_t wave_tiles = (n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile;
-            const uint64_t tiles = (wave_tiles + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-            if (tiles > 0x7fffffffull) return hipErrorInvalidConfiguration;
-            hipLaunchKernelGGL((hb::tile_kernel<W, MODE>), dim3((unsigned)tiles), dim3(hb::kBlock), 0, stream, x0, x1, n, k,
-                               seedB, seedA, o0, o1);
+            const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
+            if (grid.blocks == 0) return hipErrorInvalidConfiguration;
+            hipLaunchKernelGGL((hb::tile_kernel<W, MODE>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(grid.quarters)), stream, x0, x1, n, k,
+                               seedB, seedA, o0, o1, grid.whole_blocks);
             return hipGetLastError();
         }
     }
@@ -41,26 +40,9 @@ template <int W, int MODE>
 hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
 {
     if constexpr (hb::TileTraits<W>::kSupported) {
-        const uint64_t wave_tiles = args.tile_end[args.count - 1];
-        const uint64_t blocks = (wave_tiles + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-        if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, args);
-        return hipGetLastError();
-    } else {
-        return hipErrorInvalidDeviceFunction;
-    }
-}
-
-constexpr bool kSmallMode = (HB_PART_MODE == hb::kDrelu || HB_PART_MODE == hb::kRelu);
-
-template <int W, int MODE>
-hipError_t launch_small_batch(const hb::BatchArgs &args, hipStream_t stream)
-{
-    if constexpr (hb::SmallTraits<W>::kSupported && kSmallMode) {
-        const uint64_t wave_tiles = args.tile_end[args.count - 1];
-        const uint64_t blocks = (wave_tiles + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-        if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::small_batch_kernel<W, MODE>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, args);
+        const hb::TileGrid grid = hb::tile_grid(args.tiles, W);
+        if (grid.blocks == 0) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(grid.quarters)), stream, args);
         return hipGetLastError();
     } else {
         return hipErrorInvalidDeviceFunction;
@@ -74,11 +56,10 @@ hipError_t launch_sim(const float *x, uint64_t n, int k, uint64_t seedB, uint64_
     if constexpr (HB_PART_MODE != hb::kRelu) {
         return hipErrorInvalidDeviceFunction;
     } else if constexpr (hb::TileTraits<W>::kSupported) {
-        const uint64_t wave_tiles = (n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile;
-        const uint64_t blocks = (wave_tiles + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-        if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::tile_sim_kernel<W>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x, n, k, seedB,
-                           seedA, seedS, y);
+        const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
+        if (grid.blocks == 0) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((hb::tile_sim_kernel<W>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, hb::kRelu>(grid.quarters)), stream, x, n, k, seedB,
+                           seedA, seedS, y, grid.whole_blocks);
         return hipGetLastError();
     } else {
         const uint64_t blocks = (n + hb::kBlock - 1) / hb::kBlock;
@@ -95,7 +76,6 @@ void fill(hb::LauncherTable &t)
     if (HB_PART_MODE == hb::kRelu) t.sim[W - 1] = &launch_sim<W>;
     t.f[HB_PART_MODE][W - 1] = &launch_group<W, HB_PART_MODE>;
     t.batch[HB_PART_MODE][W - 1] = hb::TileTraits<W>::kSupported ? &launch_batch<W, HB_PART_MODE> : nullptr;
-    t.small[HB_PART_MODE][W - 1] = (hb::SmallTraits<W>::kSupported && kSmallMode) ? &launch_small_batch<W, HB_PART_MODE> : nullptr;
     if constexpr (W < HB_PART_HI) fill<W + 1>(t);
 }
 

@@ -67,9 +67,13 @@ struct Shape {
     }
 };
 
-struct Pair {      // one value held as (party 0 share, party 1 share)
-    uint64_t p0, p1;
+// The gate logic is bitwise, so it runs on whole words or on a half of one (Word = uint64_t or uint32_t).
+template <class Word>
+struct WordPair {    // one value held as (party 0 share, party 1 share)
+    Word p0, p1;
 };
+
+using Pair = WordPair<uint64_t>;
 
 // Returns z, which the compiler may not compute before `after` is known.  Dealer words depend only on the group
 // or element number, so the scheduler would otherwise generate those of every gate ahead of the circuit and
@@ -88,6 +92,11 @@ constexpr unsigned kTtXorAnd = (0xF0 ^ (0xCC & 0xAA)) & 0xFF;          // a ^ (b
 constexpr unsigned kTtAndXor = (0xF0 & (0xCC ^ 0xAA)) & 0xFF;          // a & (b ^ c)
 
 template <unsigned TT>
+__device__ __forceinline__ uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, TT);
+}
+template <unsigned TT>
 __device__ __forceinline__ uint64_t bitop3(uint64_t a, uint64_t b, uint64_t c)
 {
     const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, TT);
@@ -95,8 +104,9 @@ __device__ __forceinline__ uint64_t bitop3(uint64_t a, uint64_t b, uint64_t c)
     return ((uint64_t)hi << 32) | lo;
 }
 
+template <class Word>
 struct GateWords {   // the five dealer words of one AND gate, in stream order
-    uint64_t a0, a1, b0, b1, c0;
+    Word a0, a1, b0, b1, c0;
 };
 
 // One Beaver AND on XOR-shared words, Z = U & V, returned as acc ^ Z share by share (acc = {0, 0} for the
@@ -105,17 +115,18 @@ struct GateWords {   // the five dealer words of one AND gate, in stream order
 // send, (U_0 ^ a_0) ^ (U_1 ^ a_1) = (U_0 ^ U_1) ^ (a_0 ^ a_1); the caller passes Ux = U_0 ^ U_1 and
 // Vx = (V_0 ^ V_1) before the field mask `keep` that confines a shifted operand to its field (all ones when
 // the operand is not shifted).  Party 0 takes the public d & e term.
-__device__ __forceinline__ Pair beaver_and_words(const GateWords &t, uint64_t Ux, uint64_t Vx, uint64_t keep, Pair acc)
+template <class Word>
+__device__ __forceinline__ WordPair<Word> beaver_and_words(const GateWords<Word> &t, Word Ux, Word Vx, Word keep, WordPair<Word> acc)
 {
-    const uint64_t a0 = t.a0, a1 = t.a1, b0 = t.b0, b1 = t.b1, c0 = t.c0;
-    const uint64_t a = a0 ^ a1, b = b0 ^ b1;                    // the dealer's triple (a, b, a & b)
-    const uint64_t d = Ux ^ a;                                  // opened
-    const uint64_t e = bitop3<kTtXorAnd>(b, Vx, keep);          // opened: (Vx & keep) ^ b
-    Pair Z;
+    const Word a0 = t.a0, a1 = t.a1, b0 = t.b0, b1 = t.b1, c0 = t.c0;
+    const Word a = a0 ^ a1, b = b0 ^ b1;                        // the dealer's triple (a, b, a & b)
+    const Word d = Ux ^ a;                                      // opened
+    const Word e = bitop3<kTtXorAnd>(b, Vx, keep);              // opened: (Vx & keep) ^ b
+    WordPair<Word> Z;
     // party 0: acc ^ c_0 ^ (e & a_0) ^ (d & (b_0 ^ e))    [= c_0 ^ (d & b_0) ^ (e & a_0) ^ (d & e)]
     Z.p0 = bitop3<kTtXor3>(acc.p0, bitop3<kTtXorAnd>(c0, e, a0), bitop3<kTtAndXor>(d, b0, e));
     // party 1: acc ^ c_1 ^ (d & b_1) ^ (e & a_1), the dealer having completed c_1 = (a & b) ^ c_0
-    const uint64_t c1 = bitop3<kTtXorAnd>(c0, a, b);
+    const Word c1 = bitop3<kTtXorAnd>(c0, a, b);
     Z.p1 = bitop3<kTtXorAnd>(bitop3<kTtXorAnd>(acc.p1 ^ c1, d, b1), e, a1);
     return Z;
 }
@@ -124,7 +135,7 @@ __device__ __forceinline__ Pair beaver_and_words(const GateWords &t, uint64_t Ux
 // words a_0 a_1 b_0 b_1 c_0 are consecutive outputs.
 __device__ __forceinline__ Pair beaver_and(uint64_t zq, uint64_t Ux, uint64_t Vx, uint64_t keep, Pair acc)
 {
-    GateWords t;
+    GateWords<uint64_t> t;
     t.a0 = mix64(zq);
     t.a1 = mix64(zq + 1 * kGamma);
     t.b0 = mix64(zq + 2 * kGamma);
@@ -204,28 +215,30 @@ __device__ __forceinline__ Pair a2b_sum(uint64_t u0, uint64_t u1, uint64_t zg)
     return Pair{Sum.p0 ^ ((G.p0 << 1) & keep1), Sum.p1 ^ ((G.p1 << 1) & keep1)};
 }
 
-// The same circuit on dealer words that were generated elsewhere (standard layout): words[5q + s] is slot s of
-// gate q for q = 0 .. 2R - 1 (the last round's P-update gate, q = 2R, is not evaluated and has no entry).
-template <int W>
-__device__ __forceinline__ Pair a2b_sum_words(uint64_t u0, uint64_t u1, const uint64_t *words)
+// The same circuit on dealer words that were generated elsewhere: words[i] is word i of the group (those of the last
+// round's P-update gate, which is not evaluated, are not there).  Word = uint32_t: the lower or the upper half of the
+// fields, at bits jW of u0, u1 and of every word; S::keep is the same for both.
+template <int W, bool SHARED, class Word>
+__device__ __forceinline__ WordPair<Word> a2b_sum_words(Word u0, Word u1, const Word *words)
 {
     using S = Shape<W>;
-    auto gate = [&](int q) { return GateWords{words[5 * q], words[5 * q + 1], words[5 * q + 2], words[5 * q + 3], words[5 * q + 4]}; };
-    const Pair X{u0, 0}, Y{0, u1};
-    Pair P{X.p0 ^ Y.p0, X.p1 ^ Y.p1};
-    const Pair Sum = P;
-    Pair G = beaver_and_words(gate(0), X.p0 ^ X.p1, Y.p0 ^ Y.p1, ~0ull, Pair{0, 0});
+    using WP = WordPair<Word>;
+    auto gate = [&](int a, int b) { return GateWords<Word>{words[a], words[a + 1], words[b], words[b + 1], words[b + 2]}; };
+    const WP X{u0, 0}, Y{0, u1};
+    WP P{X.p0 ^ Y.p0, X.p1 ^ Y.p1};
+    const WP Sum = P;
+    WP G = beaver_and_words<Word>(gate(0, 2), X.p0 ^ X.p1, Y.p0 ^ Y.p1, (Word)~0ull, WP{0, 0});
 #pragma unroll
     for (int r = 0; r < S::R; ++r) {
-        const int s = 1 << r;
-        const uint64_t keep = S::keep(s);
-        const uint64_t Px = P.p0 ^ P.p1;
-        const uint64_t Gsx = (G.p0 ^ G.p1) << s, Psx = Px << s;
-        G = beaver_and_words(gate(1 + 2 * r), Px, Gsx, keep, G);
-        if (r + 1 < S::R) P = beaver_and_words(gate(2 + 2 * r), Px, Psx, keep, Pair{0, 0});
+        const int s = 1 << r, w = S::round_word(SHARED, r);
+        const Word keep = (Word)S::keep(s);
+        const Word Px = P.p0 ^ P.p1;
+        const Word Gsx = (G.p0 ^ G.p1) << s, Psx = Px << s;
+        G = beaver_and_words<Word>(gate(w, w + 2), Px, Gsx, keep, G);
+        if (r + 1 < S::R) P = beaver_and_words<Word>(SHARED ? gate(w, w + 5) : gate(w + 5, w + 7), Px, Psx, keep, WP{0, 0});
     }
-    const uint64_t keep1 = S::keep(1);
-    return Pair{Sum.p0 ^ ((G.p0 << 1) & keep1), Sum.p1 ^ ((G.p1 << 1) & keep1)};
+    const Word keep1 = (Word)S::keep(1);
+    return WP{Sum.p0 ^ ((G.p0 << 1) & keep1), Sum.p1 ^ ((G.p1 << 1) & keep1)};
 }
 
 // What an element keeps of its group's verdict: the opened bit z = sign_0 ^ rho_0 ^ sign_1 ^ rho_1 of the B2A, as
@@ -321,8 +334,9 @@ __device__ __forceinline__ Pair b2a_mul(B2aBits t, Pair x, uint64_t zA)
     const uint64_t a = a0 + a1, b = b0 + b1;                      // the dealer's triple (a, b, a * b)
     const uint64_t eps = (x.p0 + x.p1) - a;                       // opened: (x_0 - a_0) + (x_1 - a_1)
     // opened: (DReLU_0 - b_0) + (DReLU_1 - b_1), taken as ((DReLU_0 + DReLU_1) - b_1) - b_0: party 0 needs b_0 + del
-    const uint64_t b0_del = held((f.f0 + f.f1) + (uint32_t)(t.m + 2)) - b1;
-    const uint64_t del = held(b0_del) - b0;
+    // (one value, held and then used by both: a second name for it would cost a copy)
+    const uint64_t b0_del = held(held((f.f0 + f.f1) + (uint32_t)(t.m + 2)) - b1);
+    const uint64_t del = b0_del - b0;
     Pair out;
     // party 0: c_0 + eps * b_0 + del * a_0 + eps * del
     out.p0 = sum_of_products(c0, eps, b0_del, del, a0);
