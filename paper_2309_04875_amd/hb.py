@@ -151,10 +151,11 @@ def _tensor_args(*tensors):
 def _stream_handle(stream):
     import torch
     if stream is None:
-        # the raw handle of torch's current stream; several times cheaper than building a torch.cuda.Stream object
+        # The raw handle of torch's current stream, asked for through the calls that torch.cuda's own functions wrap: several
+        # times cheaper than a torch.cuda.Stream object.  The tensors of the call are on the GPU, so torch is initialised.
         raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw_stream is not None:
-            return ctypes.c_void_p(raw_stream(torch.cuda.current_device()))
+        if raw_stream is not None and torch.cuda.is_initialized():
+            return raw_stream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
