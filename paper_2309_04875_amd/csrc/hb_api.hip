@@ -488,22 +488,22 @@ LauncherTable &launcher_table()
 // where that is at most kSplitMost tiles, which then takes the time of one or two quarters instead of a tile's.
 // Measured, quarters against whole tiles: w = 8, 512 tiles 5.3 / 7.0 us, 900 6.9 / 7.1, 1088 (64 left) 7.5 / 9.9,
 // 1536 (512 left) 9.0 / 10.4, 4150 (54 left) 17.2 / 19.8; w = 10, 512 tiles 5.8 / 6.9, 900 7.9 / 7.2, 2100 (52 left) 10.8 / 13.4.
-// Three quarters' time (1700 tiles by quarters: 10.1 / 10.3) no longer pays.
-constexpr uint64_t kSimds = 1024, kSplitMost = 512;
+// Three quarters' time (1700 tiles by quarters: 10.1 / 10.3) no longer pays.  Among more parties the gate logic, which the
+// four lanes of a group repeat in part, weighs more, and the first line lies lower: four parties at w = 16, 781 tiles by quarters
+// take 21.7 us where whole ones take 18.8; 4 tiles left after 16 rounds 209 where they took 221.
+constexpr uint64_t kSimds = 1024, kSplitMost = 512, kAllBelow = 900, kAllBelowMp = 512;
 
 // HB_SMALL_TILE_LIMIT in the environment (read once) overrides the limit; 0 switches the quarters off.
-uint64_t small_tile_limit()
+uint64_t small_tile_limit(int parties)
 {
-    static const uint64_t limit = [] {
-        const char *v = std::getenv("HB_SMALL_TILE_LIMIT");
-        return v != nullptr ? (uint64_t)std::strtoull(v, nullptr, 10) : (uint64_t)900;
-    }();
-    return limit;
+    static const char *const v = std::getenv("HB_SMALL_TILE_LIMIT");
+    static const uint64_t given = v != nullptr ? (uint64_t)std::strtoull(v, nullptr, 10) : 0;
+    return v != nullptr ? given : parties == 2 ? kAllBelow : kAllBelowMp;
 }
 
-TileGrid tile_grid(uint64_t tiles, int w)
+TileGrid tile_grid(uint64_t tiles, int w, int parties)
 {
-    const uint64_t limit = small_tile_limit(), left = tiles % kSimds;
+    const uint64_t limit = small_tile_limit(parties), left = tiles % kSimds;
     uint64_t split = 0;
     if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= kSplitMost ? left : 0;
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;

@@ -45,7 +45,7 @@ struct TileGrid {
     uint32_t whole_blocks, blocks;       // blocks 0: more than a grid holds
     bool quarters;                       // blocks > whole_blocks
 };
-TileGrid tile_grid(uint64_t tiles, int w);
+TileGrid tile_grid(uint64_t tiles, int w, int parties = 2);
 
 // Debug knob: HB_KERNEL=group in the environment (read once) sends every width to the thread-per-group kernel.
 bool force_group_kernel();

@@ -15,11 +15,10 @@ hipError_t launch_mp(const hb::MpPointers &ptr, uint64_t n, int k, uint64_t seed
 {
     if constexpr (hb::MpTileTraits<W, P>::kSupported) {
         if (!hb::force_group_kernel()) {
-            const uint64_t wave_tiles = (n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile;
-            const uint64_t blocks = (wave_tiles + hb::kWavesPerBlock - 1) / hb::kWavesPerBlock;
-            if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-            hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, ptr,
-                               n, k, seedB, seedA);
+            const hb::TileGrid grid = hb::tile_grid((n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile, W, P);
+            if (grid.blocks == 0) return hipErrorInvalidConfiguration;
+            hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE>), dim3(grid.blocks), dim3(hb::kBlock),
+                               (hb::mp_lds_bytes<W, P>(grid.quarters)), stream, ptr, n, k, seedB, seedA, grid.whole_blocks);
             return hipGetLastError();
         }
     }

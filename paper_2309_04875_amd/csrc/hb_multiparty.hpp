@@ -11,7 +11,8 @@
 //
 //   mp_group_kernel   one thread per group, scalar 8-byte accesses: slice widths above 32.
 //   mp_tile_kernel    one wavefront per 64 groups (32 below w = 4, where a group has 16 or 21 elements) with
-//                     coalesced 16-byte accesses, as tile_kernel: slice widths up to 32.
+//                     coalesced 16-byte accesses, as tile_kernel: slice widths up to 32.  What cannot fill the chip goes by
+//                     quarters of a tile, four lanes per group, as there.
 //
 // Algorithmic traffic: 16 P bytes per element.
 #pragma once
@@ -22,9 +23,9 @@ namespace hb {
 
 constexpr int kMaxParties = 4;
 
-template <int P>
+template <int P, class Word = uint64_t>
 struct Shares {      // one value held as P shares
-    uint64_t v[P];
+    Word v[P];
 };
 
 struct MpPointers {  // kernel argument: the P input and P output arrays
@@ -45,30 +46,30 @@ struct MpShape {
     static constexpr int kArithWords = 4 * P - 2;
 };
 
-// Beaver AND among P parties, returned XORed onto acc share by share; zq = generator state of the gate's first
-// dealer word.  As in the two-party gate the operands enter only through the openings: Ux = XOR over the parties
-// of U_q, Vx = XOR of V_q before the field mask `keep` of a shifted operand.
-template <int P>
-__device__ __forceinline__ Shares<P> mp_and(uint64_t zq, uint64_t Ux, uint64_t Vx, uint64_t keep, const Shares<P> &acc)
+// Beaver AND among P parties, returned XORed onto acc share by share; word(i) = the gate's dealer word i.  As in the
+// two-party gate the operands enter only through the openings: Ux = XOR over the parties of U_q, Vx = XOR of V_q before the
+// field mask `keep` of a shifted operand.
+template <int P, class Word, class Words>
+__device__ __forceinline__ Shares<P, Word> mp_and(const Words &word, Word Ux, Word Vx, Word keep, const Shares<P, Word> &acc)
 {
-    uint64_t a[P], b[P], c[P];
-    uint64_t as = 0, bs = 0, cs = 0;
+    Word a[P], b[P], c[P];
+    Word as = 0, bs = 0, cs = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        a[q] = mix64(zq + (uint64_t)q * kGamma);
-        b[q] = mix64(zq + (uint64_t)(P + q) * kGamma);
+        a[q] = word(q);
+        b[q] = word(P + q);
         as ^= a[q];
         bs ^= b[q];
     }
 #pragma unroll
     for (int q = 0; q < P - 1; ++q) {
-        c[q] = mix64(zq + (uint64_t)(2 * P + q) * kGamma);
+        c[q] = word(2 * P + q);
         cs ^= c[q];
     }
     c[P - 1] = bitop3<kTtXorAnd>(cs, as, bs);               // the dealer completes the sharing of c = a & b
-    const uint64_t d = Ux ^ as;                             // opened: XOR over the parties of U_q ^ a_q
-    const uint64_t e = bitop3<kTtXorAnd>(bs, Vx, keep);     // opened: XOR over the parties of V_q ^ b_q
-    Shares<P> Z;
+    const Word d = Ux ^ as;                                 // opened: XOR over the parties of U_q ^ a_q
+    const Word e = bitop3<kTtXorAnd>(bs, Vx, keep);         // opened: XOR over the parties of V_q ^ b_q
+    Shares<P, Word> Z;
     // party 0 takes the public d & e term: c_0 ^ (d & b_0) ^ (e & a_0) ^ (d & e)
     Z.v[0] = bitop3<kTtXor3>(acc.v[0], bitop3<kTtXorAnd>(c[0], e, a[0]), bitop3<kTtAndXor>(d, b[0], e));
 #pragma unroll
@@ -76,15 +77,15 @@ __device__ __forceinline__ Shares<P> mp_and(uint64_t zq, uint64_t Ux, uint64_t V
     return Z;
 }
 
-// X + Y mod 2^W in every field, on XOR shares; za = generator state of the adder's first dealer word.
-// The last round's P-update gate is not evaluated (nothing reads it; its words are never drawn).
-template <int W, int P>
-__device__ __forceinline__ Shares<P> mp_add(uint64_t za, const Shares<P> &X, const Shares<P> &Y)
+// X + Y mod 2^W in every field, on XOR shares.  gate(q, after) gives the accessor of gate q's dealer words, which are not
+// drawn before `after` is known.  The last round's P-update gate is not evaluated (nothing reads it; its words are never
+// drawn).  Word = uint32_t: the lower or the upper half of the fields, at bits jW of every word.
+template <int W, int P, class Word, class Gates>
+__device__ __forceinline__ Shares<P, Word> mp_add_gates(const Gates &gate, const Shares<P, Word> &X, const Shares<P, Word> &Y)
 {
     using S = Shape<W>;
-    using M = MpShape<W, P>;
-    Shares<P> Pw, Sum, zero;
-    uint64_t Xx = 0, Yx = 0;
+    Shares<P, Word> Pw, Sum, zero;
+    Word Xx = 0, Yx = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
         Pw.v[q] = Sum.v[q] = X.v[q] ^ Y.v[q];
@@ -92,61 +93,78 @@ __device__ __forceinline__ Shares<P> mp_add(uint64_t za, const Shares<P> &X, con
         Xx ^= X.v[q];
         Yx ^= Y.v[q];
     }
-    Shares<P> G = mp_and<P>(za, Xx, Yx, ~0ull, zero);
+    Shares<P, Word> G = mp_and<P, Word>(gate(0, Xx), Xx, Yx, (Word)~0ull, zero);
 #pragma unroll
     for (int r = 0; r < S::R; ++r) {
         const int s = 1 << r;
-        const uint64_t keep = S::keep(s);
+        const Word keep = (Word)S::keep(s);
         // shifting is linear: the XOR of the parties' shifted shares is the shifted XOR of their shares
-        uint64_t Gx = 0, Px = 0;
+        Word Gx = 0, Px = 0;
 #pragma unroll
         for (int q = 0; q < P; ++q) {
             Gx ^= G.v[q];
             Px ^= Pw.v[q];
         }
         // one gate's dealer words at a time (not_before): 3P - 1 live words instead of the whole adder's
-        G = mp_and<P>(not_before(za + (uint64_t)((1 + 2 * r) * M::kGateWords) * kGamma, Gx), Px, Gx << s, keep, G);
-        if (r + 1 < S::R)
-            Pw = mp_and<P>(not_before(za + (uint64_t)((2 + 2 * r) * M::kGateWords) * kGamma, G.v[0]), Px, Px << s, keep, zero);
+        G = mp_and<P, Word>(gate(1 + 2 * r, Gx), Px, (Word)(Gx << s), keep, G);
+        if (r + 1 < S::R) Pw = mp_and<P, Word>(gate(2 + 2 * r, G.v[0]), Px, (Word)(Px << s), keep, zero);
     }
-    const uint64_t keep1 = S::keep(1);
-    Shares<P> out;
+    const Word keep1 = (Word)S::keep(1);
+    Shares<P, Word> out;
 #pragma unroll
     for (int q = 0; q < P; ++q) out.v[q] = Sum.v[q] ^ ((G.v[q] << 1) & keep1);
     return out;
 }
 
-// XOR shares of (u_0 + ... + u_{P-1}) mod 2^W for one group; zg = generator state of the group's first word.
+// The adder drawing its words inline; za = generator state of its first dealer word.
 template <int W, int P>
-__device__ __forceinline__ Shares<P> mp_a2b_sum(const uint64_t (&u)[P], uint64_t zg)
+__device__ __forceinline__ Shares<P> mp_add(uint64_t za, const Shares<P> &X, const Shares<P> &Y)
 {
-    using M = MpShape<W, P>;
-    Shares<P> X[P];
+    auto gate = [za](int q, uint64_t after) {
+        const uint64_t zq = za + (uint64_t)(q * MpShape<W, P>::kGateWords) * kGamma;
+        const uint64_t z = q == 0 ? zq : not_before(zq, after);
+        return [z](int i) { return mix64(z + (uint64_t)i * kGamma); };
+    };
+    return mp_add_gates<W, P, uint64_t>(gate, X, Y);
+}
+
+// XOR shares of (u_0 + ... + u_{P-1}) mod 2^W for one group; add(i, X, Y) is adder i of the tree.
+template <int P, class Word, class Add>
+__device__ __forceinline__ Shares<P, Word> mp_tree(const Word (&u)[P], const Add &add)
+{
+    Shares<P, Word> X[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
 #pragma unroll
         for (int t = 0; t < P; ++t) X[q].v[t] = (t == q) ? u[q] : 0;    // party q shares its slice trivially
     }
-    constexpr uint64_t kAdderStride = (uint64_t)M::kAdderWords * kGamma;
+    const Shares<P, Word> s01 = add(0, X[0], X[1]);
     if constexpr (P == 3) {
-        const Shares<P> s01 = mp_add<W, P>(zg, X[0], X[1]);
-        return mp_add<W, P>(zg + kAdderStride, s01, X[2]);
+        return add(1, s01, X[2]);
     } else {
-        const Shares<P> s01 = mp_add<W, P>(zg, X[0], X[1]);
-        const Shares<P> s23 = mp_add<W, P>(zg + kAdderStride, X[2], X[3]);
-        return mp_add<W, P>(zg + 2 * kAdderStride, s01, s23);
+        const Shares<P, Word> s23 = add(1, X[2], X[3]);
+        return add(2, s01, s23);
     }
 }
 
-// Everything after the circuit for one element.  sign / rho: bit q = party q's XOR share of the sign / of the
-// dealer bit.  zA = generator state of the element's first arithmetic word.  MODE: kDrelu or kRelu.
+// The same drawing its words inline; zg = generator state of the group's first word.
+template <int W, int P>
+__device__ __forceinline__ Shares<P> mp_a2b_sum(const uint64_t (&u)[P], uint64_t zg)
+{
+    auto add = [zg](int i, const Shares<P> &X, const Shares<P> &Y) {
+        return mp_add<W, P>(zg + (uint64_t)(i * MpShape<W, P>::kAdderWords) * kGamma, X, Y);
+    };
+    return mp_tree<P, uint64_t>(u, add);
+}
+
+// Everything after the circuit for one element.  t: the opened bit and the dealer's bit.  zA = generator state of the element's first arithmetic word.  MODE: kDrelu or kRelu.
 // As for two parties (b2a_shares): with c_q = ~r^A_q and q = r^A_{P-1} - 1 = c_0 + ... + c_{P-2} + (P - 2) + r,
 //   DReLU_0 = (c_0 ^ m) + 2 (1 - z),  DReLU_q = (c_q ^ m) + (1 - z),  DReLU_{P-1} = ~(q ^ m) + z.
 template <int P, int MODE>
-__device__ __forceinline__ Shares<P> mp_finish(uint32_t sign, uint32_t rho, const Shares<P> &x, uint64_t zA)
+__device__ __forceinline__ Shares<P> mp_finish(B2aBits t, const Shares<P> &x, uint64_t zA)
 {
-    const uint32_t r = (uint32_t)__popc(rho) & 1u;            // known to the dealer only
-    const int32_t m = minus_bit((uint32_t)__popc(sign ^ rho), 0);    // -z, the opened bit
+    const uint32_t r = t.r;                                   // known to the dealer only
+    const int32_t m = t.m;                                    // -z, the opened bit
     const uint64_t mm = (uint64_t)(int64_t)m;
     uint64_t f[P], csum = 0;
 #pragma unroll
@@ -235,17 +253,18 @@ mp_group_kernel(const MpPointers ptr, uint64_t n, uint64_t groups, int k, uint64
             }
             const uint32_t rho = (uint32_t)(wb >> (P * j)) & ((1u << P) - 1);
             const uint64_t zA = seedA + ((uint64_t)M::kArithWords * (i0 + j) + 1) * kGamma;
-            const Shares<P> out = mp_finish<P, MODE>(sign, rho, x, zA);
+            const B2aBits t{minus_bit((uint32_t)__popc(sign ^ rho), 0), (uint32_t)__popc(rho) & 1u};
+            const Shares<P> out = mp_finish<P, MODE>(t, x, zA);
 #pragma unroll
             for (int q = 0; q < P; ++q) store_stream(ptr.o[q] + i0 + j, out.v[q]);
         }
     }
 }
 
-// Tile kernel among P parties: the owner / group-lane scheme of tile_body.  LDS per wavefront: P arrays of one
-// entry (1, 2 or 4 bytes) per element for the slices, and per group {sign shares, B2A word}; the sign share of
-// party q for lane j sits at bit j*W + q when a field has room for P bits (W >= P); narrower fields publish one
-// word per party instead (the sum word itself: the sign of lane j is bit j*W + W - 1).
+// Tile kernel among P parties: the owner / group-lane scheme of tile_body.  LDS per wavefront: P arrays of one entry (1, 2
+// or 4 bytes) per element for the slices, and a byte {z, r} per element for the verdict, as Verdict's in the widths that are
+// not packed.  (With sign shares and the B2A word published per group, an owner spent 14 instructions per element on
+// finding and decoding them.)
 template <int W, int P>
 struct MpTileTraits {
     using M = MpShape<W, P>;
@@ -253,36 +272,51 @@ struct MpTileTraits {
     static constexpr bool kSupported = (W <= 32);
     static constexpr int kGroups = (W >= 4) ? kWave : kWave / 2;   // half the lanes run the circuit when L > 16:
     static constexpr int kTile = kGroups * L;                      // a lane then owns at most 6 element pairs
-    static constexpr int kPairs = (kTile / 2 + kWave - 1) / kWave;
-    static constexpr bool kSignWords = (W < P);
     using Entry = typename std::conditional<(W <= 8), uint8_t,
                   typename std::conditional<(W <= 16), uint16_t, uint32_t>::type>::type;
     static constexpr bool kWordIsPacked = (int)sizeof(Entry) * 8 == W;   // the L entries of a group are its SWAR word
-    static constexpr int kSliceBytes = ((kTile * (int)sizeof(Entry) + 15) / 16) * 16;   // per party
+    static constexpr int slice_bytes(int groups) { return (groups * L * (int)sizeof(Entry) + 15) / 16 * 16; }   // per party
+    static constexpr int verdict_bytes(int groups) { return (groups * L + 15) / 16 * 16; }
+    static constexpr int kLdsBytes = P * slice_bytes(kGroups) + verdict_bytes(kGroups);
 };
 
-// Work of one wavefront on wave-tile `tile` (uniform over the wavefront).  FULL: the whole tile lies inside the
-// tensor, so no access needs a bounds check (every tile but the last).
-template <int W, int P, int MODE, bool FULL>
-__device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                                             uint64_t tile, int lane, unsigned char (*slice_lds)[MpTileTraits<W, P>::kSliceBytes],
-                                             U64x2 *verdict, uint64_t (*sign_words)[P])
-{
-    using S = Shape<W>;
+// A quarter of a tile: 16 groups, four lanes per group (QuarterTraits).  The words of one adder are exchanged at a time.
+template <int W, int P>
+struct MpQuarterTraits {
     using M = MpShape<W, P>;
     using T = MpTileTraits<W, P>;
-    using Entry = typename T::Entry;
-    constexpr int L = T::L;
-    const uint64_t tile0 = tile * T::kTile;
+    static constexpr int L = M::L;
+    static constexpr int kSplit = 4, kGroups = kWave / kSplit, kTile = kGroups * L;
+    static constexpr bool kHalves = (L % 2 == 0);
+    using Word = typename std::conditional<kHalves, uint32_t, uint64_t>::type;
+    static constexpr int kFields = kHalves ? L / 2 : L;
+    static constexpr int kWords = 2 * M::R * M::kGateWords;        // evaluated words of an adder: all but the last P-update's
+    static constexpr int kPad = (kWords + 1 + 3) / 4 * 4;          // and the B2A word, with the last adder's
+    static constexpr int kRow = 2 * kPad + 4;                      // 32-bit units, an odd multiple of four
+    static constexpr int kWordsAt = P * T::slice_bytes(kGroups), kVerdictAt = kWordsAt + kGroups * kRow * 4;
+    static constexpr int kLdsBytes = kVerdictAt + T::verdict_bytes(kGroups);
+};
 
-    // ---- owners: load, slice, deposit
-    U64x2 xs[P][T::kPairs];
+template <int W, int P>
+constexpr unsigned mp_lds_bytes(bool quarters)
+{
+    int most = MpTileTraits<W, P>::kLdsBytes;
+    if constexpr (quarters_supported(W)) {
+        if (quarters && MpQuarterTraits<W, P>::kLdsBytes > most) most = MpQuarterTraits<W, P>::kLdsBytes;
+    }
+    return (unsigned)(kWavesPerBlock * most);
+}
+
+// Owners' part before the circuit: the pairs of all parties (PAIRS per lane of TILE elements), and their slices.
+template <int P, int PAIRS, int TILE, bool FULL>
+__device__ __forceinline__ void mp_load(const MpPointers &ptr, uint64_t tile0, uint64_t n, int lane, U64x2 (&xs)[P][PAIRS])
+{
 #pragma unroll
-    for (int c = 0; c < T::kPairs; ++c) {
+    for (int c = 0; c < PAIRS; ++c) {
         const unsigned e = 2 * (c * kWave + lane);
 #pragma unroll
         for (int q = 0; q < P; ++q) xs[q][c] = U64x2{0, 0};
-        if (e < (unsigned)T::kTile) {
+        if (e < (unsigned)TILE) {
 #pragma unroll
             for (int q = 0; q < P; ++q) {
                 const uint64_t *t = ptr.x[q] + tile0;       // scalar base, 32-bit lane offset
@@ -291,74 +325,84 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
                 } else if (tile0 + e < n) {
                     xs[q][c].a = load_stream(t + e);
                 }
-                Entry *sl = reinterpret_cast<Entry *>(slice_lds[q]);
+            }
+        }
+    }
+}
+template <int W, int P, int PAIRS, int TILE, int BYTES>
+__device__ __forceinline__ void mp_deposit(unsigned char *lds, int k, int lane, const U64x2 (&xs)[P][PAIRS])
+{
+    using S = Shape<W>;
+    using Entry = typename MpTileTraits<W, P>::Entry;
+#pragma unroll
+    for (int c = 0; c < PAIRS; ++c) {
+        const unsigned e = 2 * (c * kWave + lane);
+        if (e < (unsigned)TILE) {
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                Entry *sl = reinterpret_cast<Entry *>(lds + q * BYTES);
                 sl[e] = (Entry)((xs[q][c].a >> k) & S::kField);
                 sl[e + 1] = (Entry)((xs[q][c].b >> k) & S::kField);
             }
         }
     }
-    wave_sync();
-
-    // ---- group lanes: collect the fields of group `lane`, run the adder tree, publish signs and B2A word
-    if (T::kGroups == kWave || lane < T::kGroups) {
-        uint64_t u[P];
+}
+// The FIELDS fields of word `slot` of one party's slices.
+template <int W, int P, class Word, int FIELDS>
+__device__ __forceinline__ Word mp_collect(const unsigned char *lds, int slot)
+{
+    using T = MpTileTraits<W, P>;
+    if constexpr (T::kWordIsPacked) {
+        return reinterpret_cast<const Word *>(lds)[slot];
+    } else {
+        const typename T::Entry *sl = reinterpret_cast<const typename T::Entry *>(lds) + slot * FIELDS;
+        Word u = 0;
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-            if constexpr (T::kWordIsPacked) {
-                u[q] = reinterpret_cast<const uint64_t *>(slice_lds[q])[lane];
-            } else {
-                const Entry *sl = reinterpret_cast<const Entry *>(slice_lds[q]);
-                u[q] = 0;
-#pragma unroll
-                for (int j = 0; j < L; ++j) u[q] |= (uint64_t)sl[lane * L + j] << (j * W);
-            }
-        }
-        const uint64_t g = tile * T::kGroups + lane;
-        const uint64_t zg = seedB + (g * (uint64_t)M::kWordsPerGroup + 1) * kGamma;
-        const Shares<P> sum = mp_a2b_sum<W, P>(u, zg);
-        const uint64_t ones = S::ones();
-        uint64_t sg = 0;
-        if constexpr (T::kSignWords) {
-#pragma unroll
-            for (int q = 0; q < P; ++q) sign_words[lane][q] = sum.v[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < P; ++q) sg |= ((sum.v[q] >> (W - 1)) & ones) << q;
-        }
-        verdict[lane] = U64x2{sg, mix64(zg + (uint64_t)M::kB2aWord * kGamma)};
+        for (int j = 0; j < FIELDS; ++j) u |= (Word)sl[j] << (j * W);
+        return u;
     }
-    wave_sync();
-
-    // ---- owners: pick up the verdict of each element's group, finish, store
-    const uint64_t zA0 = seedA + ((uint64_t)M::kArithWords * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
+}
+// {z, r} of the FIELDS fields of word `slot`.  wb: the group's B2A word with the first of these fields' P bits at 0.
+template <int W, int P, class Word, int FIELDS>
+__device__ __forceinline__ void mp_publish(unsigned char *verdict, int slot, const Shares<P, Word> &sum, uint64_t wb)
+{
+    Word sx = 0;
+    uint64_t rx = 0, ones = 0;
 #pragma unroll
-    for (int c = 0; c < T::kPairs; ++c) {
-        const unsigned e = 2 * (c * kWave + lane);
-        if (e < (unsigned)T::kTile) {
-            const int grp0 = e / L, j0 = e - grp0 * L;
-            const U64x2 v0 = verdict[grp0];
-            const bool split = (L % 2 != 0) && (j0 == L - 1);     // the pair straddles two groups (odd L only)
-            const U64x2 v1 = split ? verdict[grp0 + 1] : v0;
+    for (int q = 0; q < P; ++q) {
+        sx ^= sum.v[q];
+        rx ^= wb >> q;                                          // bit P j: r
+    }
+#pragma unroll
+    for (int j = 0; j < FIELDS; ++j) ones |= 1ull << (P * j);
+    const uint64_t rr = (rx & ones) | ((rx & ones) << 1);
+    sx >>= W - 1;                                               // bit jW: XOR of the parties' sign shares
+#pragma unroll
+    for (int j = 0; j < FIELDS; ++j) {                          // bits above the two are never looked at
+        verdict[slot * FIELDS + j] = (unsigned char)(Verdict<5, kRelu>::bit_at(sx, j * W) ^ (uint32_t)(rr >> (P * j)));
+    }
+}
+// Owners' part after the circuit.
+template <int P, int MODE, int PAIRS, int TILE, bool FULL>
+__device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t tile0, uint64_t n, int lane, uint64_t seedA,
+                                                const U64x2 (&xs)[P][PAIRS], const unsigned char *verdict)
+{
+    constexpr uint64_t kArithWords = 4 * P - 2;
+    uint64_t zA0 = seedA + (kArithWords * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
+#pragma unroll
+    for (int c = 0; c < PAIRS; ++c) {
+        const int pr = c * kWave + lane;
+        const unsigned e = 2 * pr;
+        if (e < (unsigned)TILE) {
+            const uint32_t v = reinterpret_cast<const uint16_t *>(verdict)[pr];
             Shares<P> r[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const U64x2 v = h ? v1 : v0;
-                const int j = h ? (split ? 0 : j0 + 1) : j0;
-                uint32_t sign;
-                if constexpr (T::kSignWords) {
-                    const int gj = h ? (split ? grp0 + 1 : grp0) : grp0;
-                    sign = 0;
-#pragma unroll
-                    for (int q = 0; q < P; ++q) sign |= ((uint32_t)(sign_words[gj][q] >> (j * W + W - 1)) & 1u) << q;
-                } else {
-                    sign = (uint32_t)(v.a >> (j * W)) & ((1u << P) - 1);
-                }
-                const uint32_t rho = (uint32_t)(v.b >> (P * j)) & ((1u << P) - 1);
+                const B2aBits t{minus_bit(v, 8 * h), __builtin_amdgcn_ubfe(v, 8 * h + 1, 1)};
                 Shares<P> x;
 #pragma unroll
                 for (int q = 0; q < P; ++q) x.v[q] = h ? xs[q][c].b : xs[q][c].a;
-                const uint64_t zA = zA0 + (uint64_t)(M::kArithWords * (2 * c * kWave + h)) * kGamma;
-                r[h] = mp_finish<P, MODE>(sign, rho, x, zA);
+                r[h] = mp_finish<P, MODE>(t, x, zA0 + kArithWords * (uint64_t)(2 * c * kWave + h) * kGamma);
             }
 #pragma unroll
             for (int q = 0; q < P; ++q) {
@@ -369,26 +413,140 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
                     store_stream(t + e, r[0].v[q]);
                 }
             }
+            zA0 = not_before(zA0, r[1].v[P - 1]);               // one pair's dealer words at a time
         }
     }
 }
 
+// Work of one wavefront on wave-tile `tile` (uniform over the wavefront).  FULL: the whole tile lies inside the
+// tensor, so no access needs a bounds check (every tile but the last).
+template <int W, int P, int MODE, bool FULL>
+__device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
+                                             uint64_t tile, int lane, unsigned char *lds)
+{
+    using M = MpShape<W, P>;
+    using T = MpTileTraits<W, P>;
+    constexpr int kPairs = (T::kTile / 2 + kWave - 1) / kWave, kBytes = T::slice_bytes(T::kGroups);
+    const uint64_t tile0 = tile * T::kTile;
+    unsigned char *verdict = lds + P * kBytes;
+
+    U64x2 xs[P][kPairs];
+    mp_load<P, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, xs);
+    mp_deposit<W, P, kPairs, T::kTile, kBytes>(lds, k, lane, xs);
+    wave_sync();
+
+    // ---- group lanes: collect the fields of group `lane`, run the adder tree, publish the verdict
+    if (T::kGroups == kWave || lane < T::kGroups) {
+        uint64_t u[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) u[q] = mp_collect<W, P, uint64_t, T::L>(lds + q * kBytes, lane);
+        const uint64_t g = tile * T::kGroups + lane;
+        const uint64_t zg = seedB + (g * (uint64_t)M::kWordsPerGroup + 1) * kGamma;
+        const Shares<P> sum = mp_a2b_sum<W, P>(u, zg);
+        mp_publish<W, P, uint64_t, T::L>(verdict, lane, sum, mix64(zg + (uint64_t)M::kB2aWord * kGamma));
+    }
+    wave_sync();
+    mp_finish_pairs<P, MODE, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
+}
+
+// The same on a quarter of a tile: 1170 vector instructions per wavefront at w = 8 among three parties where the tile has
+// 4250.  4,195,307 elements (8195 tiles: three after the last full round) take 70.5 us instead of 75.2; at w = 4, 55.3
+// instead of 72.4.
+template <int W, int P, int MODE, bool FULL>
+__device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
+                                                uint64_t quarter, int lane, unsigned char *lds)
+{
+    using M = MpShape<W, P>;
+    using T = MpTileTraits<W, P>;
+    using Q = MpQuarterTraits<W, P>;
+    using Word = typename Q::Word;
+    constexpr int kPairs = (Q::kTile / 2 + kWave - 1) / kWave, kBytes = T::slice_bytes(Q::kGroups);
+    const uint64_t tile0 = quarter * Q::kTile;
+    unsigned char *verdict = lds + Q::kVerdictAt;
+    U64x2 xs[P][kPairs];
+    mp_load<P, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, xs);
+
+    const int grp = lane / Q::kSplit, sub = lane % Q::kSplit, half = sub % 2;
+    const int slot = Q::kHalves ? 2 * grp + half : grp;
+    const uint64_t g = quarter * Q::kGroups + grp;
+    const uint64_t zs = seedB + (g * (uint64_t)M::kWordsPerGroup + 1 + (uint64_t)sub) * kGamma;
+    uint32_t *row = reinterpret_cast<uint32_t *>(lds + Q::kWordsAt) + grp * Q::kRow;
+    const int words_at = Q::kWordsAt + 4 * (grp * Q::kRow + (Q::kHalves ? half * Q::kPad : 0));
+
+    auto put = [&](int j, uint64_t v, int upper) {
+        if constexpr (Q::kHalves) {
+            row[j] = (uint32_t)v;
+            row[Q::kPad + j] = word_at(v, upper);
+        } else {
+            reinterpret_cast<uint64_t *>(row)[j] = v;
+        }
+    };
+    // every lane draws its share of an adder's dealer words, and with the last adder's one of them the B2A word
+    auto draw = [&](int adder) {
+#pragma unroll
+        for (int t = 0; t < (Q::kWords + Q::kSplit - 1) / Q::kSplit; ++t) {
+            const int j = t * Q::kSplit + sub;
+            if ((t + 1) * Q::kSplit <= Q::kWords || j < Q::kWords)
+                put(j, mix64(zs + (uint64_t)(adder * M::kAdderWords + t * Q::kSplit) * kGamma), Q::kFields * W);
+        }
+        if (adder == P - 2 && sub == 3) put(Q::kWords, mix64(zs + (uint64_t)(M::kB2aWord - 3) * kGamma), P * Q::kFields);
+    };
+    draw(0);                                                   // while the loads are under way
+    mp_deposit<W, P, kPairs, Q::kTile, kBytes>(lds, k, lane, xs);
+    wave_sync();
+
+    Word u[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) u[q] = mp_collect<W, P, Word, Q::kFields>(lds + q * kBytes, slot);
+    auto add = [&](int i, const Shares<P, Word> &X, const Shares<P, Word> &Y) {
+        if (i > 0) {
+            wave_sync();                                       // the adder before has read its words
+            draw(i);
+            wave_sync();
+        }
+        // one gate's words in registers at a time: read ahead, those of a whole adder would halve the kernel's occupancy
+        auto gate = [&](int q, Word after) {
+            int at = words_at;
+            asm("" : "+v"(at) : "v"(after));
+            const Word *words = reinterpret_cast<const Word *>(__builtin_assume_aligned(lds + at, 16)) + q * M::kGateWords;
+            return [words](int w) { return words[w]; };
+        };
+        return mp_add_gates<W, P, Word>(gate, X, Y);
+    };
+    const Shares<P, Word> sum = mp_tree<P, Word>(u, add);
+    if (sub < (Q::kHalves ? 2 : 1))
+        mp_publish<W, P, Word, Q::kFields>(verdict, slot, sum, reinterpret_cast<const Word *>(lds + words_at)[Q::kWords]);
+    wave_sync();
+    mp_finish_pairs<P, MODE, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
+}
+
 template <int W, int P, int MODE>
 __global__ void __launch_bounds__(kBlock)
-mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA)
+mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint32_t whole_blocks)
 {
     using T = MpTileTraits<W, P>;
     static_assert(T::kSupported, "tile kernel needs W <= 32");
-    __shared__ __attribute__((aligned(16))) unsigned char slices_all[kWavesPerBlock][P][T::kSliceBytes];
-    __shared__ U64x2 verdict_all[kWavesPerBlock][kWave];
-    __shared__ uint64_t sign_words_all[kWavesPerBlock][T::kSignWords ? kWave : 1][P];
+    extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wv;
-    if (tile * T::kTile >= n) return;        // whole wavefront beyond the tensor
-    if ((tile + 1) * T::kTile <= n)
-        mp_tile_body<W, P, MODE, true>(ptr, n, k, seedB, seedA, tile, lane, slices_all[wv], verdict_all[wv], sign_words_all[wv]);
+    const TileWork t = tile_work<W>(whole_blocks, wv);
+    if (t.tile * T::kTile >= n) return;        // whole wavefront beyond the tensor
+    if constexpr (quarters_supported(W)) {
+        if (t.quarter >= 0) {
+            using Q = MpQuarterTraits<W, P>;
+            const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
+            unsigned char *lds = tile_lds + wv * Q::kLdsBytes;
+            if ((quarter + 1) * Q::kTile <= n)
+                mp_quarter_body<W, P, MODE, true>(ptr, n, k, seedB, seedA, quarter, lane, lds);
+            else if (quarter * Q::kTile < n)
+                mp_quarter_body<W, P, MODE, false>(ptr, n, k, seedB, seedA, quarter, lane, lds);
+            return;
+        }
+    }
+    unsigned char *lds = tile_lds + wv * T::kLdsBytes;
+    if ((t.tile + 1) * T::kTile <= n)
+        mp_tile_body<W, P, MODE, true>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
     else
-        mp_tile_body<W, P, MODE, false>(ptr, n, k, seedB, seedA, tile, lane, slices_all[wv], verdict_all[wv], sign_words_all[wv]);
+        mp_tile_body<W, P, MODE, false>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
 }
 
 }  // namespace hb
