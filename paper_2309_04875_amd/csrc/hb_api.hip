@@ -483,29 +483,38 @@ LauncherTable &launcher_table()
     return table;
 }
 
-// A tile that runs alone on a SIMD takes as long as a full round of tiles, one per SIMD.  Launches of fewer than
-// small_tile_limit() tiles share every tile out by quarters; longer ones share out what is left after their last full round
-// where that is at most kSplitMost tiles, which then takes the time of one or two quarters instead of a tile's.
-// Measured, quarters against whole tiles: w = 8, 512 tiles 5.3 / 7.0 us, 900 6.9 / 7.1, 1088 (64 left) 7.5 / 9.9,
-// 1536 (512 left) 9.0 / 10.4, 4150 (54 left) 17.2 / 19.8; w = 10, 512 tiles 5.8 / 6.9, 900 7.9 / 7.2, 2100 (52 left) 10.8 / 13.4.
-// Three quarters' time (1700 tiles by quarters: 10.1 / 10.3) no longer pays.  Among more parties the gate logic, which the
-// four lanes of a group repeat in part, weighs more, and the first line lies lower: four parties at w = 16, 781 tiles by quarters
-// take 21.7 us where whole ones take 18.8; 4 tiles left after 16 rounds 209 where they took 221.
-constexpr uint64_t kSimds = 1024, kSplitMost = 512, kAllBelow = 900, kAllBelowMp = 512;
+// A tile that runs alone on a SIMD takes as long as a full round of tiles, one per SIMD.  256 tiles shared out by quarters are
+// one round of quarters; quarter_rounds says how many of those still cost less than a round of whole tiles, which
+// depends on how much of a quarter is spent on gate logic that its lanes repeat (most where a word has few fields) and on
+// idle owners.  Launches of up to that many rounds of quarters share every tile out, longer ones what is left after their last
+// full round, up to two rounds of quarters.  Measured (ReLU, us), quarters against whole tiles:
+//   w = 4   1000 tiles  9.1 / 10.0                       w = 8    768  6.0 / 7.4,    896  7.0 / 7.4 (DReLU 5.5 / 5.4)
+//   w = 6    768  7.9 / 8.6,    896  9.3 / 8.7           w = 12   768  6.8 / 7.6,    896  8.1 / 7.7
+//   w = 7    640  9.3 / 8.9 (72 pairs: two passes of the 64 lanes, the second one nearly empty)
+//   w = 16   640  6.2 / 5.9,   1400 (376 left) 7.8 / 8.2 w = 24   640  6.5 / 5.3,   1280 (256 left) 6.8 / 7.0, 1400  8.1 / 7.1
+// Among more parties the gate logic weighs more (four at w = 16, 781 tiles: 21.7 / 18.8).
+constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
+constexpr int quarter_rounds(int w, int parties)
+{
+    if (parties > 2) return w <= 12 ? 2 : 1;
+    return w == 4 ? 4 : w == 7 ? 2 : w <= 12 ? 3 : w <= 21 ? 2 : 1;
+}
 
-// HB_SMALL_TILE_LIMIT in the environment (read once) overrides the limit; 0 switches the quarters off.
-uint64_t small_tile_limit(int parties)
+// HB_SMALL_TILE_LIMIT in the environment (read once): launches of fewer tiles share every tile out; 0 switches the quarters off.
+uint64_t small_tile_limit(uint64_t usual)
 {
     static const char *const v = std::getenv("HB_SMALL_TILE_LIMIT");
     static const uint64_t given = v != nullptr ? (uint64_t)std::strtoull(v, nullptr, 10) : 0;
-    return v != nullptr ? given : parties == 2 ? kAllBelow : kAllBelowMp;
+    return v != nullptr ? given : usual;
 }
 
 TileGrid tile_grid(uint64_t tiles, int w, int parties)
 {
-    const uint64_t limit = small_tile_limit(parties), left = tiles % kSimds;
+    const uint64_t rounds = (uint64_t)quarter_rounds(w, parties), left = tiles % kSimds;
+    const uint64_t limit = small_tile_limit(rounds * kQuarterRound + 1), most = (rounds < 2 ? rounds : 2) * kQuarterRound;
     uint64_t split = 0;
-    if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= kSplitMost ? left : 0;
+    if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= most ? left : 0;
+    if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
     if (blocks > 0x7fffffffull) return TileGrid{0, 0, false};
     return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0};

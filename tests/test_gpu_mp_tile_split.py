@@ -1,4 +1,5 @@
-"""Three and four parties where tiles are shared out by quarters: sizes around the rule's lines (512 tiles, 1024 and 512 more),
+"""Three and four parties where tiles are shared out by quarters: sizes around the rule's lines (256 or 512 tiles, and
+1024 more),
 one element short of a tile or three into one.  Bit for bit against the oracle."""
 import numpy as np
 import pytest
@@ -16,7 +17,7 @@ SEED, DEV = 0x2309048750000055, "cuda"
 def test_sizes_around_the_lines(parties, w):
     k, per = 7, 64 * (64 // w)
     rng = np.random.default_rng(w)
-    for n in (3, per - 1, 511 * per - 1, 512 * per + 3, 1025 * per - 1, 1536 * per + 3):
+    for n in (3, per - 1, 256 * per - 1, 256 * per + 3, 512 * per + 3, 1025 * per - 1, 1536 * per + 3):
         host = [rng.integers(-2**62, 2**62, n, dtype=np.int64) for _ in range(parties)]
         dev = [torch.from_numpy(h).to(DEV) for h in host]
         for call, what in ((hb.hb_relu_mp, oracle.WHAT_RELU), (hb.hb_drelu_mp, oracle.WHAT_DRELU)):

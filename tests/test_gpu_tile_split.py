@@ -1,7 +1,7 @@
 """Launches whose last tiles are shared out by quarters: sizes around the rule's lines, bit for bit against the oracle.
 
-A tile has 64 groups.  Below 900 tiles every tile goes to a workgroup by quarters, above that what is left after the last
-1024 whole ones if it is at most 512; the tensors here end one element short of a tile or five elements into one (whose
+A tile has 64 groups.  Up to 256 to 1024 tiles, by width, every tile goes to a workgroup by quarters, above that what is left
+after the last 1024 whole ones if it is at most 256 or 512; the tensors here end one element short of a tile or five elements into one (whose
 other quarters are then empty), and the batched call has the line between whole and shared-out tiles inside a tensor.
 """
 import numpy as np
@@ -26,7 +26,7 @@ def _same(t, e):
     return np.array_equal(t.cpu().numpy(), e)
 
 
-@pytest.mark.parametrize("tiles", [1, 899, 900, 1025, 1536, 1537])
+@pytest.mark.parametrize("tiles", [1, 257, 513, 769, 1024, 1025, 1281, 1537])
 @pytest.mark.parametrize("w", [4, 6, 7, 8, 10, 20, 32])
 def test_single_tensor(w, tiles):
     k, per = 9, 64 * (64 // w)
