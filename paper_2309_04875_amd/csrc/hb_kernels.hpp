@@ -561,15 +561,6 @@ struct QuarterTraits {
     static constexpr int kLdsBytes = kVerdictAt + Verdict<W, MODE>::bytes(kGroups);
 };
 
-// Bits at .. at + 31 of v, 0 <= at <= 32, where `at` differs between lanes.  Not a 64-bit shift: with its amount in the last
-// vector register of the wavefront's allocation v_lshrrev_b64 has shifted by something else now and then (seen with the
-// amount in v63 of 64), and the compiler does not keep it from there.
-__device__ __forceinline__ uint32_t word_at(uint64_t v, int at)
-{
-    const uint32_t low = __builtin_amdgcn_alignbit((uint32_t)(v >> 32), (uint32_t)v, (uint32_t)at);
-    return at >= 32 ? (uint32_t)(v >> 32) : low;
-}
-
 template <int W, int MODE, bool FULL, class IO>
 __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                   uint64_t quarter, int lane, unsigned char *lds)

@@ -55,9 +55,12 @@ struct PartyTile {
     using Entry = typename std::conditional<(W <= 8), uint8_t,
                   typename std::conditional<(W <= 16), uint16_t,
                   typename std::conditional<(W <= 32), uint32_t, uint64_t>::type>::type>::type;
-    // LDS per wavefront: the slices, and in the same place, when they are dead, {sign word, dealer word} per lane
+    // LDS per wavefront: the slices, and in the same place, when they are dead, a byte (at W = 4 half a byte) per element
+    // and party: the bit that the party sends in the B2A, above it the dealer's bit r
     static constexpr int kSliceBytes = kPacked ? 8 * kWave : 2 * kTile * (int)sizeof(Entry);
-    static constexpr int kVerdictBytes = kWave * (int)sizeof(U64x2);
+    static constexpr int kVerdictBits = W == 4 ? 4 : 8;
+    static constexpr int kVerdictBytes = 2 * kTile * kVerdictBits / 8;
+    using VerdictPair = typename std::conditional<(W == 4), uint8_t, uint16_t>::type;
     static constexpr int kExchangeBytes = ((kSliceBytes > kVerdictBytes ? kSliceBytes : kVerdictBytes) + 15) / 16 * 16;
 };
 
@@ -158,7 +161,7 @@ __device__ __forceinline__ void party_tile_body(const PartyCtx &c, uint64_t tile
     uint64_t live = S::keep(0);
     if (!FULL) {
         const uint64_t first = g * (uint64_t)L;
-        if (here && c.n - first < (uint64_t)L) live = (1ull << ((c.n - first) * (uint64_t)W)) - 1;    // below 64 bits
+        if (here && c.n - first < (uint64_t)L) live = low_bits((int)(c.n - first) * W);               // below 64 bits
     }
     uint64_t u = 0;
     if constexpr (T::kPacked) {
@@ -216,17 +219,34 @@ __device__ __forceinline__ void party_tile_body(const PartyCtx &c, uint64_t tile
     }
 
     // ---- B2A message: sign share ^ dealer bit share, one bit per element ---------------------------------------
-    U64x2 *verdict = reinterpret_cast<U64x2 *>(lds);
+    // The group's lane publishes a byte per element, which an owner finds at its element's index.  (Finding the group and
+    // shifting its words by the field's place takes 64-bit shifts by an amount that differs between lanes: word_at.)
+    unsigned char *verdict = lds + p * (T::kVerdictBytes / 2);
     wave_sync();
-    verdict[lane] = U64x2{(u ^ ((G << 1) & S::keep(1))) >> (W - 1), wb};      // sign of field j at bit jW; rho_p at bit 2j + p
+    {
+        const uint64_t sign = (u ^ ((G << 1) & S::keep(1))) >> (W - 1);                       // bit jW: sign share
+        const uint64_t own_rho = ((wb >> 1) & party1) | (wb & party0), rx = wb ^ (wb >> 1);   // bit 2j: rho_p, r
+        if constexpr (T::kVerdictBits == W) {                                                 // the word's fields
+            using V = Verdict<W, kRelu>;
+            const uint64_t v = ((sign & S::ones()) ^ V::template spread<uint64_t>(own_rho)) | (V::template spread<uint64_t>(rx) << 1);
+            reinterpret_cast<uint64_t *>(lds)[lane] = v;
+        } else {
+            constexpr uint64_t kEven = 0x5555555555555555ull;
+            const uint64_t q = (own_rho & kEven) | ((rx & kEven) << 1);
+#pragma unroll
+            for (int j = 0; j < L; ++j) {
+                const uint32_t rho = 2 * j < 32 ? (uint32_t)q >> (2 * j % 32) : (uint32_t)(q >> 32) >> (2 * j % 32);
+                verdict[l * L + j] = (unsigned char)(Verdict<5, kRelu>::bit_at(sign, j * W) ^ rho);   // two bits are looked at
+            }
+        }
+    }
     wave_sync();
     uint32_t message = 0, opened = 0;           // lane t < L of a half: bits of elements 32t .. 32t + 31 of the tile
 #pragma unroll
     for (int t = 0; t < L; ++t) {
-        const int e = t * kHalfWave + l, grp = e / L, j = e - grp * L;
-        const U64x2 v = verdict[p * kHalfWave + grp];
-        const uint32_t bit = (uint32_t)((v.a >> (j * W)) ^ (v.b >> (2 * j + p))) & 1u;
-        const uint64_t sent = __ballot(bit != 0 && (FULL || tile0 + e < c.n));    // party 0's bits, then party 1's
+        const int e = t * kHalfWave + l;
+        const uint32_t own = W == 4 ? (uint32_t)verdict[e / 2] >> (4 * (l & 1)) : verdict[e];
+        const uint64_t sent = __ballot((own & 1) != 0 && (FULL || tile0 + e < c.n));    // party 0's bits, then party 1's
         const uint32_t lo = (uint32_t)sent, hi = (uint32_t)(sent >> 32);
         if (l == t) {
             message = p ? hi : lo;
@@ -245,14 +265,19 @@ __device__ __forceinline__ void party_tile_body(const PartyCtx &c, uint64_t tile
 
     // ---- multiply: send x_p - a_p and DReLU_p - b_p, then finish, one element pair per lane at a time ---------
     const uint64_t zA0 = c.seedA + (6 * (tile0 + 2 * (uint64_t)l) + 1) * kGamma;       // A[6i] of the lane's first element
+    // In the tensor's last tile every pair has addresses and bounds of its own; worked out again here they are not kept across
+    // the circuit.  At W = 4 that is 124 vector registers, four wavefronts per SIMD, instead of 139 and three.
+    int own_l = l;
+    if constexpr (W == 4 && !FULL) asm("" : "+v"(own_l));
 #pragma unroll
     for (int i = 0; i < T::kPairs; ++i) {
-        const int pr = i * kHalfWave + l;
+        const int pr = i * kHalfWave + own_l;
         const unsigned e = 2 * pr;
         const bool two = e < (unsigned)T::kTile && (FULL || tile0 + e + 1 < c.n);
         const bool one = !FULL && !two && e < (unsigned)T::kTile && tile0 + e < c.n;
         const uint64_t zA = zA0 + (uint64_t)(12 * i * kHalfWave) * kGamma;
         const uint32_t zw = opened_bits[(e / kHalfWave) % L] >> (e % kHalfWave);
+        const uint32_t both = reinterpret_cast<const typename T::VerdictPair *>(verdict)[e < (unsigned)T::kTile ? pr : 0];
         // r^A_0 and c_0 of the pair's first element from the lower half, of its second from the upper half
         const uint64_t zh = zA + (6 * kGamma & party1);
         const Pair rA0 = dealt(mix64(zh)), c0 = dealt(mix64(zh + 5 * kGamma));
@@ -261,9 +286,7 @@ __device__ __forceinline__ void party_tile_body(const PartyCtx &c, uint64_t tile
         for (int h = 0; h < 2; ++h) {
             const int32_t m = minus_bit(zw, h);
             const uint64_t mm = (uint64_t)(int64_t)m;
-            const unsigned eh = (e + h) % (unsigned)T::kTile, grp = eh / L, j = eh - grp * L;
-            const uint32_t rho = (uint32_t)(verdict[grp].b >> (2 * j));
-            const uint32_t r = (rho ^ (rho >> 1)) & (uint32_t)p;               // in party 1's r^A_1 = r - r^A_0 only
+            const uint32_t r = (both >> (T::kVerdictBits * h + 1)) & (uint32_t)p;            // in party 1's r^A_1 = r - r^A_0 only
             // as in b2a_shares: (~r^A_0 ^ m) + 2 (1 - z) for party 0, ~((~r^A_0 + r) ^ m) + z for party 1
             const uint64_t D = ((~(h ? rA0.p1 : rA0.p0) + r) ^ mm ^ party1) + (uint32_t)(p ? -m : 2 * (m + 1));
             a[h] = mix64(zA + (uint64_t)(6 * h + 1) * kGamma + own);           // A[6i+1] / A[6i+2]
@@ -295,8 +318,11 @@ __device__ __forceinline__ void party_tile_body(const PartyCtx &c, uint64_t tile
     }
 }
 
+// At most four wavefronts per SIMD (two for W <= 2), whatever registers would allow: the writes of more of them get in one
+// another's way.  4,000,000 elements, us, with and without the bound: w = 1 63.8 / 67.5, w = 9 108.5 / 112.7, w = 12 107.4 /
+// 110.6, w = 48 368 / 392.
 template <int W, bool SHARED>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, (W <= 2 ? 2 : 4))))
 party_tile_kernel(const PartyCtx c)
 {
     using T = PartyTile<W>;

@@ -104,6 +104,26 @@ __device__ __forceinline__ uint64_t bitop3(uint64_t a, uint64_t b, uint64_t c)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// ---- shifts of 64-bit values by an amount that differs between lanes ---------------------------------------------
+// No kernel has the 64-bit shift instruction with its amount in a vector register: where that was the last vector register
+// of a wavefront's allocation (v63 of 64, the DReLU kernel of w = 10), whole wavefronts got wrong results now and then, and
+// the compiler does not keep the amount from there.  That this instruction was the cause is inferred: of the kernels run
+// against the oracle only the one with that assignment failed, and without the instruction it no longer did.  The built
+// library is searched for the form by a test.
+
+// Bits at .. at + 31 of v, 0 <= at <= 32.
+__device__ __forceinline__ uint32_t word_at(uint64_t v, int at)
+{
+    const uint32_t low = __builtin_amdgcn_alignbit((uint32_t)(v >> 32), (uint32_t)v, (uint32_t)at);
+    return at >= 32 ? (uint32_t)(v >> 32) : low;
+}
+// The lowest `count` bits set, 0 <= count < 64.
+__device__ __forceinline__ uint64_t low_bits(int count)
+{
+    const uint32_t part = (1u << (count & 31)) - 1;
+    return count < 32 ? part : ((uint64_t)part << 32) | 0xffffffffu;
+}
+
 template <class Word>
 struct GateWords {   // the five dealer words of one AND gate, in stream order
     Word a0, a1, b0, b1, c0;
