@@ -513,10 +513,14 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
     wave_sync();
 
     // ---- owners: pick up the verdict of each element's group, finish, store ---------------------
-    const uint64_t zA0 = seedA + (6 * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;   // A[6i] of the lane's first element
+    // In a tensor's last tile every pair has addresses and bounds of its own: worked out again here they are not kept in
+    // registers across the circuit
+    int own = lane;
+    if constexpr (!FULL) asm("" : "+v"(own));
+    const uint64_t zA0 = seedA + (6 * (tile0 + 2 * (uint64_t)own) + 1) * kGamma;   // A[6i] of the lane's first element
 #pragma unroll
     for (int c = 0; c < T::kPairs; ++c) {
-        const int pr = c * kWave + lane, e = 2 * pr;
+        const int pr = c * kWave + own, e = 2 * pr;
         if (e < T::kTile) {
             Pair r[2];
             finish_pair<W, MODE>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
@@ -644,8 +648,7 @@ __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int 
     }
 }
 
-// LDS of a workgroup.  It is allocated at launch, so that a launch without quarters, whose rows of dealer words are the
-// larger part, keeps room for more workgroups per compute unit.
+// LDS of a workgroup, allocated at launch.
 template <int W, int MODE>
 constexpr int whole_lds_bytes()
 {
@@ -669,24 +672,28 @@ __device__ __forceinline__ int wave_index()
 }
 
 // Which part of a launch a wavefront takes: workgroups 0 .. whole_blocks - 1 take four tiles each, the others one tile each.
+// Every tile kernel exists twice.  The one with QUARTERS holds both forms, and with them the larger one's registers and LDS
+// for every workgroup (ReLU at w = 24: 72 registers and 28 KiB; whole tiles alone 60 and 5 KiB, eight wavefronts per SIMD instead
+// of five), so launches without shared-out tiles take the one without: w = 24 on the shared-mask layout, 640 tiles 4.43 us instead
+// of 4.88, 1536 tiles 6.57 instead of 7.01; three parties at w = 4, DReLU, 4 M elements 37 instead of 41.
 struct TileWork {
     uint64_t tile;
     int quarter;        // -1: the whole tile
 };
-template <int W>
+template <bool QUARTERS>
 __device__ __forceinline__ TileWork tile_work(uint32_t whole_blocks, int wv)
 {
     const uint32_t b = blockIdx.x;
-    const bool split = quarters_supported(W) && b >= whole_blocks;
+    const bool split = QUARTERS && b >= whole_blocks;
     return TileWork{split ? (uint64_t)whole_blocks * (kWavesPerBlock - 1) + b : (uint64_t)b * kWavesPerBlock + wv, split ? wv : -1};
 }
 
 // t.tile must be uniform over the wavefront; the tile lies inside the tensor at least in part.
-template <int W, int MODE, class IO>
+template <int W, int MODE, bool QUARTERS, class IO>
 __device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA, TileWork t, int lane, int wv,
                                           unsigned char *tile_lds)
 {
-    if constexpr (quarters_supported(W)) {
+    if constexpr (QUARTERS) {
         if (t.quarter >= 0) {
             using Q = QuarterTraits<W, MODE>;
             const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
@@ -705,16 +712,23 @@ __device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint6
         tile_body_impl<W, MODE, false>(io, n, k, seedB, seedA, t.tile, lane, lds);
 }
 
-template <int W, int MODE>
-__global__ void __launch_bounds__(kBlock)
+// Wavefronts per SIMD that the registers of a kernel of whole tiles have to leave room for, where the compiler's own choice
+// is fewer (ReLU at w = 9, 10: 128 and 108 registers instead of 87 and 79; w = 13..16 on the shared-mask layout 73 instead of 72).
+constexpr int whole_tile_waves(int w, int op)
+{
+    return op != kRelu ? 1 : w == 9 || w == 10 ? 5 : w >= 13 && w <= 16 ? 7 : 1;
+}
+
+template <int W, int MODE, bool QUARTERS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUARTERS ? 1 : whole_tile_waves(W, op_of(MODE)))))
 tile_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t *o0,
             uint64_t *o1, uint32_t whole_blocks)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<W>(whole_blocks, wv);
+    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
     if (t.tile * TileTraits<W>::kTile >= n) return;        // whole wavefront beyond the tensor (uniform per wave)
-    tile_body<W, MODE>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, t, lane, wv, tile_lds);
+    tile_body<W, MODE, QUARTERS>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, t, lane, wv, tile_lds);
 }
 
 // Several tensors of one slice width in a single launch.  The descriptors travel in the kernel
@@ -740,13 +754,13 @@ struct BatchArgs {
     int count;
 };
 
-template <int W, int MODE>
-__global__ void __launch_bounds__(kBlock)
+template <int W, int MODE, bool QUARTERS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUARTERS ? 1 : whole_tile_waves(W, op_of(MODE)))))
 tile_batch_kernel(const BatchArgs args)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    TileWork t = tile_work<W>(args.whole_blocks, wv);                          // tile number over the whole batch
+    TileWork t = tile_work<QUARTERS>(args.whole_blocks, wv);                          // tile number over the whole batch
     const uint32_t gt = (uint32_t)t.tile;                                      // below 2^31 + 4
     if (gt >= args.tiles) return;
     int ti = 0;
@@ -754,7 +768,7 @@ tile_batch_kernel(const BatchArgs args)
     for (int i = 0; i < kBatchMax; ++i) ti += (int)((args.tile_end[i] - 1 - gt) >> 31);   // scalar: the borrow, not a comparison
     const BatchTensor &d = args.t[__builtin_amdgcn_readfirstlane(ti)];
     t.tile = gt - d.first_tile;
-    tile_body<W, MODE>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, t, lane, wv, tile_lds);
+    tile_body<W, MODE, QUARTERS>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, t, lane, wv, tile_lds);
 }
 
 // The simulator kernel: ReLU on plaintext floats through the whole protocol, 8 bytes of traffic per element.
@@ -776,15 +790,15 @@ wide_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seed
     y[i] = decode_fixed16(r.p0 + r.p1);
 }
 
-template <int W>
+template <int W, bool QUARTERS>
 __global__ void __launch_bounds__(kBlock)
 tile_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t seedS, float *y, uint32_t whole_blocks)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<W>(whole_blocks, wv);
+    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
     if (t.tile * TileTraits<W>::kTile >= n) return;
-    tile_body<W, kRelu>(FloatIO{x, y, seedS}, n, k, seedB, seedA, t, lane, wv, tile_lds);
+    tile_body<W, kRelu, QUARTERS>(FloatIO{x, y, seedS}, n, k, seedB, seedA, t, lane, wv, tile_lds);
 }
 
 }  // namespace hb

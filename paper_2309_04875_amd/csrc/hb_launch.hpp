@@ -47,6 +47,16 @@ struct TileGrid {
 };
 TileGrid tile_grid(uint64_t tiles, int w, int parties = 2);
 
+// go(std::true_type) where tiles of the grid are shared out, go(std::false_type) otherwise.
+template <int W, class Go>
+hipError_t with_quarters(const TileGrid &grid, const Go &go)
+{
+    if constexpr (quarters_supported(W)) {
+        if (grid.quarters) return go(std::true_type{});
+    }
+    return go(std::false_type{});
+}
+
 // Debug knob: HB_KERNEL=group in the environment (read once) sends every width to the thread-per-group kernel.
 bool force_group_kernel();
 

@@ -21,9 +21,13 @@ hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int 
         if (!hb::force_group_kernel()) {
             const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-            hipLaunchKernelGGL((hb::tile_kernel<W, MODE>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(grid.quarters)), stream, x0, x1, n, k,
-                               seedB, seedA, o0, o1, grid.whole_blocks);
-            return hipGetLastError();
+            auto go = [&](auto quarters) {
+                constexpr bool kQuarters = decltype(quarters)::value;
+                hipLaunchKernelGGL((hb::tile_kernel<W, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(kQuarters)),
+                                   stream, x0, x1, n, k, seedB, seedA, o0, o1, grid.whole_blocks);
+                return hipGetLastError();
+            };
+            return hb::with_quarters<W>(grid, go);
         }
     }
     if (vec16) {
@@ -42,8 +46,13 @@ hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
     if constexpr (hb::TileTraits<W>::kSupported) {
         const hb::TileGrid grid = hb::tile_grid(args.tiles, W);
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(grid.quarters)), stream, args);
-        return hipGetLastError();
+        auto go = [&](auto quarters) {
+            constexpr bool kQuarters = decltype(quarters)::value;
+            hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(kQuarters)),
+                               stream, args);
+            return hipGetLastError();
+        };
+        return hb::with_quarters<W>(grid, go);
     } else {
         return hipErrorInvalidDeviceFunction;
     }
@@ -58,9 +67,13 @@ hipError_t launch_sim(const float *x, uint64_t n, int k, uint64_t seedB, uint64_
     } else if constexpr (hb::TileTraits<W>::kSupported) {
         const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::tile_sim_kernel<W>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, hb::kRelu>(grid.quarters)), stream, x, n, k, seedB,
-                           seedA, seedS, y, grid.whole_blocks);
-        return hipGetLastError();
+        auto go = [&](auto quarters) {
+            constexpr bool kQuarters = decltype(quarters)::value;
+            hipLaunchKernelGGL((hb::tile_sim_kernel<W, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, hb::kRelu>(kQuarters)),
+                               stream, x, n, k, seedB, seedA, seedS, y, grid.whole_blocks);
+            return hipGetLastError();
+        };
+        return hb::with_quarters<W>(grid, go);
     } else {
         const uint64_t blocks = (n + hb::kBlock - 1) / hb::kBlock;
         if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;

@@ -17,9 +17,13 @@ hipError_t launch_mp(const hb::MpPointers &ptr, uint64_t n, int k, uint64_t seed
         if (!hb::force_group_kernel()) {
             const hb::TileGrid grid = hb::tile_grid((n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile, W, P);
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-            hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE>), dim3(grid.blocks), dim3(hb::kBlock),
-                               (hb::mp_lds_bytes<W, P>(grid.quarters)), stream, ptr, n, k, seedB, seedA, grid.whole_blocks);
-            return hipGetLastError();
+            auto go = [&](auto quarters) {
+                constexpr bool kQuarters = decltype(quarters)::value;
+                hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::mp_lds_bytes<W, P>(kQuarters)),
+                                   stream, ptr, n, k, seedB, seedA, grid.whole_blocks);
+                return hipGetLastError();
+            };
+            return hb::with_quarters<W>(grid, go);
         }
     }
     constexpr uint64_t L = hb::MpShape<W, P>::L;

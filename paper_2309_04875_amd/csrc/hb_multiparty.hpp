@@ -307,43 +307,37 @@ constexpr unsigned mp_lds_bytes(bool quarters)
     return (unsigned)(kWavesPerBlock * most);
 }
 
-// Owners' part before the circuit: the pairs of all parties (PAIRS per lane of TILE elements), and their slices.
+// Owners' part before the circuit: pair c of a lane (of PAIRS, in a tile of TILE elements) from all parties, and its slices.
 template <int P, int PAIRS, int TILE, bool FULL>
-__device__ __forceinline__ void mp_load(const MpPointers &ptr, uint64_t tile0, uint64_t n, int lane, U64x2 (&xs)[P][PAIRS])
+__device__ __forceinline__ void mp_load(const MpPointers &ptr, uint64_t tile0, uint64_t n, int lane, int c, U64x2 (&xs)[P][PAIRS])
 {
+    const unsigned e = 2 * (c * kWave + lane);
 #pragma unroll
-    for (int c = 0; c < PAIRS; ++c) {
-        const unsigned e = 2 * (c * kWave + lane);
+    for (int q = 0; q < P; ++q) xs[q][c] = U64x2{0, 0};
+    if (e < (unsigned)TILE) {
 #pragma unroll
-        for (int q = 0; q < P; ++q) xs[q][c] = U64x2{0, 0};
-        if (e < (unsigned)TILE) {
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                const uint64_t *t = ptr.x[q] + tile0;       // scalar base, 32-bit lane offset
-                if (FULL || tile0 + e + 1 < n) {
-                    xs[q][c] = load_stream2(t + e);
-                } else if (tile0 + e < n) {
-                    xs[q][c].a = load_stream(t + e);
-                }
+        for (int q = 0; q < P; ++q) {
+            const uint64_t *t = ptr.x[q] + tile0;       // scalar base, 32-bit lane offset
+            if (FULL || tile0 + e + 1 < n) {
+                xs[q][c] = load_stream2(t + e);
+            } else if (tile0 + e < n) {
+                xs[q][c].a = load_stream(t + e);
             }
         }
     }
 }
 template <int W, int P, int PAIRS, int TILE, int BYTES>
-__device__ __forceinline__ void mp_deposit(unsigned char *lds, int k, int lane, const U64x2 (&xs)[P][PAIRS])
+__device__ __forceinline__ void mp_deposit(unsigned char *lds, int k, int lane, int c, const U64x2 (&xs)[P][PAIRS])
 {
     using S = Shape<W>;
     using Entry = typename MpTileTraits<W, P>::Entry;
+    const unsigned e = 2 * (c * kWave + lane);
+    if (e < (unsigned)TILE) {
 #pragma unroll
-    for (int c = 0; c < PAIRS; ++c) {
-        const unsigned e = 2 * (c * kWave + lane);
-        if (e < (unsigned)TILE) {
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                Entry *sl = reinterpret_cast<Entry *>(lds + q * BYTES);
-                sl[e] = (Entry)((xs[q][c].a >> k) & S::kField);
-                sl[e + 1] = (Entry)((xs[q][c].b >> k) & S::kField);
-            }
+        for (int q = 0; q < P; ++q) {
+            Entry *sl = reinterpret_cast<Entry *>(lds + q * BYTES);
+            sl[e] = (Entry)((xs[q][c].a >> k) & S::kField);
+            sl[e + 1] = (Entry)((xs[q][c].b >> k) & S::kField);
         }
     }
 }
@@ -388,6 +382,7 @@ __device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t 
                                                 const U64x2 (&xs)[P][PAIRS], const unsigned char *verdict)
 {
     constexpr uint64_t kArithWords = 4 * P - 2;
+    if constexpr (!FULL) asm("" : "+v"(lane));                 // as in tile_body_impl
     uint64_t zA0 = seedA + (kArithWords * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
 #pragma unroll
     for (int c = 0; c < PAIRS; ++c) {
@@ -431,8 +426,11 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
     unsigned char *verdict = lds + P * kBytes;
 
     U64x2 xs[P][kPairs];
-    mp_load<P, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, xs);
-    mp_deposit<W, P, kPairs, T::kTile, kBytes>(lds, k, lane, xs);
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) {          // pair by pair: DReLU at w = 4 would hold 96 registers of shares at once
+        mp_load<P, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, c, xs);
+        mp_deposit<W, P, kPairs, T::kTile, kBytes>(lds, k, lane, c, xs);
+    }
     wave_sync();
 
     // ---- group lanes: collect the fields of group `lane`, run the adder tree, publish the verdict
@@ -464,7 +462,8 @@ __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t 
     const uint64_t tile0 = quarter * Q::kTile;
     unsigned char *verdict = lds + Q::kVerdictAt;
     U64x2 xs[P][kPairs];
-    mp_load<P, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, xs);
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) mp_load<P, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, c, xs);
 
     const int grp = lane / Q::kSplit, sub = lane % Q::kSplit, half = sub % 2;
     const int slot = Q::kHalves ? 2 * grp + half : grp;
@@ -492,7 +491,8 @@ __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t 
         if (adder == P - 2 && sub == 3) put(Q::kWords, mix64(zs + (uint64_t)(M::kB2aWord - 3) * kGamma), P * Q::kFields);
     };
     draw(0);                                                   // while the loads are under way
-    mp_deposit<W, P, kPairs, Q::kTile, kBytes>(lds, k, lane, xs);
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) mp_deposit<W, P, kPairs, Q::kTile, kBytes>(lds, k, lane, c, xs);
     wave_sync();
 
     Word u[P];
@@ -520,7 +520,7 @@ __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t 
     mp_finish_pairs<P, MODE, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
 }
 
-template <int W, int P, int MODE>
+template <int W, int P, int MODE, bool QUARTERS>
 __global__ void __launch_bounds__(kBlock)
 mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint32_t whole_blocks)
 {
@@ -528,9 +528,9 @@ mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t
     static_assert(T::kSupported, "tile kernel needs W <= 32");
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<W>(whole_blocks, wv);
+    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
     if (t.tile * T::kTile >= n) return;        // whole wavefront beyond the tensor
-    if constexpr (quarters_supported(W)) {
+    if constexpr (QUARTERS) {
         if (t.quarter >= 0) {
             using Q = MpQuarterTraits<W, P>;
             const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
