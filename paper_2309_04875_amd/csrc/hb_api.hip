@@ -229,7 +229,7 @@ int plan_launches(int mode, const hb_tensor *tensors, size_t count, std::vector<
             for (uint32_t &e : it.args.tile_end) e = hb::kNoTile;
         };
         auto finish = [&] {
-            it.args.whole_blocks = hb::tile_grid(it.args.tiles, w).whole_blocks;
+            it.args.whole_blocks = hb::tile_grid(it.args.tiles, w, 2, hb::op_of(mode)).whole_blocks;
             items.push_back(it);
         };
         start();
@@ -485,19 +485,53 @@ LauncherTable &launcher_table()
 
 // A tile that runs alone on a SIMD takes as long as a full round of tiles, one per SIMD.  256 tiles shared out by quarters are
 // one round of quarters; quarter_rounds says how many of those still cost less than a round of whole tiles, which
-// depends on how much of a quarter is spent on gate logic that its lanes repeat (most where a word has few fields) and on
-// idle owners.  Launches of up to that many rounds of quarters share every tile out, longer ones what is left after their last
-// full round, up to two rounds of quarters.  Measured (ReLU, us), quarters against whole tiles:
-//   w = 4   1000 tiles  9.1 / 10.0                       w = 8    768  6.0 / 7.4,    896  7.0 / 7.4 (DReLU 5.5 / 5.4)
-//   w = 6    768  7.9 / 8.6,    896  9.3 / 8.7           w = 12   768  6.8 / 7.6,    896  8.1 / 7.7
-//   w = 7    640  9.3 / 8.9 (72 pairs: two passes of the 64 lanes, the second one nearly empty)
-//   w = 16   640  6.2 / 5.9,   1400 (376 left) 7.8 / 8.2 w = 24   640  6.5 / 5.3,   1280 (256 left) 6.8 / 7.0, 1400  8.1 / 7.1
-// Among more parties the gate logic weighs more (four at w = 16, 781 tiles: 21.7 / 18.8).
+// depends on how much of a quarter is spent on gate logic that its lanes repeat (most where a word has few fields), on idle
+// owners, and on what an operation spends beside the dealer's words.  Launches of up to that many rounds of quarters share every
+// tile out.  Measured, us, quarters / whole tiles:
+//              w     512 tiles     768 tiles     1024 tiles                  w     512           768           1024
+//   ReLU       4     5.6 /  9.1    7.0 / 10.1    8.4 / 10.4      sign        4     4.1 /  5.3    5.0 /  5.8    6.2 /  6.8
+//              6     6.0 /  7.8    7.5 /  7.9    8.9 /  8.1                  6     3.9 /  5.0    4.5 /  5.2    5.1 /  5.5
+//              7     7.5 /  8.4    9.1 /  8.5                                7     4.2 /  5.2    4.9 /  5.4    5.7 /  5.7
+//              8     4.5 /  6.8    5.5 /  6.9    6.6 /  7.1                 10     3.8 /  4.7    4.4 /  4.8    5.1 /  5.0
+//             10     4.8 /  6.5    6.0 /  6.6    7.2 /  6.7                 12     4.2 /  4.9    5.0 /  5.1    5.8 /  5.2
+//             12     5.1 /  6.8    6.6 /  7.0    8.0 /  7.1      simulator   4     5.9 /  9.8    7.7 /  9.9    9.5 / 10.1
+//             16     4.7 /  4.9    5.8 /  5.0                                6     6.5 /  7.8    8.4 /  7.9
+//             24     5.0 /  4.6 (256: 3.8 / 4.5)                             7     7.9 /  7.8 (256: 6.4 / 7.8)
+//   DReLU      4     3.9 /  6.0    5.2 /  6.3    5.9 /  7.2                  8     4.6 /  6.4    5.6 /  6.5    6.8 /  6.7
+//              8     3.7 /  4.7    4.3 /  4.8    5.2 /  5.1                 12     5.3 /  6.3    6.8 /  6.3
+//             12     4.4 /  5.2    5.4 /  5.5    6.4 /  5.6      four        4    12.8 / 26.1   17.6 / 28.4   22.7 / 33.0
+//   three      4     8.7 / 15.5   12.6 / 15.9   15.6 / 16.8                  6    14.6 / 19.8   20.5 / 20.0   25.3 / 20.5
+//              6     9.8 / 12.8   12.4 / 12.9   15.3 / 13.2                  8    12.1 / 17.4   15.4 / 17.6   19.2 / 17.9
+//             16     8.0 /  9.8   10.5 /  9.9                               16    13.2 / 16.4   17.3 / 16.6
+// (ReLU at w = 4, 1280 tiles: 10.2, as 1024 whole ones and 256 by quarters 11.6.  w = 7 has 72 pairs in a quarter: two passes
+// of the 64 lanes, the second one nearly empty.)
 constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
-constexpr int quarter_rounds(int w, int parties)
+constexpr int quarter_rounds(int w, int parties, int op)
 {
-    if (parties > 2) return w <= 12 ? 2 : 1;
-    return w == 4 ? 4 : w == 7 ? 2 : w <= 12 ? 3 : w <= 21 ? 2 : 1;
+    if (parties > 2) return w == 4 ? 4 : w == 5 || w == 8 || (parties == 3 && (w == 6 || w == 10)) ? 3 : 2;
+    if (w > 12) return w <= 21 ? 2 : 1;
+    if (op == kSimulator) return w == 4 ? 4 : w == 7 ? 1 : w == 6 || w >= 11 ? 2 : 3;
+    if (op == kSign) return w <= 6 || w == 8 ? 4 : 3;
+    if (op == kDrelu) return w <= 5 ? 4 : 3;
+    return w == 4 ? 5 : w == 8 ? 4 : w == 7 ? 2 : 3;
+}
+// Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
+// w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third would give ReLU at w = 8 (766 left: 8.9 / 10.3) what it takes from DReLU at w = 5
+// (after two full rounds 13.4 / 11.5).  One round only
+//   - from w = 22, among more parties from w = 13 on, and of the simulator at w = 7 and from w = 17 on (376 left 9.0 / 8.8),
+//   - of sign shares at w = 5 and 6 after two full rounds (452 left 11.4 / 11.1 and 9.8 / 8.7; after one 6.2 / 6.8, after three
+//     15.9 / 17.2 and 12.9 / 13.9): three rounds of them reside together and wait for memory alone.
+// None where the quarter form's registers and LDS, which every workgroup of the launch then has, cost a long launch as much as a
+// round saves it: after 16 full rounds from w = 22 on (32 rounds and 8 tiles, shared-mask ReLU at w = 24 76.8 / 76.0), after 32
+// from w = 17 on among more parties (85 rounds and 8 tiles, four at w = 17 1289 / 1275).
+constexpr uint64_t shared_remainder(uint64_t tiles, int w, int parties, int op)
+{
+    const uint64_t full = tiles / kSimds;
+    if (parties > 2 ? w >= 17 && full >= 32 : w >= 22 && full >= 16) return 0;
+    if (parties > 2 ? w >= 13 : w >= 22) return kQuarterRound;
+    if (op == kSimulator && (w == 7 || w >= 17)) return kQuarterRound;
+    if (op == kSign && (w == 5 || w == 6) && full == 2) return kQuarterRound;
+    return 2 * kQuarterRound;
 }
 
 // HB_SMALL_TILE_LIMIT in the environment (read once): launches of fewer tiles share every tile out; 0 switches the quarters off.
@@ -508,12 +542,12 @@ uint64_t small_tile_limit(uint64_t usual)
     return v != nullptr ? given : usual;
 }
 
-TileGrid tile_grid(uint64_t tiles, int w, int parties)
+TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
 {
-    const uint64_t rounds = (uint64_t)quarter_rounds(w, parties), left = tiles % kSimds;
-    const uint64_t limit = small_tile_limit(rounds * kQuarterRound + 1), most = (rounds < 2 ? rounds : 2) * kQuarterRound;
+    const uint64_t left = tiles % kSimds;
+    const uint64_t limit = small_tile_limit((uint64_t)quarter_rounds(w, parties, op) * kQuarterRound + 1);
     uint64_t split = 0;
-    if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= most ? left : 0;
+    if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= shared_remainder(tiles, w, parties, op) ? left : 0;
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
     if (blocks > 0x7fffffffull) return TileGrid{0, 0, false};

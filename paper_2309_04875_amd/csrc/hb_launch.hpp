@@ -45,7 +45,9 @@ struct TileGrid {
     uint32_t whole_blocks, blocks;       // blocks 0: more than a grid holds
     bool quarters;                       // blocks > whole_blocks
 };
-TileGrid tile_grid(uint64_t tiles, int w, int parties = 2);
+// op: kDrelu, kRelu, kSign or kSimulator.
+constexpr int kSimulator = 3;
+TileGrid tile_grid(uint64_t tiles, int w, int parties, int op);
 
 // go(std::true_type) where tiles of the grid are shared out, go(std::false_type) otherwise.
 template <int W, class Go>

@@ -19,7 +19,7 @@ hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int 
     if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     if constexpr (hb::TileTraits<W>::kSupported) {
         if (!hb::force_group_kernel()) {
-            const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
+            const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W, 2, hb::op_of(MODE));
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
             auto go = [&](auto quarters) {
                 constexpr bool kQuarters = decltype(quarters)::value;
@@ -44,7 +44,7 @@ template <int W, int MODE>
 hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
 {
     if constexpr (hb::TileTraits<W>::kSupported) {
-        const hb::TileGrid grid = hb::tile_grid(args.tiles, W);
+        const hb::TileGrid grid = hb::tile_grid(args.tiles, W, 2, hb::op_of(MODE));
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
         auto go = [&](auto quarters) {
             constexpr bool kQuarters = decltype(quarters)::value;
@@ -65,7 +65,7 @@ hipError_t launch_sim(const float *x, uint64_t n, int k, uint64_t seedB, uint64_
     if constexpr (HB_PART_MODE != hb::kRelu) {
         return hipErrorInvalidDeviceFunction;
     } else if constexpr (hb::TileTraits<W>::kSupported) {
-        const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W);
+        const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W, 2, hb::kSimulator);
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
         auto go = [&](auto quarters) {
             constexpr bool kQuarters = decltype(quarters)::value;

@@ -15,7 +15,7 @@ hipError_t launch_mp(const hb::MpPointers &ptr, uint64_t n, int k, uint64_t seed
 {
     if constexpr (hb::MpTileTraits<W, P>::kSupported) {
         if (!hb::force_group_kernel()) {
-            const hb::TileGrid grid = hb::tile_grid((n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile, W, P);
+            const hb::TileGrid grid = hb::tile_grid((n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile, W, P, MODE);
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
             auto go = [&](auto quarters) {
                 constexpr bool kQuarters = decltype(quarters)::value;
