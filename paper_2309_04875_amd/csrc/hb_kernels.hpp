@@ -268,8 +268,9 @@ struct Slices {
 
 // ---- what a group lane publishes for the owners of its elements -------------------------------------------------
 // Two bits per element: the opened bit z and the dealer's bit r (B2aBits), or the two parties' sign shares.  Where a pair
-// of fields is an LDS item (kPacked) they sit at bits jW and jW + 1 of one word per group, other widths publish a byte
-// per element.  Either way an owner reads its pair's item at its pair's index and takes four bits at constant places.
+// of fields is an LDS item (kPacked) they sit at bits jW and jW + 1 of one word per group, where a group has 32 elements
+// (kDense, W <= 2) at bits 2j and 2j + 1 of one word, other widths publish a byte per element.  Either way an owner reads its
+// pair's item at its pair's index and takes four bits at constant places.
 // (Publishing two words per group, for every owner to find its group and shift by its field's place, took 14 more vector
 // instructions per pair in the widths that are not packed.)
 template <int W, int MODE>
@@ -277,7 +278,8 @@ struct Verdict {
     using T = TileTraits<W>;
     using S = Shape<W>;
     static constexpr bool kSigns = op_of(MODE) == kSign;
-    static constexpr int bytes(int groups) { return T::kPacked ? 8 * groups : (groups * T::L + 15) / 16 * 16; }
+    static constexpr bool kDense = T::L == 32;
+    static constexpr int bytes(int groups) { return T::kPacked || kDense ? 8 * groups : (groups * T::L + 15) / 16 * 16; }
 
     // bit 2j -> bit jW, for the packed widths
     static __device__ __forceinline__ uint32_t spread_half(uint32_t v)
@@ -306,6 +308,43 @@ struct Verdict {
     {
         return at < 32 ? __builtin_amdgcn_ubfe((uint32_t)v, at, 1) : __builtin_amdgcn_ubfe((uint32_t)(v >> 32), at - 32, 1);
     }
+    // bit jW -> bit 2j, for the dense widths
+    static __device__ __forceinline__ uint32_t to_even_half(uint32_t v)
+    {
+        v = (v | (v << 8)) & 0x00ff00ffu;
+        v = (v | (v << 4)) & 0x0f0f0f0fu;
+        v = (v | (v << 2)) & 0x33333333u;
+        return (v | (v << 1)) & 0x55555555u;
+    }
+    static __device__ __forceinline__ uint64_t to_even(uint64_t v)
+    {
+        if constexpr (W == 2) return v & 0x5555555555555555ull;
+        else return ((uint64_t)to_even_half((uint32_t)v >> 16) << 32) | to_even_half((uint32_t)v & 0xffffu);
+    }
+    // Bits at .. at + COUNT - 1 (COUNT <= 4) of v; `at` is known at compile time once the loop around is unrolled.
+    template <int COUNT>
+    static __device__ __forceinline__ uint32_t bits_at(uint64_t v, int at)
+    {
+        if (at % 32 + COUNT > 32) return (uint32_t)(v >> at) & ((1u << COUNT) - 1);
+        return __builtin_amdgcn_ubfe(at < 32 ? (uint32_t)v : (uint32_t)(v >> 32), at % 32, COUNT);
+    }
+    // Writes the bytes of FIELDS elements, byte(j) or two(j) (those of j and j + 1), four, two or one at a time as their
+    // number allows.  Three parties, w = 5, DReLU, 1000 tiles: 10.5 us, with a store per element 11.0; sign shares at w = 6 4.9
+    // and 5.1.
+    template <int FIELDS, class Byte, class Two>
+    static __device__ __forceinline__ void store_bytes(unsigned char *to, const Byte &byte, const Two &two)
+    {
+        if constexpr (FIELDS % 4 == 0) {
+#pragma unroll
+            for (int j = 0; j < FIELDS; j += 4) reinterpret_cast<uint32_t *>(to)[j / 4] = two(j) | (two(j + 2) << 16);
+        } else if constexpr (FIELDS % 2 == 0) {
+#pragma unroll
+            for (int j = 0; j < FIELDS; j += 2) reinterpret_cast<uint16_t *>(to)[j / 2] = (uint16_t)two(j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < FIELDS; ++j) to[j] = (unsigned char)byte(j);
+        }
+    }
     // The FIELDS fields of one word of the circuit's sum; `slot`: number of the word in the tile.  wb: the group's B2A
     // word with the bits of the first of these fields at 0 and 1.
     template <class Word, int FIELDS>
@@ -313,8 +352,8 @@ struct Verdict {
     {
         const Word s0 = sum.p0 >> (W - 1), s1 = sum.p1 >> (W - 1), sx = (sum.p0 ^ sum.p1) >> (W - 1);     // field j: bit jW
         const uint64_t rx = wb ^ (wb >> 1);                                                              // bit 2j: r
+        constexpr Word ones = (Word)S::ones();
         if constexpr (T::kPacked) {
-            constexpr Word ones = (Word)S::ones();
             Word v;
             if constexpr (kSigns) {
                 v = (s0 & ones) | ((s1 & ones) << 1);
@@ -323,24 +362,36 @@ struct Verdict {
                 v = bitop3<kTtAndXor>(ones, sx, r) | (r << 1);
             }
             reinterpret_cast<Word *>(lds)[slot] = v;
+        } else if constexpr (kDense) {
+            constexpr uint64_t kEven = 0x5555555555555555ull;
+            const uint64_t r = rx & kEven;
+            reinterpret_cast<uint64_t *>(lds)[slot] = kSigns ? to_even(s0) | (to_even(s1) << 1) : (to_even(sx) ^ r) | (r << 1);
+        } else if constexpr (kSigns) {
+            const uint64_t both = (uint64_t)(s0 & ones) | ((uint64_t)(s1 & ones) << 1);
+            auto byte = [&](int j) { return bits_at<2>(both, j * W); };
+            auto two = [&](int j) { return byte(j) | (byte(j + 1) << 8); };
+            store_bytes<FIELDS>(lds + slot * FIELDS, byte, two);
         } else {
+            // bits above the two of a byte are never looked at
             const uint64_t r = rx & 0x5555555555555555ull, rr = r | (r << 1);
-#pragma unroll
-            for (int j = 0; j < FIELDS; ++j) {
-                // bits above the two are never looked at
-                const uint32_t v = kSigns ? bit_at(s0, j * W) | (bit_at(s1, j * W) << 1) : bit_at(sx, j * W) ^ (uint32_t)(rr >> (2 * j));
-                lds[slot * FIELDS + j] = (unsigned char)v;
-            }
+            auto byte = [&](int j) { return bit_at(sx, j * W) ^ bits_at<2>(rr, 2 * j); };
+            auto two = [&](int j) {
+                const uint32_t r4 = bits_at<4>(rr, 2 * j);
+                return (bit_at(sx, j * W) | (bit_at(sx, (j + 1) * W) << 8)) ^ (r4 | (r4 << 6));
+            };
+            store_bytes<FIELDS>(lds + slot * FIELDS, byte, two);
         }
     }
     // What pair `pr` of the tile reads: its first element's bits at 0 and 1 of `lo`, its second's at kSecond of `hi`.
-    static constexpr int kSecond = T::kPacked ? W % 32 : 8;
+    static constexpr int kSecond = T::kPacked ? W % 32 : kDense ? 2 : 8;
     static __device__ __forceinline__ void read(const unsigned char *lds, int pr, uint32_t &lo, uint32_t &hi)
     {
         if constexpr (T::kPacked) {
             const typename T::Item it = reinterpret_cast<const typename T::Item *>(lds)[pr];
             lo = (uint32_t)it;
             hi = W == 32 ? (uint32_t)((uint64_t)it >> 32) : lo;
+        } else if constexpr (kDense) {
+            lo = hi = (uint32_t)lds[pr / 2] >> (4 * (pr & 1));
         } else {
             lo = hi = reinterpret_cast<const uint16_t *>(lds)[pr];
         }
@@ -513,10 +564,12 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
     wave_sync();
 
     // ---- owners: pick up the verdict of each element's group, finish, store ---------------------
-    // In a tensor's last tile every pair has addresses and bounds of its own: worked out again here they are not kept in
-    // registers across the circuit
+    // In a tensor's last tile every pair has addresses and bounds of its own.  Where keeping them across the circuit costs the
+    // kernel a wavefront per SIMD (ReLU at w = 4: 125 registers and four of them, otherwise 136 and three) they are worked out
+    // again; elsewhere that would only lengthen the one tile (0.2 us of a small launch).
+    constexpr bool kAgain = !FULL && (W == 4 ? op_of(MODE) != kSign : W <= 2 && op_of(MODE) == kRelu);
     int own = lane;
-    if constexpr (!FULL) asm("" : "+v"(own));
+    if constexpr (kAgain) asm("" : "+v"(own));
     const uint64_t zA0 = seedA + (6 * (tile0 + 2 * (uint64_t)own) + 1) * kGamma;   // A[6i] of the lane's first element
 #pragma unroll
     for (int c = 0; c < T::kPairs; ++c) {
@@ -713,7 +766,8 @@ __device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint6
 }
 
 // Wavefronts per SIMD that the registers of a kernel of whole tiles have to leave room for, where the compiler's own choice
-// is fewer (ReLU at w = 9, 10: 128 and 108 registers instead of 87 and 79; w = 13..16 on the shared-mask layout 73 instead of 72).
+// is fewer (ReLU at w = 9 and 10: 128 and 108 registers instead of 91 and 81; w = 13..16 on the shared-mask layout 73 instead
+// of 71).
 constexpr int whole_tile_waves(int w, int op)
 {
     return op != kRelu ? 1 : w == 9 || w == 10 ? 5 : w >= 13 && w <= 16 ? 7 : 1;

@@ -371,10 +371,10 @@ __device__ __forceinline__ void mp_publish(unsigned char *verdict, int slot, con
     for (int j = 0; j < FIELDS; ++j) ones |= 1ull << (P * j);
     const uint64_t rr = (rx & ones) | ((rx & ones) << 1);
     sx >>= W - 1;                                               // bit jW: XOR of the parties' sign shares
-#pragma unroll
-    for (int j = 0; j < FIELDS; ++j) {                          // bits above the two are never looked at
-        verdict[slot * FIELDS + j] = (unsigned char)(Verdict<5, kRelu>::bit_at(sx, j * W) ^ (uint32_t)(rr >> (P * j)));
-    }
+    using V = Verdict<5, kRelu>;
+    auto byte = [&](int j) { return V::bit_at(sx, j * W) ^ V::template bits_at<2>(rr, P * j); };
+    auto two = [&](int j) { return byte(j) | (byte(j + 1) << 8); };
+    V::template store_bytes<FIELDS>(verdict + slot * FIELDS, byte, two);
 }
 // Owners' part after the circuit.
 template <int P, int MODE, int PAIRS, int TILE, bool FULL>
@@ -382,7 +382,6 @@ __device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t 
                                                 const U64x2 (&xs)[P][PAIRS], const unsigned char *verdict)
 {
     constexpr uint64_t kArithWords = 4 * P - 2;
-    if constexpr (!FULL) asm("" : "+v"(lane));                 // as in tile_body_impl
     uint64_t zA0 = seedA + (kArithWords * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
 #pragma unroll
     for (int c = 0; c < PAIRS; ++c) {
