@@ -172,13 +172,14 @@ HB_API int hb_relu_mp(const int64_t *const *shares, int parties, size_t n, int k
 HB_API uint64_t hb_opened_bits_mp(int relu, int parties, int k, int m, size_t n);   /* 0 for invalid arguments */
 
 /*
- * Party-faithful ReLU: the same protocol and dealer material as hb_relu, but every opening is a message, put in
- * memory the way it would go over the link between two GPUs (Sec. 2.2: each AND, the B2A and the multiply
- * open masked values; Sec. 4.2: the w-bit fields are packed into 64-bit words before each communication).
- * Each party is evaluated by its own threads, owns its state and writes the words it sends to its "wire";
- * of the other party it learns those words alone, one communication round after the other (slice + gate 0,
- * R prefix rounds, B2A bits, multiply openings; one kernel launch).  out0 / out1 are bit-for-bit the shares
- * hb_relu returns.
+ * Party-faithful ReLU: the same protocol and dealer material as hb_relu, but every opening is a message between the
+ * parties (Sec. 2.2: each AND, the B2A and the multiply open masked values; Sec. 4.2: the w-bit fields are packed into
+ * 64-bit words before each communication).  Each party is evaluated by its own threads (one half of a wavefront each)
+ * and owns its state; of the other party it learns the messages alone, one communication round after the other (slice +
+ * gate 0, R prefix rounds, B2A bits, multiply openings; one kernel launch), handed over between the lanes of the
+ * wavefront.  The "wire" of a party is the transcript of what it sends, laid out in memory the way it would go over the
+ * link between two GPUs: the kernel writes every word of it and reads none back.  out0 / out1 are bit-for-bit the
+ * shares hb_relu returns.
  *
  * Wire of party p, 64-bit words: [2G: gate 0][4G per round, R rounds][ceil(n/64): B2A][2n: multiply], G =
  * ceil(n / L) groups of L = min(floor(64/w), 32) elements; in a group word field j sits at bit j*w; word
@@ -187,7 +188,8 @@ HB_API uint64_t hb_opened_bits_mp(int relu, int parties, int k, int m, size_t n)
  * DReLU_p - b_p.  Bits that belong to no element are zero.  hb_party_wire_words gives the word count
  * (8 bytes each; 64 x words = opened bits when w*L = 64 and 64 divides n).
  *
- * workspace: DEVICE memory, 256-byte aligned, hb_party_workspace_bytes(n, k, m) bytes, not overlapping any
+ * workspace: DEVICE memory, 256-byte aligned, hb_party_workspace_bytes(n, k, m) bytes (the wires, and a reserve of four
+ * words per group and one per element for each party that the kernel leaves alone), not overlapping any
  * other buffer of the call; after the call the wires are at byte offsets hb_party_wire_offset(n, k, m, p).
  * Inputs and outputs must not overlap each other here (in place is not supported).  wire_bytes (HOST, may
  * be NULL) receives the bytes each party wrote to its wire.

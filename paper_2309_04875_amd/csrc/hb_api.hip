@@ -445,7 +445,7 @@ int run_party(const int64_t *share0, const int64_t *share1, size_t n, int k, int
         for (const Range &b : bufs) {
             if (!disjoint(ws, b)) return HB_EINVAL;
         }
-        // each party re-reads its share after the other party's kernels have run: no in-place operation here
+        // no in-place operation here: a rule of the interface, which the kernel (it loads a tile before it stores it) would not need
         if (!disjoint(bufs[2], bufs[0]) || !disjoint(bufs[2], bufs[1]) || !disjoint(bufs[3], bufs[0]) ||
             !disjoint(bufs[3], bufs[1]))
             return HB_EINVAL;

@@ -166,7 +166,8 @@ open_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int binary, uint
 // consecutive addresses.  The circuit is laid out for dealer-word sharing: lane l evaluates group l
 // of the tile.  The two layouts meet in the wave's private piece of LDS: owners deposit the sliced
 // shares of their elements, group lanes collect the L fields of their group, and after the circuit
-// each group lane leaves its sign shares and B2A dealer word for the owners of its elements.
+// each group lane leaves two bits per element for the owners (Verdict): the opened bit and the dealer's bit, or the two
+// parties' sign shares.
 // All exchange stays inside one wavefront, whose LDS operations execute in program order, so no
 // workgroup barrier is needed; wave_sync() only keeps the compiler from moving LDS accesses across.
 // ------------------------------------------------------------------------------------------------
@@ -588,8 +589,8 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
 // tile, 16 groups each.  The four lanes of a group draw every fourth dealer word of the group each and hand them to one
 // another through LDS; where the fields of a word split into two halves (L even) lanes then evaluate the gate logic on
 // one half, 32 bits, which halves it.  Owners finish one element pair per lane (at w = 8) instead of four.  Same dealer
-// indices, same results; about a third of the tile's instructions per wavefront, 1.25 times the tile's in all, so this
-// form takes only what cannot fill the chip (tile_grid).  4 <= w <= 32.
+// indices, same results; 0.30 of the tile's instructions per wavefront (591 of 1974, ReLU at w = 8), 1.2 times the tile's in
+// all, so this form takes only what cannot fill the chip (tile_grid).  4 <= w <= 32.
 template <int W, int MODE>
 struct QuarterTraits {
     using S = Shape<W>;

@@ -446,9 +446,9 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
     mp_finish_pairs<P, MODE, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
 }
 
-// The same on a quarter of a tile: 1170 vector instructions per wavefront at w = 8 among three parties where the tile has
-// 4250.  4,195,307 elements (8195 tiles: three after the last full round) take 70.5 us instead of 75.2; at w = 4, 55.3
-// instead of 72.4.
+// The same on a quarter of a tile: about 1230 vector instructions per wavefront at w = 8 among three parties where the tile has
+// 4250.  4,195,307 elements (8195 tiles: three after the last full round) take 72.6 us, with whole tiles only 76.6; at w = 4
+// 53.5 and 63.8.
 template <int W, int P, int MODE, bool FULL>
 __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                 uint64_t quarter, int lane, unsigned char *lds)

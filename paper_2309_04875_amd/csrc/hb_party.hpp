@@ -2,10 +2,11 @@
 //
 // The fused kernels keep both parties in one thread and open values in registers.  Here each party is evaluated by its
 // own threads: lanes 0-31 of a wavefront are party 0 and lanes 32-63 party 1, lane l and lane l + 32 working on the same
-// group or elements.  A lane owns its party's share and circuit state, writes every word it sends to its party's "wire"
-// (the packed words of paper Sec. 2.2 and Sec. 4.2: every AND, the B2A and the multiply open masked values, w-bit
-// fields packed in 64-bit words, depth ceil(log2 w)), and learns of the other party only what two
-// exchange operations deliver: that party's messages, and what the dealer has to send.  The message schedule is
+// group or elements.  A lane owns its party's share and circuit state, and learns of the other party only what two
+// exchange operations inside the wavefront deliver: that party's messages, and what the dealer has to send.  Every word it
+// sends it also writes to its party's "wire" (the packed words of paper Sec. 2.2 and Sec. 4.2: every AND, the B2A and the
+// multiply open masked values, w-bit fields packed in 64-bit words, depth ceil(log2 w)): a transcript, which nothing
+// here reads back.  The message schedule is
 //     slice + gate 0  ->  R prefix rounds  ->  B2A bits  ->  multiply openings
 // The words on the wires are what a two-GPU run would put on the link, and the result shares are bit-identical to the
 // fused kernels'.
@@ -15,10 +16,11 @@
 // both parties' shares of the B2A bit) is drawn by one half of the wavefront and handed over, two words per generator
 // pass: the lower half draws one, the upper half the next.
 //
-// What bounds it: HBM, with vector-ALU issue close behind (the kernel without its wire stores takes 24 us of the 38 below).
+// What bounds it: HBM, with vector-ALU issue close behind (the kernel without its wire stores takes 24 us of the 37 below).
 // It moves the 92 bytes per element at w = 8 that it must (shares, results, both wires written once).  2,097,152
-// elements at w = 8: 37.6 us, 5.1 TB/s.  One launch per round with all state in memory took 118 us (271 bytes per element:
-// every round reloaded the state and both wires, and the masks of a gate were drawn twice); the parties in two wavefronts
+// elements at w = 8: 37.2 us, 5.2 TB/s.  One launch per round with all state in memory took 118 us (271 bytes per element:
+// every round reloaded the state and both wires, which is how a party got the other's messages, and the masks of a gate were
+// drawn twice); the parties in two wavefronts
 // that met at workgroup barriers and read each other's wires 64 us (waiting for messages to come back from L2).
 //
 // Wire of party p (64-bit words): [2G gate 0][4G per round x R][ceil(n/64) B2A][2n multiply]; field j of a

@@ -285,7 +285,7 @@ __device__ __forceinline__ int32_t minus_bit(uint32_t v, int at) { return (int32
 // two.  -v = ~v + 1 turns the conditional negations into xors with m; with c = ~r^A_0 (the complement is free: the
 // generator's last xor becomes an xnor) and q = r^A_1 - 1 = c + r,
 //   DReLU_0 = (c ^ m) + 2 (1 - z),   DReLU_1 = ~(q ^ m) + z.
-// With the verdict published as (z, r) pairs the w = 8 ReLU tile is 1986 vector instructions per wavefront where selects
+// With the verdict published as (z, r) pairs the w = 8 ReLU tile was 1986 vector instructions per wavefront where selects
 // and subtracts on separately shifted sign shares and dealer bits took 2060: 285,212,672 elements in 2.175 ms against
 // 2.227, the simulator's 4,194,304 in 34.7 us against 35.6.
 struct B2aShares {
