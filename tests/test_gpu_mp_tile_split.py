@@ -1,6 +1,5 @@
-"""Three and four parties where tiles are shared out by quarters: sizes around the rule's lines (256 or 512 tiles, and
-1024 more),
-one element short of a tile or three into one.  Bit for bit against the oracle."""
+"""Three and four parties where tiles are shared out by quarters: sizes around the rule's lines (512 to 1024 tiles by width, 256 or
+512 after a full round of 1024), one element short of a tile or three into one.  Bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch

@@ -1,7 +1,7 @@
 """Launches whose last tiles are shared out by quarters: sizes around the rule's lines, bit for bit against the oracle.
 
-A tile has 64 groups.  Up to 256 to 1024 tiles, by width, every tile goes to a workgroup by quarters, above that what is left
-after the last 1024 whole ones if it is at most 256 or 512; the tensors here end one element short of a tile or five elements into one (whose
+A tile has 64 groups.  Up to 256 to 1280 tiles, by width and operation, every tile goes to a workgroup by quarters, above that what is
+left after the last 1024 whole ones if it is at most 256 or 512; the tensors here end one element short of a tile or five elements into one (whose
 other quarters are then empty), and the batched call has the line between whole and shared-out tiles inside a tensor.
 """
 import numpy as np
