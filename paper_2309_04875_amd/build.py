@@ -67,8 +67,10 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         for lo, hi in PARTY_WIDTH_RANGES:
             units.append((os.path.join(CSRC, "hb_party_part.hip"), os.path.join(work, "party_w%d.o" % lo),
                           [("HB_PART_LO", lo), ("HB_PART_HI", hi)]))
+        # the multi-party units take longest: started first, so that none of them is left to compile alone at the end
+        longest_first = sorted([probes] + units, key=lambda unit: "hb_mp_part" not in unit[0])
         with ThreadPoolExecutor(max_workers=jobs) as pool:
-            for out in pool.map(_compile, [probes] + units):
+            for out in pool.map(_compile, longest_first):
                 if verbose and out.strip():
                     print(out)
         for objects, library in (([u[1] for u in units], LIBRARY), ([probes[1]], PROBES_LIBRARY)):
