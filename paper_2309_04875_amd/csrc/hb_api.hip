@@ -167,14 +167,13 @@ struct LaunchItem {
     hb::BatchLauncher tiles = nullptr;   // wave-tile launch of args.t[0 .. args.count)
     hb::GroupLauncher single = nullptr;  // per-tensor launch of args.t[0]
     hb::BatchArgs args = {};
-    bool vec16 = false;
 };
 
 hipError_t enqueue(const LaunchItem &it, hipStream_t stream)
 {
     if (it.tiles != nullptr) return it.tiles(it.args, stream);
     const hb::BatchTensor &d = it.args.t[0];
-    return it.single(d.x0, d.x1, d.n, d.k, d.seedB, d.seedA, d.o0, d.o1, it.vec16, stream);
+    return it.single(d.x0, d.x1, d.n, d.k, d.seedB, d.seedA, d.o0, d.o1, stream);
 }
 
 void fill_tensor(hb::BatchTensor &d, const hb_tensor &t)
@@ -208,8 +207,6 @@ int plan_launches(int mode, const hb_tensor *tensors, size_t count, std::vector<
             if (it.single == nullptr) return fail_hip(hipErrorInvalidDeviceFunction, "no kernel was built for this slice width");
             fill_tensor(it.args.t[0], first);
             it.args.count = 1;
-            const void *ptrs[4] = {first.share0, first.share1, first.out0, first.out1};
-            it.vec16 = all_aligned16(ptrs, 4);
             items.push_back(it);
             continue;
         }
@@ -268,11 +265,10 @@ int run(int mode, const int64_t *share0, const int64_t *share1, size_t n, int k,
     }
     if (n > 0) {
         const uint64_t seedB = hb::stream_word(seed, 0), seedA = hb::stream_word(seed, 1);
-        const void *ptrs[4] = {share0, share1, out0, out1};
         const hb::GroupLauncher f = hb::launcher_table().f[mode][w - 1];
         if (f == nullptr) return fail_hip(hipErrorInvalidDeviceFunction, "no kernel was built for this slice width");
         const hipError_t e = f((const uint64_t *)share0, (const uint64_t *)share1, (uint64_t)n, k, seedB, seedA,
-                               (uint64_t *)out0, (uint64_t *)out1, all_aligned16(ptrs, 4), (hipStream_t)stream);
+                               (uint64_t *)out0, (uint64_t *)out1, (hipStream_t)stream);
         if (e != hipSuccess) return fail_hip(e, "kernel launch");
     }
     if (opened_bits) *opened_bits = bits;
@@ -542,6 +538,26 @@ uint64_t small_tile_limit(uint64_t usual)
     return v != nullptr ? given : usual;
 }
 
+// Which launches take the form with RUNS (mix_words): those whose SIMDs hold a second wavefront for most of the time, or, where
+// tiles are shared out, more than one round of quarters.  Two parties, ReLU, us, without / with:
+//      all by quarters             whole tiles             1024 whole tiles and the rest by quarters         longer
+//   w   300 tiles   1000 tiles     1000 tiles              1088           1400                               1700           2^25 elements
+//   4   5.3 / 5.1    8.7 / 7.9                                            11.1 / 11.4                         15.7 / 14.6    213 / 204
+//   6   5.6 / 5.3                   7.9 /  8.2              8.5 / 8.6     10.3 /  9.6                         12.0 / 11.1    248 / 232
+//   8   4.2 / 4.0    6.6 / 6.2                              7.0 / 7.3      7.8 /  7.8                         10.1 /  9.5    258 / 240
+//  12   4.8 / 4.8                   6.6 /  6.9              7.0 / 7.3      8.4 /  8.0                          9.9 /  9.3    360 / 333
+//  16   4.5 / 4.4                   5.0 /  5.3              6.4 / 5.9      7.5 /  6.7                          7.9 /  7.5    375 / 352
+//  32                               4.8 /  5.0              6.6 / 5.8      7.1 /  6.5                          7.2 /  6.6   1280 / 1174
+// (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1; at w = 4 1088 to 1280
+// tiles, which go by quarters, take as long either way.)
+bool tile_runs(uint64_t tiles, uint64_t split, int w)
+{
+    if (split == tiles) return tiles > kQuarterRound && tiles <= kSimds;
+    if (tiles <= kSimds) return false;
+    if (w <= 3 || w == 7 || w >= 13) return true;
+    return tiles - kSimds > (w == 4 ? 2 * kQuarterRound : 320);
+}
+
 TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
 {
     const uint64_t left = tiles % kSimds;
@@ -550,9 +566,11 @@ TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
     if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= shared_remainder(tiles, w, parties, op) ? left : 0;
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
-    if (blocks > 0x7fffffffull) return TileGrid{0, 0, false};
-    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0};
+    if (blocks > 0x7fffffffull) return TileGrid{0, 0, false, false};
+    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0, tile_runs(tiles, split, w)};
 }
+
+bool group_runs(uint64_t blocks) { return blocks > kSimds / kWavesPerBlock; }
 
 bool force_group_kernel()
 {

@@ -41,7 +41,7 @@ __device__ __forceinline__ void store_stream2(uint64_t *p, U64x2 v)
 __device__ __forceinline__ uint64_t load_stream(const uint64_t *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void store_stream(uint64_t *p, uint64_t v) { __builtin_nontemporal_store(v, p); }
 
-template <int W, int MODE, bool VEC>
+template <int W, int MODE, bool RUNS>
 __global__ void __launch_bounds__(kBlock)
 group_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, uint64_t groups, int k, uint64_t seedB,
              uint64_t seedA, uint64_t *o0, uint64_t *o1)
@@ -60,7 +60,7 @@ group_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, uint64_t groups
     uint64_t xa[kHold ? L : 1], xb[kHold ? L : 1];
     uint64_t u0 = 0, u1 = 0;
 
-    if (VEC && full && (L % 2 == 0)) {
+    if (full && (L % 2 == 0)) {
 #pragma unroll
         for (int j = 0; j < L / 2; ++j) {
             const U64x2 a = load_stream2(x0 + i0 + 2 * j), b = load_stream2(x1 + i0 + 2 * j);
@@ -93,12 +93,11 @@ group_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, uint64_t groups
     }
 
     const uint64_t zg = seedB + (g * (uint64_t)S::words_per_group(shared_of(MODE)) + 1) * kGamma;
-    const Pair sum = a2b_sum<W, shared_of(MODE)>(u0, u1, zg);
     uint64_t wb = 0;
-    if (op_of(MODE) != kSign) wb = mix64(zg + (uint64_t)S::b2a_word(shared_of(MODE)) * kGamma);
+    const Pair sum = a2b_sum<W, shared_of(MODE), op_of(MODE) != kSign, RUNS>(u0, u1, zg, wb);
 
     const uint64_t zA0 = seedA + (6 * i0 + 1) * kGamma;
-    if (VEC && full && (L % 2 == 0)) {
+    if (full && (L % 2 == 0)) {
 #pragma unroll
         for (int j = 0; j < L / 2; ++j) {
             Pair xe{0, 0}, xo{0, 0};
@@ -113,8 +112,8 @@ group_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, uint64_t groups
                     xo = Pair{a.b, b.b};
                 }
             }
-            const Pair re = finish_element<W, MODE>(sum, wb, 2 * j, xe, zA0 + (uint64_t)(6 * (2 * j)) * kGamma);
-            const Pair ro = finish_element<W, MODE>(sum, wb, 2 * j + 1, xo, zA0 + (uint64_t)(6 * (2 * j + 1)) * kGamma);
+            const Pair re = finish_element<W, MODE, RUNS>(sum, wb, 2 * j, xe, zA0 + (uint64_t)(6 * (2 * j)) * kGamma);
+            const Pair ro = finish_element<W, MODE, RUNS>(sum, wb, 2 * j + 1, xo, zA0 + (uint64_t)(6 * (2 * j + 1)) * kGamma);
             store_stream2(o0 + i0 + 2 * j, U64x2{re.p0, ro.p0});
             store_stream2(o1 + i0 + 2 * j, U64x2{re.p1, ro.p1});
         }
@@ -124,7 +123,7 @@ group_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, uint64_t groups
             if (j < cnt) {
                 Pair x{0, 0};
                 if (op_of(MODE) == kRelu) x = kHold ? Pair{xa[j], xb[j]} : Pair{load_stream(x0 + i0 + j), load_stream(x1 + i0 + j)};
-                const Pair r = finish_element<W, MODE>(sum, wb, j, x, zA0 + (uint64_t)(6 * j) * kGamma);
+                const Pair r = finish_element<W, MODE, RUNS>(sum, wb, j, x, zA0 + (uint64_t)(6 * j) * kGamma);
                 store_stream(o0 + i0 + j, r.p0);
                 store_stream(o1 + i0 + j, r.p1);
             }
@@ -190,6 +189,12 @@ constexpr int tile_lanes_per_word(int w) { return 64 / w > 32 ? 32 : 64 / w; }
 constexpr int tile_groups(int w) { return tile_lanes_per_word(w) > 16 ? 32 : 64; }
 constexpr int tile_elements(int w) { return tile_groups(w) * tile_lanes_per_word(w); }
 constexpr bool quarters_supported(int w) { return w >= 4 && w <= 32; }      // a tile of 64 groups splits into quarters of 16
+
+// The forms that a tile kernel is built in: with or without the code for quarters of a tile, and with or without RUNS
+// (mix_words).
+constexpr int kWholeTiles = 0, kQuartersForm = 1, kRunsForm = 2;
+constexpr bool has_quarters(int form) { return (form & kQuartersForm) != 0; }
+constexpr bool has_runs(int form) { return (form & kRunsForm) != 0; }
 
 template <int W>
 struct TileTraits {
@@ -414,7 +419,7 @@ struct Verdict {
 };
 
 // The owner's part for one pair: what `io` stores for elements e, e + 1 of the tile.
-template <int W, int MODE>
+template <int W, int MODE, bool RUNS>
 __device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr, U64x2 xa, U64x2 xb, uint64_t zA, Pair (&r)[2])
 {
     using V = Verdict<W, MODE>;
@@ -423,8 +428,13 @@ __device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr
     } else {
         B2aBits t[2];
         V::pick(verdict, pr, t);
-        r[0] = op_of(MODE) == kDrelu ? b2a_drelu(t[0], zA) : b2a_mul(t[0], Pair{xa.a, xb.a}, zA);
-        r[1] = op_of(MODE) == kDrelu ? b2a_drelu(t[1], zA + 6 * kGamma) : b2a_mul(t[1], Pair{xa.b, xb.b}, zA + 6 * kGamma);
+        const Pair x[2] = {Pair{xa.a, xb.a}, Pair{xa.b, xb.b}};
+        if constexpr (RUNS && op_of(MODE) == kRelu) {       // twelve words in step would take 16 registers more
+            finish_elements<MODE, RUNS, 1>({t[0]}, {x[0]}, zA, &r[0]);
+            finish_elements<MODE, RUNS, 1>({t[1]}, {x[1]}, zA + 6 * kGamma, &r[1]);
+        } else {
+            finish_elements<MODE, RUNS, 2>(t, x, zA, r);
+        }
     }
 }
 
@@ -433,6 +443,7 @@ __device__ __forceinline__ void finish_pair(const unsigned char *verdict, int pr
 // Element i = tile0 + e: tile0 (the tile's first element) is uniform over the wavefront, e is the lane's
 // 32-bit offset inside the tile, so an address is a scalar base plus a 32-bit vector offset.
 struct ShareIO {
+    static constexpr bool kDraws = false;      // shares are what is loaded
     const uint64_t *x0, *x1;
     uint64_t *o0, *o1;
     template <bool FULL>
@@ -488,29 +499,39 @@ struct alignas(8) F32x2 {
 // point and shares additively with share0[i] = output i of the SplitMix64 stream started at seedS; the store opens
 // the two result shares and decodes.  Nothing but 4 bytes per element travels each way.
 struct FloatIO {
+    static constexpr bool kDraws = true;       // load_pair leaves encoded numbers in b; share() then draws the shares
     const float *x;
     float *y;
     uint64_t seedS;
     template <bool FULL>
-    __device__ __forceinline__ void load_pair(uint64_t tile0, unsigned e, uint64_t n, U64x2 &a, U64x2 &b) const
+    __device__ __forceinline__ void load_pair(uint64_t tile0, unsigned e, uint64_t n, U64x2 &, U64x2 &b) const
     {
         const uint64_t i = tile0 + e;
         const float *t = x + tile0;
-        float f0 = 0.0f, f1 = 0.0f;
         if (FULL || i + 1 < n) {
             const F32x2 v = *reinterpret_cast<const F32x2 *>(t + e);
-            f0 = v.a;
-            f1 = v.b;
+            b = U64x2{encode_fixed16(v.a), encode_fixed16(v.b)};
         } else if (i < n) {
-            f0 = t[e];
-        } else {
-            return;
+            b.a = encode_fixed16(t[e]);
         }
-        const uint64_t z = seedS + (i + 1) * kGamma;
-        a.a = mix64(z);
-        a.b = mix64(z + kGamma);
-        b.a = encode_fixed16(f0) - a.a;
-        b.b = encode_fixed16(f1) - a.b;
+    }
+    // Of COUNT pairs, those at elements e, e + 2 kWave, ..  Pairs beyond the tensor get shares that nothing reads.
+    template <bool RUNS, int COUNT>
+    __device__ __forceinline__ void share(uint64_t tile0, unsigned e, U64x2 *a, U64x2 *b) const
+    {
+        const uint64_t z = seedS + (tile0 + e + 1) * kGamma;
+        uint64_t v[2 * COUNT];
+        priority<RUNS, kElsewhere>();
+#pragma unroll
+        for (int i = 0; i < 2 * COUNT; ++i) v[i] = z + (uint64_t)(i / 2 * 2 * kWave + i % 2) * kGamma;
+        mix_words<RUNS>(v);
+        if constexpr (RUNS) settle(v);
+        priority<RUNS, kElsewhere>();
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            a[c] = U64x2{v[2 * c], v[2 * c + 1]};
+            b[c] = U64x2{b[c].a - a[c].a, b[c].b - a[c].b};
+        }
     }
     template <bool FULL>
     __device__ __forceinline__ void store_pair(uint64_t tile0, unsigned e, uint64_t n, Pair r0, Pair r1) const
@@ -524,9 +545,21 @@ struct FloatIO {
     }
 };
 
+// FloatIO::share of all pairs with RUNS, up to four of them in step.  (Without RUNS, and in a quarter, pairs are shared as they
+// arrive: in step they took 3 to 5 % longer in launches of 100 to 1100 tiles.)
+template <int PAIRS, class IO>
+__device__ __forceinline__ void draw_shares(const IO &io, uint64_t tile0, int lane, U64x2 (&xa)[PAIRS], U64x2 (&xb)[PAIRS])
+{
+    constexpr int kAtOnce = PAIRS < 4 ? PAIRS : 4, kRest = PAIRS % kAtOnce;
+#pragma unroll
+    for (int c = 0; c + kAtOnce <= PAIRS; c += kAtOnce) io.template share<true, kAtOnce>(tile0, (unsigned)(2 * (c * kWave + lane)), xa + c, xb + c);
+    if constexpr (kRest > 0)
+        io.template share<true, kRest>(tile0, (unsigned)(2 * ((PAIRS - kRest) * kWave + lane)), xa + PAIRS - kRest, xb + PAIRS - kRest);
+}
+
 // Work of one wavefront on wave-tile `tile` of one tensor.  lds: this wave's LDS.  FULL: the whole tile lies inside the
 // tensor, so no access needs a bounds check (every tile but a tensor's last).
-template <int W, int MODE, bool FULL, class IO>
+template <int W, int MODE, bool RUNS, bool FULL, class IO>
 __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                uint64_t tile, int lane, unsigned char *lds)
 {
@@ -537,6 +570,7 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
     const uint64_t tile0 = tile * T::kTile;
     unsigned char *verdict = lds + Sl::kBytes;
 
+    priority<RUNS, kElsewhere>();
     // ---- owners: load, slice, deposit -------------------------------------------------------
     U64x2 xa[T::kPairs], xb[T::kPairs];
 #pragma unroll
@@ -547,7 +581,16 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         xb[c] = U64x2{0, 0};
         if (e < T::kTile) {
             io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
-            Sl::deposit(lds, pr, xa[c], xb[c], k);
+            if constexpr (IO::kDraws && !RUNS) io.template share<false, 1>(tile0, (unsigned)e, &xa[c], &xb[c]);
+            if constexpr (!IO::kDraws || !RUNS) Sl::deposit(lds, pr, xa[c], xb[c], k);
+        }
+    }
+    if constexpr (IO::kDraws && RUNS) {
+        draw_shares(io, tile0, lane, xa, xb);
+#pragma unroll
+        for (int c = 0; c < T::kPairs; ++c) {
+            const int pr = c * kWave + lane;
+            if (2 * pr < T::kTile) Sl::deposit(lds, pr, xa[c], xb[c], k);
         }
     }
     wave_sync();
@@ -557,9 +600,8 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         const Pair u = Sl::collect(lds, lane);
         const uint64_t g = tile * T::kGroups + lane;
         const uint64_t zg = seedB + (g * (uint64_t)S::words_per_group(shared_of(MODE)) + 1) * kGamma;
-        const Pair sum = a2b_sum<W, shared_of(MODE)>(u.p0, u.p1, zg);
         uint64_t wb = 0;
-        if (op_of(MODE) != kSign) wb = mix64(zg + (uint64_t)S::b2a_word(shared_of(MODE)) * kGamma);
+        const Pair sum = a2b_sum<W, shared_of(MODE), op_of(MODE) != kSign, RUNS>(u.p0, u.p1, zg, wb);
         Verdict<W, MODE>::template publish<uint64_t, T::L>(verdict, lane, sum, wb);
     }
     wave_sync();
@@ -577,7 +619,7 @@ __device__ __forceinline__ void tile_body_impl(const IO &io, uint64_t n, int k, 
         const int pr = c * kWave + own, e = 2 * pr;
         if (e < T::kTile) {
             Pair r[2];
-            finish_pair<W, MODE>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
+            finish_pair<W, MODE, RUNS>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
@@ -619,7 +661,7 @@ struct QuarterTraits {
     static constexpr int kLdsBytes = kVerdictAt + Verdict<W, MODE>::bytes(kGroups);
 };
 
-template <int W, int MODE, bool FULL, class IO>
+template <int W, int MODE, bool RUNS, bool FULL, class IO>
 __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                   uint64_t quarter, int lane, unsigned char *lds)
 {
@@ -630,6 +672,7 @@ __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int 
     const uint64_t tile0 = quarter * Q::kTile;
     unsigned char *verdict = lds + Q::kVerdictAt;
 
+    priority<RUNS, kElsewhere>();
     // ---- owners: load ------------------------------------------------------------------------------------
     U64x2 xa[Q::kPairs], xb[Q::kPairs];
 #pragma unroll
@@ -637,7 +680,10 @@ __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int 
         const int e = 2 * (c * kWave + lane);
         xa[c] = U64x2{0, 0};
         xb[c] = U64x2{0, 0};
-        if (e < Q::kTile) io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
+        if (e < Q::kTile) {
+            io.template load_pair<FULL>(tile0, (unsigned)e, n, xa[c], xb[c]);
+            if constexpr (IO::kDraws) io.template share<false, 1>(tile0, (unsigned)e, &xa[c], &xb[c]);
+        }
     }
 
     // ---- every lane, while the loads are under way: its share of the group's dealer words ------------------
@@ -645,6 +691,7 @@ __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int 
     const uint64_t g = quarter * Q::kGroups + grp;
     const uint64_t zs = seedB + (g * (uint64_t)S::words_per_group(Q::kShared) + 1 + (uint64_t)sub) * kGamma;
     uint32_t *row = reinterpret_cast<uint32_t *>(lds + Q::kWordsAt) + grp * Q::kRow;
+    // (one by one: in step they cost 2 to 5 % of a launch of 300 to 700 tiles)
 #pragma unroll
     for (int t = 0; t < Q::kWordsPerLane; ++t) {
         const int j = t * Q::kSplit + sub;                      // word j of the group; the last one drawn is the B2A word
@@ -696,7 +743,7 @@ __device__ __forceinline__ void quarter_body_impl(const IO &io, uint64_t n, int 
         const int pr = c * kWave + lane, e = 2 * pr;
         if (e < Q::kTile) {
             Pair r[2];
-            finish_pair<W, MODE>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
+            finish_pair<W, MODE, RUNS>(verdict, pr, xa[c], xb[c], zA0 + (uint64_t)(12 * c * kWave) * kGamma, r);
             io.template store_pair<FULL>(tile0, (unsigned)e, n, r[0], r[1]);
         }
     }
@@ -743,27 +790,28 @@ __device__ __forceinline__ TileWork tile_work(uint32_t whole_blocks, int wv)
 }
 
 // t.tile must be uniform over the wavefront; the tile lies inside the tensor at least in part.
-template <int W, int MODE, bool QUARTERS, class IO>
+template <int W, int MODE, int FORM, class IO>
 __device__ __forceinline__ void tile_body(const IO &io, uint64_t n, int k, uint64_t seedB, uint64_t seedA, TileWork t, int lane, int wv,
                                           unsigned char *tile_lds)
 {
-    if constexpr (QUARTERS) {
+    constexpr bool RUNS = has_runs(FORM);
+    if constexpr (has_quarters(FORM)) {
         if (t.quarter >= 0) {
             using Q = QuarterTraits<W, MODE>;
             const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
             unsigned char *lds = tile_lds + wv * Q::kLdsBytes;
             if ((quarter + 1) * Q::kTile <= n)
-                quarter_body_impl<W, MODE, true>(io, n, k, seedB, seedA, quarter, lane, lds);
+                quarter_body_impl<W, MODE, RUNS, true>(io, n, k, seedB, seedA, quarter, lane, lds);
             else if (quarter * Q::kTile < n)
-                quarter_body_impl<W, MODE, false>(io, n, k, seedB, seedA, quarter, lane, lds);
+                quarter_body_impl<W, MODE, RUNS, false>(io, n, k, seedB, seedA, quarter, lane, lds);
             return;
         }
     }
     unsigned char *lds = tile_lds + wv * whole_lds_bytes<W, MODE>();
     if ((t.tile + 1) * TileTraits<W>::kTile <= n)
-        tile_body_impl<W, MODE, true>(io, n, k, seedB, seedA, t.tile, lane, lds);
+        tile_body_impl<W, MODE, RUNS, true>(io, n, k, seedB, seedA, t.tile, lane, lds);
     else
-        tile_body_impl<W, MODE, false>(io, n, k, seedB, seedA, t.tile, lane, lds);
+        tile_body_impl<W, MODE, RUNS, false>(io, n, k, seedB, seedA, t.tile, lane, lds);
 }
 
 // Wavefronts per SIMD that the registers of a kernel of whole tiles have to leave room for, where the compiler's own choice
@@ -774,16 +822,16 @@ constexpr int whole_tile_waves(int w, int op)
     return op != kRelu ? 1 : w == 9 || w == 10 ? 5 : w >= 13 && w <= 16 ? 7 : 1;
 }
 
-template <int W, int MODE, bool QUARTERS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUARTERS ? 1 : whole_tile_waves(W, op_of(MODE)))))
+template <int W, int MODE, int FORM>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(has_quarters(FORM) ? 1 : whole_tile_waves(W, op_of(MODE)))))
 tile_kernel(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t *o0,
             uint64_t *o1, uint32_t whole_blocks)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
+    const TileWork t = tile_work<has_quarters(FORM)>(whole_blocks, wv);
     if (t.tile * TileTraits<W>::kTile >= n) return;        // whole wavefront beyond the tensor (uniform per wave)
-    tile_body<W, MODE, QUARTERS>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, t, lane, wv, tile_lds);
+    tile_body<W, MODE, FORM>(ShareIO{x0, x1, o0, o1}, n, k, seedB, seedA, t, lane, wv, tile_lds);
 }
 
 // Several tensors of one slice width in a single launch.  The descriptors travel in the kernel
@@ -809,13 +857,13 @@ struct BatchArgs {
     int count;
 };
 
-template <int W, int MODE, bool QUARTERS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUARTERS ? 1 : whole_tile_waves(W, op_of(MODE)))))
+template <int W, int MODE, int FORM>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(has_quarters(FORM) ? 1 : whole_tile_waves(W, op_of(MODE)))))
 tile_batch_kernel(const BatchArgs args)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    TileWork t = tile_work<QUARTERS>(args.whole_blocks, wv);                          // tile number over the whole batch
+    TileWork t = tile_work<has_quarters(FORM)>(args.whole_blocks, wv);                          // tile number over the whole batch
     const uint32_t gt = (uint32_t)t.tile;                                      // below 2^31 + 4
     if (gt >= args.tiles) return;
     int ti = 0;
@@ -823,12 +871,12 @@ tile_batch_kernel(const BatchArgs args)
     for (int i = 0; i < kBatchMax; ++i) ti += (int)((args.tile_end[i] - 1 - gt) >> 31);   // scalar: the borrow, not a comparison
     const BatchTensor &d = args.t[__builtin_amdgcn_readfirstlane(ti)];
     t.tile = gt - d.first_tile;
-    tile_body<W, MODE, QUARTERS>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, t, lane, wv, tile_lds);
+    tile_body<W, MODE, FORM>(ShareIO{d.x0, d.x1, d.o0, d.o1}, d.n, d.k, d.seedB, d.seedA, t, lane, wv, tile_lds);
 }
 
 // The simulator kernel: ReLU on plaintext floats through the whole protocol, 8 bytes of traffic per element.
 // Slice widths up to 32 run the wave-tile body; wider slices (one element per word) take one thread per element.
-template <int W>
+template <int W, bool RUNS>
 __global__ void __launch_bounds__(kBlock)
 wide_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t seedS, float *y)
 {
@@ -839,21 +887,21 @@ wide_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seed
     const uint64_t x0 = mix64(seedS + (i + 1) * kGamma);
     const uint64_t x1 = encode_fixed16(x[i]) - x0;
     const uint64_t zg = seedB + (i * (uint64_t)S::words_per_group(false) + 1) * kGamma;
-    const Pair sum = a2b_sum<W, false>((x0 >> k) & S::kField, (x1 >> k) & S::kField, zg);
-    const uint64_t wb = mix64(zg + (uint64_t)S::b2a_word(false) * kGamma);
-    const Pair r = finish_element<W, kRelu>(sum, wb, 0, Pair{x0, x1}, seedA + (6 * i + 1) * kGamma);
+    uint64_t wb = 0;
+    const Pair sum = a2b_sum<W, false, true, RUNS>((x0 >> k) & S::kField, (x1 >> k) & S::kField, zg, wb);
+    const Pair r = finish_element<W, kRelu, RUNS>(sum, wb, 0, Pair{x0, x1}, seedA + (6 * i + 1) * kGamma);
     y[i] = decode_fixed16(r.p0 + r.p1);
 }
 
-template <int W, bool QUARTERS>
+template <int W, int FORM>
 __global__ void __launch_bounds__(kBlock)
 tile_sim_kernel(const float *x, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint64_t seedS, float *y, uint32_t whole_blocks)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
+    const TileWork t = tile_work<has_quarters(FORM)>(whole_blocks, wv);
     if (t.tile * TileTraits<W>::kTile >= n) return;
-    tile_body<W, kRelu, QUARTERS>(FloatIO{x, y, seedS}, n, k, seedB, seedA, t, lane, wv, tile_lds);
+    tile_body<W, kRelu, FORM>(FloatIO{x, y, seedS}, n, k, seedB, seedA, t, lane, wv, tile_lds);
 }
 
 }  // namespace hb

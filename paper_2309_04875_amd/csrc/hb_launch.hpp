@@ -12,7 +12,7 @@
 namespace hb {
 
 using GroupLauncher = hipError_t (*)(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB,
-                                     uint64_t seedA, uint64_t *o0, uint64_t *o1, bool vec16, hipStream_t stream);
+                                     uint64_t seedA, uint64_t *o0, uint64_t *o1, hipStream_t stream);
 
 // Launches the tensors described by `args` (all of one slice width, tile-kernel eligible) in one grid.
 using BatchLauncher = hipError_t (*)(const BatchArgs &args, hipStream_t stream);
@@ -44,19 +44,41 @@ LauncherTable &launcher_table();
 struct TileGrid {
     uint32_t whole_blocks, blocks;       // blocks 0: more than a grid holds
     bool quarters;                       // blocks > whole_blocks
+    bool runs;                           // which form of the dealer-word generator (mix_words)
 };
 // op: kDrelu, kRelu, kSign or kSimulator.
 constexpr int kSimulator = 3;
 TileGrid tile_grid(uint64_t tiles, int w, int parties, int op);
 
-// go(std::true_type) where tiles of the grid are shared out, go(std::false_type) otherwise.
-template <int W, class Go>
-hipError_t with_quarters(const TileGrid &grid, const Go &go)
+// Whether tile kernels have the form with RUNS (mix_words), which long launches then take (tile_runs).  Not where memory bounds long
+// launches, which wavefronts of unequal priority disturb: 2^25 elements, us, without / with: DReLU at w = 6 177 / 183, w = 8 175 /
+// 181, w = 9 216 / 207, w = 10 217 / 200; sign shares at w = 6 172 / 180, w = 12 211 / 204 (8 M elements 57 / 58), w = 16 241 / 221.
+constexpr bool runs_supported(int w, int op)
 {
+    if (op == kSign) return w >= 13;
+    if (op == kDrelu) return w >= 9;
+    return true;
+}
+
+// The form of the generator (mix_words) for kernels of one thread per group in `blocks` workgroups: RUNS from where a SIMD has a
+// second wavefront.  ReLU at w = 64, us, without / with: 256 blocks 4.5 / 4.8, 272 7.0 / 6.3, 4096 44 / 38, 131072 1320 / 1144.
+bool group_runs(uint64_t blocks);
+
+// go(std::integral_constant<int, form>) with the form of kernel that the grid asks for.  RUNS: whether there is one with RUNS.
+template <int W, bool RUNS, class Go>
+hipError_t with_form(const TileGrid &grid, const Go &go)
+{
+    auto runs_or_not = [&](auto quarters) {
+        constexpr int kQuarters = decltype(quarters)::value;
+        if constexpr (RUNS) {
+            if (grid.runs) return go(std::integral_constant<int, kQuarters | kRunsForm>{});
+        }
+        return go(std::integral_constant<int, kQuarters>{});
+    };
     if constexpr (quarters_supported(W)) {
-        if (grid.quarters) return go(std::true_type{});
+        if (grid.quarters) return runs_or_not(std::integral_constant<int, kQuartersForm>{});
     }
-    return go(std::false_type{});
+    return runs_or_not(std::integral_constant<int, kWholeTiles>{});
 }
 
 // Debug knob: HB_KERNEL=group in the environment (read once) sends every width to the thread-per-group kernel.

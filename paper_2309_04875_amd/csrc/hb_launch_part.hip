@@ -11,7 +11,7 @@ namespace {
 
 template <int W, int MODE>
 hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
-                        uint64_t *o0, uint64_t *o1, bool vec16, hipStream_t stream)
+                        uint64_t *o0, uint64_t *o1, hipStream_t stream)
 {
     constexpr uint64_t L = hb::Shape<W>::L;
     const uint64_t groups = (n + L - 1) / L;
@@ -21,23 +21,24 @@ hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int 
         if (!hb::force_group_kernel()) {
             const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W, 2, hb::op_of(MODE));
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-            auto go = [&](auto quarters) {
-                constexpr bool kQuarters = decltype(quarters)::value;
-                hipLaunchKernelGGL((hb::tile_kernel<W, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(kQuarters)),
+            auto go = [&](auto form) {
+                constexpr int kForm = decltype(form)::value;
+                hipLaunchKernelGGL((hb::tile_kernel<W, MODE, kForm>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(hb::has_quarters(kForm))),
                                    stream, x0, x1, n, k, seedB, seedA, o0, o1, grid.whole_blocks);
                 return hipGetLastError();
             };
-            return hb::with_quarters<W>(grid, go);
+            return hb::with_form<W, hb::runs_supported(W, hb::op_of(MODE))>(grid, go);
         }
     }
-    if (vec16) {
-        hipLaunchKernelGGL((hb::group_kernel<W, MODE, true>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x0,
+    auto go = [&](auto runs) {
+        hipLaunchKernelGGL((hb::group_kernel<W, MODE, decltype(runs)::value>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x0,
                            x1, n, groups, k, seedB, seedA, o0, o1);
-    } else {
-        hipLaunchKernelGGL((hb::group_kernel<W, MODE, false>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x0,
-                           x1, n, groups, k, seedB, seedA, o0, o1);
+        return hipGetLastError();
+    };
+    if constexpr (!hb::TileTraits<W>::kSupported) {
+        if (hb::group_runs(blocks)) return go(std::true_type{});
     }
-    return hipGetLastError();
+    return go(std::false_type{});
 }
 
 template <int W, int MODE>
@@ -46,13 +47,13 @@ hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
     if constexpr (hb::TileTraits<W>::kSupported) {
         const hb::TileGrid grid = hb::tile_grid(args.tiles, W, 2, hb::op_of(MODE));
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-        auto go = [&](auto quarters) {
-            constexpr bool kQuarters = decltype(quarters)::value;
-            hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(kQuarters)),
+        auto go = [&](auto form) {
+            constexpr int kForm = decltype(form)::value;
+            hipLaunchKernelGGL((hb::tile_batch_kernel<W, MODE, kForm>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, MODE>(hb::has_quarters(kForm))),
                                stream, args);
             return hipGetLastError();
         };
-        return hb::with_quarters<W>(grid, go);
+        return hb::with_form<W, hb::runs_supported(W, hb::op_of(MODE))>(grid, go);
     } else {
         return hipErrorInvalidDeviceFunction;
     }
@@ -67,19 +68,22 @@ hipError_t launch_sim(const float *x, uint64_t n, int k, uint64_t seedB, uint64_
     } else if constexpr (hb::TileTraits<W>::kSupported) {
         const hb::TileGrid grid = hb::tile_grid((n + hb::TileTraits<W>::kTile - 1) / hb::TileTraits<W>::kTile, W, 2, hb::kSimulator);
         if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-        auto go = [&](auto quarters) {
-            constexpr bool kQuarters = decltype(quarters)::value;
-            hipLaunchKernelGGL((hb::tile_sim_kernel<W, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, hb::kRelu>(kQuarters)),
+        auto go = [&](auto form) {
+            constexpr int kForm = decltype(form)::value;
+            hipLaunchKernelGGL((hb::tile_sim_kernel<W, kForm>), dim3(grid.blocks), dim3(hb::kBlock), (hb::tile_lds_bytes<W, hb::kRelu>(hb::has_quarters(kForm))),
                                stream, x, n, k, seedB, seedA, seedS, y, grid.whole_blocks);
             return hipGetLastError();
         };
-        return hb::with_quarters<W>(grid, go);
+        return hb::with_form<W, true>(grid, go);
     } else {
         const uint64_t blocks = (n + hb::kBlock - 1) / hb::kBlock;
         if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((hb::wide_sim_kernel<W>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x, n, k, seedB,
-                           seedA, seedS, y);
-        return hipGetLastError();
+        auto go = [&](auto runs) {
+            hipLaunchKernelGGL((hb::wide_sim_kernel<W, decltype(runs)::value>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, x, n, k,
+                               seedB, seedA, seedS, y);
+            return hipGetLastError();
+        };
+        return hb::group_runs(blocks) ? go(std::true_type{}) : go(std::false_type{});
     }
 }
 

@@ -23,7 +23,7 @@ hipError_t launch_mp(const hb::MpPointers &ptr, uint64_t n, int k, uint64_t seed
                                    stream, ptr, n, k, seedB, seedA, grid.whole_blocks);
                 return hipGetLastError();
             };
-            return hb::with_quarters<W>(grid, go);
+            return hb::with_form<W, false>(grid, [&](auto form) { return go(std::bool_constant<hb::has_quarters(decltype(form)::value)>{}); });
         }
     }
     constexpr uint64_t L = hb::MpShape<W, P>::L;

@@ -75,6 +75,43 @@ struct WordPair {    // one value held as (party 0 share, party 1 share)
 
 using Pair = WordPair<uint64_t>;
 
+// ---- dealer words, several at a time ---------------------------------------------------------------------------------
+// What bounds every kernel here is vector-ALU issue, and three quarters of it are SplitMix64.  A third of its
+// instructions, the 32-bit xors, take two cycles of a SIMD instead of four, but only while two of its wavefronts are at such
+// instructions at the same time; left to themselves the wavefronts are spread evenly over the generator and pay four for nearly
+// every instruction (3.9 on average).  With RUNS the words that a gate or an element needs are drawn in step, the xors of all of
+// them in one run, and a wavefront gives way (lowest wave priority) while it is in such a run: the others then use the SIMD for
+// their multiplies until they too stand before xors, which are issued two at a time.  Words alone, four wavefronts per
+// SIMD, five or ten words in step: 72 cycles a word without priorities whatever the order of the instructions, 61 and 58
+// with them, 72 with the priorities the other way round.  One wavefront per SIMD has nobody to share with, and the changes of
+// priority cost it 1 to 5 %, so kernels exist with RUNS and without.
+constexpr int kXorRuns = 0, kElsewhere = 1;        // wave priorities
+
+template <bool RUNS, int PRIORITY>
+__device__ __forceinline__ void priority()
+{
+    if constexpr (RUNS) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(PRIORITY);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The values are computed before, and their uses come after, whatever else has this order (priority() does).  No instruction.
+template <class Word>
+__device__ __forceinline__ void settle(Word &v) { asm volatile("" : "+v"(v)); }
+template <class Word, int N>
+__device__ __forceinline__ void settle(Word (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) settle(v[i]);
+}
+__device__ __forceinline__ void settle(Pair &v)
+{
+    settle(v.p0);
+    settle(v.p1);
+}
+
 // Returns z, which the compiler may not compute before `after` is known.  Dealer words depend only on the group
 // or element number, so the scheduler would otherwise generate those of every gate ahead of the circuit and
 // hold them all in registers; tying a gate's generator state to the previous gate's result keeps their live
@@ -83,6 +120,71 @@ __device__ __forceinline__ uint64_t not_before(uint64_t z, uint64_t after)
 {
     asm("" : "+v"(z) : "v"(after));
     return z;
+}
+
+// kGamma in scalar registers, as a value that the compiler does not fold into others: consecutive states are one addition
+// each, from one register pair, instead of an addition of a constant that two scalar moves make each time.
+__device__ __forceinline__ uint64_t gamma()
+{
+    uint64_t g = kGamma;
+    asm("" : "+s"(g));
+    return g;
+}
+
+template <int N>
+__device__ __forceinline__ void xor_shift(uint64_t (&z)[N], int by)
+{
+    uint64_t t[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) t[i] = z[i] >> by;
+    settle(t);
+    priority<true, kXorRuns>();
+#pragma unroll
+    for (int i = 0; i < N; ++i) z[i] ^= t[i];
+}
+// mix64 of N states.  With RUNS it starts at priority kElsewhere (the states have been computed there) and ends at
+// kXorRuns, where the xors that use the words go on; whoever goes on with something else raises it again.
+template <bool RUNS, int N>
+__device__ __forceinline__ void mix_words(uint64_t (&z)[N])
+{
+    if constexpr (RUNS) {
+        xor_shift(z, 30);
+        settle(z);
+        priority<true, kElsewhere>();
+#pragma unroll
+        for (int i = 0; i < N; ++i) z[i] *= 0xBF58476D1CE4E5B9ull;
+        xor_shift(z, 27);
+        settle(z);
+        priority<true, kElsewhere>();
+#pragma unroll
+        for (int i = 0; i < N; ++i) z[i] *= 0x94D049BB133111EBull;
+        xor_shift(z, 31);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) z[i] = mix64(z[i]);
+    }
+}
+
+// The next N words of the generator whose next word has state z, which moves on, then (EXTRA = 1) one that lies `skip` words
+// further.
+template <bool RUNS, int N, int EXTRA = 0>
+__device__ __forceinline__ void draw_words(uint64_t &z, uint64_t (&v)[N + EXTRA], int skip = 0)
+{
+    if constexpr (RUNS) {
+        settle(z);
+        priority<true, kElsewhere>();
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            v[i] = z;
+            z += gamma();
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = z + (uint64_t)i * kGamma;
+        z += (uint64_t)N * kGamma;
+    }
+    if constexpr (EXTRA != 0) v[N] = z + (uint64_t)skip * kGamma;
+    mix_words<RUNS>(v);
 }
 
 // ---- three-input bitwise operations (v_bitop3_b32, one instruction per 32-bit half) ----------------------------
@@ -200,35 +302,62 @@ __device__ __forceinline__ void beaver_and_shared(uint64_t zr, uint64_t Ux, uint
 }
 
 // A2B + sign for one group.  u0/u1: the L sliced shares of party 0 / party 1 packed as fields.
-// zg: generator state of the group's first dealer word.  Returns XOR shares of the sum word
+// z: generator state of the group's first dealer word.  Returns XOR shares of the sum word
 // S ^ (G << 1); the sign of field j is bit jW + W - 1.  The last round's P-update gate is not
 // evaluated: nothing reads its result (its dealer words are simply never drawn).  SHARED selects the
-// dealer layout in which the two gates of a round share the mask of P.
-template <int W, bool SHARED>
-__device__ __forceinline__ Pair a2b_sum(uint64_t u0, uint64_t u1, uint64_t zg)
+// dealer layout in which the two gates of a round share the mask of P (words a_0 a_1 | b_0 b_1 c_0 of the G-update |
+// b_0 b_1 c_0 of the P-update).  B2A: the group's B2A word is drawn with the last gate's and left in `b2a`.
+// A gate's words are used up before the next are drawn.  (Ten words in step, those of a round, take 16 registers more, which
+// costs a wavefront per SIMD at most widths: w = 8 and 10 as fast, w = 16 6 % slower.)
+template <int W, bool SHARED, bool B2A, bool RUNS>
+__device__ __forceinline__ Pair a2b_sum(uint64_t u0, uint64_t u1, uint64_t z, uint64_t &b2a)
 {
     using S = Shape<W>;
+    using GW = GateWords<uint64_t>;
+    auto gate = [&] {
+        uint64_t v[5];
+        draw_words<RUNS, 5>(z, v);
+        return GW{v[0], v[1], v[2], v[3], v[4]};
+    };
+    // the five words of the circuit's last gate, and the B2A word, which lies `skip` words behind them
+    auto last_gate = [&](int skip) {
+        uint64_t v[B2A ? 6 : 5];
+        draw_words<RUNS, 5, B2A ? 1 : 0>(z, v, skip);
+        if constexpr (B2A) b2a = v[5];
+        return GW{v[0], v[1], v[2], v[3], v[4]};
+    };
     // X = (u0, 0), Y = (0, u1): each party XOR-shares its own slice trivially
     const Pair X{u0, 0}, Y{0, u1};
     Pair P{X.p0 ^ Y.p0, X.p1 ^ Y.p1};
     const Pair Sum = P;
-    Pair G = beaver_and(zg, X.p0 ^ X.p1, Y.p0 ^ Y.p1, ~0ull, Pair{0, 0});
+    Pair G = beaver_and_words<uint64_t>(S::R == 0 ? last_gate(0) : gate(), X.p0 ^ X.p1, Y.p0 ^ Y.p1, ~0ull, Pair{0, 0});
 #pragma unroll
     for (int r = 0; r < S::R; ++r) {
         const int s = 1 << r;
+        const bool last = r + 1 == S::R;
         const uint64_t keep = S::keep(s);
         // shifting is linear: the XOR of the parties' shifted shares is the shifted XOR of their shares
         const uint64_t Px = P.p0 ^ P.p1;
         const uint64_t Gsx = (G.p0 ^ G.p1) << s, Psx = Px << s;
-        const uint64_t zr = not_before(zg + (uint64_t)S::round_word(SHARED, r) * kGamma, G.p0);
-        if (SHARED) {
-            Pair Pn = P;
-            if (r + 1 < S::R) beaver_and_shared<true>(zr, Px, Gsx, Psx, keep, G, G, Pn);
-            else beaver_and_shared<false>(zr, Px, Gsx, Psx, keep, G, G, Pn);
-            P = Pn;
+        if constexpr (RUNS) {
+            settle(G);
+            if (!(last && W >= 34)) settle(P);             // (a last round on one field reads the upper half only)
         } else {
-            G = beaver_and(zr, Px, Gsx, keep, G);
-            if (r + 1 < S::R) P = beaver_and(zr + 5 * kGamma, Px, Psx, keep, Pair{0, 0});
+            z = not_before(z, G.p0);
+        }
+        if (last) {
+            G = beaver_and_words<uint64_t>(last_gate(SHARED ? 3 : 5), Px, Gsx, keep, G);
+        } else if constexpr (SHARED) {
+            const GW g = gate();
+            G = beaver_and_words<uint64_t>(g, Px, Gsx, keep, G);
+            if constexpr (RUNS) settle(G);
+            uint64_t v[3];
+            draw_words<RUNS, 3>(z, v);
+            P = beaver_and_words<uint64_t>(GW{g.a0, g.a1, v[0], v[1], v[2]}, Px, Psx, keep, Pair{0, 0});
+        } else {
+            G = beaver_and_words<uint64_t>(gate(), Px, Gsx, keep, G);
+            if constexpr (RUNS) settle(G);
+            P = beaver_and_words<uint64_t>(gate(), Px, Psx, keep, Pair{0, 0});
         }
     }
     const uint64_t keep1 = S::keep(1);
@@ -291,16 +420,15 @@ __device__ __forceinline__ int32_t minus_bit(uint32_t v, int at) { return (int32
 struct B2aShares {
     uint64_t f0, f1;    // DReLU_0 less 2 (1 - z), DReLU_1 less z
 };
-__device__ __forceinline__ B2aShares b2a_shares(B2aBits t, uint64_t zA)
+// c: the complement of the element's word r^A_0, held (the compiler would make a subtraction of ~r^A_0 + r); f0: c ^ m.
+__device__ __forceinline__ uint64_t b2a_first(B2aBits t, uint64_t c) { return held(c ^ (uint64_t)(int64_t)t.m); }
+__device__ __forceinline__ B2aShares b2a_shares(B2aBits t, uint64_t c, uint64_t f0)
 {
-    const uint64_t c = ~mix64(zA);
     const uint64_t q = c + t.r;
-    const uint64_t m = (uint64_t)(int64_t)t.m;
-    return B2aShares{held(c ^ m), held(~(q ^ m))};
+    return B2aShares{f0, held(~(q ^ (uint64_t)(int64_t)t.m))};
 }
-__device__ __forceinline__ Pair b2a_drelu(B2aBits t, uint64_t zA)
+__device__ __forceinline__ Pair b2a_drelu(B2aBits t, B2aShares f)
 {
-    const B2aShares f = b2a_shares(t, zA);
     return Pair{f.f0 + (uint32_t)(2 * (t.m + 1)), f.f1 + (uint32_t)-t.m};
 }
 
@@ -342,21 +470,16 @@ __device__ __forceinline__ uint64_t sum_of_products(uint64_t acc, uint64_t x, ui
     return add_to_high(held(low), cross);
 }
 
-// Beaver multiply x * DReLU on Z_2^64 for one element; the triple is A[6i+1 .. 6i+5].
-__device__ __forceinline__ Pair b2a_mul(B2aBits t, Pair x, uint64_t zA)
+// Beaver multiply x * DReLU on Z_2^64 for one element; v: its triple A[6i+1 .. 6i+5].
+__device__ __forceinline__ Pair b2a_mul(B2aBits t, B2aShares f, Pair x, const uint64_t *v)
 {
-    const B2aShares f = b2a_shares(t, zA);
-    const uint64_t a0 = mix64(zA + 1 * kGamma);
-    const uint64_t a1 = mix64(zA + 2 * kGamma);
-    const uint64_t b0 = mix64(zA + 3 * kGamma);
-    const uint64_t b1 = mix64(zA + 4 * kGamma);
-    const uint64_t c0 = mix64(zA + 5 * kGamma);
+    const uint64_t a0 = v[0], a1 = v[1], b0 = v[2], b1 = v[3], c0 = v[4];
     const uint64_t a = a0 + a1, b = b0 + b1;                      // the dealer's triple (a, b, a * b)
     const uint64_t eps = (x.p0 + x.p1) - a;                       // opened: (x_0 - a_0) + (x_1 - a_1)
-    // opened: (DReLU_0 - b_0) + (DReLU_1 - b_1), taken as ((DReLU_0 + DReLU_1) - b_1) - b_0: party 0 needs b_0 + del
-    // (one value, held and then used by both: a second name for it would cost a copy)
-    const uint64_t b0_del = held(held((f.f0 + f.f1) + (uint32_t)(t.m + 2)) - b1);
-    const uint64_t del = b0_del - b0;
+    // opened: (DReLU_0 - b_0) + (DReLU_1 - b_1).  Party 0 needs b_0 + del besides: an addition, where that first and del out
+    // of it are two subtractions (two instructions each, the second waiting for the first's carry).
+    const uint64_t del = held(held((f.f0 + f.f1) + (uint32_t)(t.m + 2)) - b);
+    const uint64_t b0_del = del + b0;
     Pair out;
     // party 0: c_0 + eps * b_0 + del * a_0 + eps * del
     out.p0 = sum_of_products(c0, eps, b0_del, del, a0);
@@ -371,16 +494,55 @@ enum Mode { kDrelu = 0, kRelu = 1, kSign = 2, kDreluShared = 3, kReluShared = 4,
 constexpr int op_of(int mode) { return mode >= kDreluShared ? mode - kDreluShared : mode; }
 constexpr bool shared_of(int mode) { return mode >= kDreluShared; }
 
+// Everything after the circuit for COUNT consecutive elements: B2A, multiply.  z: generator state of the first element's
+// word A[6i].
+template <int MODE, bool RUNS, int COUNT>
+__device__ __forceinline__ void finish_elements(const B2aBits (&t)[COUNT], const Pair (&x)[COUNT], uint64_t z, Pair *out)
+{
+    constexpr bool kMul = op_of(MODE) == kRelu;
+    constexpr int kWords = kMul ? 6 : 1;                          // of an element; DReLU reads the first only
+    uint64_t v[kWords * COUNT];
+    if constexpr (kMul) {
+        draw_words<RUNS, kWords * COUNT>(z, v);
+    } else {
+        priority<RUNS, kElsewhere>();
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) v[i] = z + (uint64_t)(6 * i) * kGamma;
+        mix_words<RUNS>(v);
+    }
+    uint64_t c[COUNT], f0[COUNT];
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+        c[i] = held(~v[kWords * i]);
+        f0[i] = b2a_first(t[i], c[i]);
+    }
+    if constexpr (RUNS) {
+        if constexpr (kMul) settle(v);
+        settle(c);
+        settle(f0);
+        priority<true, kElsewhere>();
+    }
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+        const B2aShares f = b2a_shares(t[i], c[i], f0[i]);
+        if constexpr (kMul) out[i] = b2a_mul(t[i], f, x[i], v + kWords * i + 1);
+        else out[i] = b2a_drelu(t[i], f);
+        if constexpr (RUNS) settle(out[i]);
+    }
+}
+
 // Everything after the circuit for element j of a group: pick the element's sign and dealer bits
-// out of the group words, B2A, multiply.
-template <int W, int MODE>
-__device__ __forceinline__ Pair finish_element(Pair sum, uint64_t wb, int j, Pair x, uint64_t zA)
+// out of the group words, B2A, multiply.  z as in finish_elements.
+template <int W, int MODE, bool RUNS>
+__device__ __forceinline__ Pair finish_element(Pair sum, uint64_t wb, int j, Pair x, uint64_t z)
 {
     const int sb = j * W + W - 1;
     if (op_of(MODE) == kSign) return Pair{(sum.p0 >> sb) & 1, (sum.p1 >> sb) & 1};
     const uint32_t r = (uint32_t)((wb ^ (wb >> 1)) >> (2 * j)) & 1u;
     const B2aBits t{minus_bit((uint32_t)((sum.p0 ^ sum.p1) >> sb) ^ r, 0), r};
-    return op_of(MODE) == kDrelu ? b2a_drelu(t, zA) : b2a_mul(t, x, zA);
+    Pair out;
+    finish_elements<MODE, RUNS, 1>({t}, {x}, z, &out);
+    return out;
 }
 
 }  // namespace hb
