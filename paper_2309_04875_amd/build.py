@@ -31,7 +31,7 @@ MODES = (0, 1, 2, 3, 4)                                 # DReLU, ReLU, sign shar
 WIDTH_RANGES = ((1, 16), (17, 32), (33, 48), (49, 64))
 MP_PARTIES = (3, 4)                                     # multi-party kernels (two parties: the kernels above)
 PARTY_WIDTH_RANGES = ((1, 4), (5, 8), (9, 16), (17, 32), (33, 48), (49, 64))   # party-faithful kernels
-MP_WIDTH_RANGES = ((1, 8), (9, 16), (17, 32), (33, 48), (49, 64))
+MP_WIDTH_RANGES = tuple((w, w + 3) for w in range(1, 33, 4)) + ((33, 48), (49, 64))
 
 
 def _hipcc():
@@ -67,8 +67,9 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         for lo, hi in PARTY_WIDTH_RANGES:
             units.append((os.path.join(CSRC, "hb_party_part.hip"), os.path.join(work, "party_w%d.o" % lo),
                           [("HB_PART_LO", lo), ("HB_PART_HI", hi)]))
-        # the multi-party units take longest: started first, so that none of them is left to compile alone at the end
-        longest_first = sorted([probes] + units, key=lambda unit: "hb_mp_part" not in unit[0])
+        # the multi-party units take longest, those of four parties twice as long as those of three: started first, so that none
+        # of them is left to compile alone at the end
+        longest_first = sorted([probes] + units, key=lambda unit: ("hb_mp_part" not in unit[0], ("HB_PART_PARTIES", 4) not in unit[2]))
         with ThreadPoolExecutor(max_workers=jobs) as pool:
             for out in pool.map(_compile, longest_first):
                 if verbose and out.strip():

@@ -550,10 +550,13 @@ uint64_t small_tile_limit(uint64_t usual)
 //  32                               4.8 /  5.0              6.6 / 5.8      7.1 /  6.5                          7.2 /  6.6   1280 / 1174
 // (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1; at w = 4 1088 to 1280
 // tiles, which go by quarters, take as long either way.)
-bool tile_runs(uint64_t tiles, uint64_t split, int w)
+// Among more parties a kernel's second round counts from its first tile on (76 tiles beyond 1024: w = 8 12.4 / 12.4 and 20.0 / 19.3,
+// w = 32 13.3 / 11.3 and 24.1 / 20.5; 676 tiles 5 to 15 % of any width).
+bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties)
 {
     if (split == tiles) return tiles > kQuarterRound && tiles <= kSimds;
     if (tiles <= kSimds) return false;
+    if (parties > 2) return w != 4 || tiles - kSimds > kQuarterRound;
     if (w <= 3 || w == 7 || w >= 13) return true;
     return tiles - kSimds > (w == 4 ? 2 * kQuarterRound : 320);
 }
@@ -567,7 +570,7 @@ TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
     if (blocks > 0x7fffffffull) return TileGrid{0, 0, false, false};
-    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0, tile_runs(tiles, split, w)};
+    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0, tile_runs(tiles, split, w, parties)};
 }
 
 bool group_runs(uint64_t blocks) { return blocks > kSimds / kWavesPerBlock; }

@@ -27,7 +27,7 @@ hipError_t launch_group(const uint64_t *x0, const uint64_t *x1, uint64_t n, int 
                                    stream, x0, x1, n, k, seedB, seedA, o0, o1, grid.whole_blocks);
                 return hipGetLastError();
             };
-            return hb::with_form<W, hb::runs_supported(W, hb::op_of(MODE))>(grid, go);
+            return hb::with_form<W, hb::runs_supported(W, 2, hb::op_of(MODE))>(grid, go);
         }
     }
     auto go = [&](auto runs) {
@@ -53,7 +53,7 @@ hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
                                stream, args);
             return hipGetLastError();
         };
-        return hb::with_form<W, hb::runs_supported(W, hb::op_of(MODE))>(grid, go);
+        return hb::with_form<W, hb::runs_supported(W, 2, hb::op_of(MODE))>(grid, go);
     } else {
         return hipErrorInvalidDeviceFunction;
     }

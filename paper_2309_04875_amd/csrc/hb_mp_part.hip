@@ -17,22 +17,28 @@ hipError_t launch_mp(const hb::MpPointers &ptr, uint64_t n, int k, uint64_t seed
         if (!hb::force_group_kernel()) {
             const hb::TileGrid grid = hb::tile_grid((n + hb::MpTileTraits<W, P>::kTile - 1) / hb::MpTileTraits<W, P>::kTile, W, P, MODE);
             if (grid.blocks == 0) return hipErrorInvalidConfiguration;
-            auto go = [&](auto quarters) {
-                constexpr bool kQuarters = decltype(quarters)::value;
-                hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE, kQuarters>), dim3(grid.blocks), dim3(hb::kBlock), (hb::mp_lds_bytes<W, P>(kQuarters)),
+            auto go = [&](auto form) {
+                constexpr int kForm = decltype(form)::value;
+                hipLaunchKernelGGL((hb::mp_tile_kernel<W, P, MODE, kForm>), dim3(grid.blocks), dim3(hb::kBlock), (hb::mp_lds_bytes<W, P>(hb::has_quarters(kForm))),
                                    stream, ptr, n, k, seedB, seedA, grid.whole_blocks);
                 return hipGetLastError();
             };
-            return hb::with_form<W, false>(grid, [&](auto form) { return go(std::bool_constant<hb::has_quarters(decltype(form)::value)>{}); });
+            return hb::with_form<W, hb::runs_supported(W, P, MODE)>(grid, go);
         }
     }
     constexpr uint64_t L = hb::MpShape<W, P>::L;
     const uint64_t groups = (n + L - 1) / L;
     const uint64_t blocks = (groups + hb::kBlock - 1) / hb::kBlock;
     if (blocks == 0 || blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((hb::mp_group_kernel<W, P, MODE>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, ptr, n,
-                       groups, k, seedB, seedA);
-    return hipGetLastError();
+    auto go = [&](auto runs) {
+        hipLaunchKernelGGL((hb::mp_group_kernel<W, P, MODE, decltype(runs)::value>), dim3((unsigned)blocks), dim3(hb::kBlock), 0, stream, ptr,
+                           n, groups, k, seedB, seedA);
+        return hipGetLastError();
+    };
+    if constexpr (!hb::MpTileTraits<W, P>::kSupported) {
+        if (hb::group_runs(blocks)) return go(std::true_type{});
+    }
+    return go(std::false_type{});
 }
 
 template <int W>

@@ -78,9 +78,9 @@ __device__ __forceinline__ Shares<P, Word> mp_and(const Words &word, Word Ux, Wo
 }
 
 // X + Y mod 2^W in every field, on XOR shares.  gate(q, after) gives the accessor of gate q's dealer words, which are not
-// drawn before `after` is known.  The last round's P-update gate is not evaluated (nothing reads it; its words are never
+// drawn before `after` is known (with RUNS not before all shares of the gates before).  The last round's P-update gate is not evaluated (nothing reads it; its words are never
 // drawn).  Word = uint32_t: the lower or the upper half of the fields, at bits jW of every word.
-template <int W, int P, class Word, class Gates>
+template <int W, int P, class Word, bool RUNS, class Gates>
 __device__ __forceinline__ Shares<P, Word> mp_add_gates(const Gates &gate, const Shares<P, Word> &X, const Shares<P, Word> &Y)
 {
     using S = Shape<W>;
@@ -105,8 +105,11 @@ __device__ __forceinline__ Shares<P, Word> mp_add_gates(const Gates &gate, const
             Gx ^= G.v[q];
             Px ^= Pw.v[q];
         }
-        // one gate's dealer words at a time (not_before): 3P - 1 live words instead of the whole adder's
+        // one gate's dealer words at a time: 3P - 1 live words instead of the whole adder's
+        if constexpr (RUNS) settle(G.v);
+        if (RUNS && !(r + 1 == S::R && W >= 34)) settle(Pw.v);      // (a last round on one field reads the upper half only)
         G = mp_and<P, Word>(gate(1 + 2 * r, Gx), Px, (Word)(Gx << s), keep, G);
+        if constexpr (RUNS) settle(G.v);
         if (r + 1 < S::R) Pw = mp_and<P, Word>(gate(2 + 2 * r, G.v[0]), Px, (Word)(Px << s), keep, zero);
     }
     const Word keep1 = (Word)S::keep(1);
@@ -116,16 +119,44 @@ __device__ __forceinline__ Shares<P, Word> mp_add_gates(const Gates &gate, const
     return out;
 }
 
+// N consecutive words; with RUNS and more than ten of them (four parties) in two batches: in step they would take 12 registers
+// more, a wavefront per SIMD.
+template <bool RUNS, int N>
+__device__ __forceinline__ void draw_in_two(uint64_t z, uint64_t (&v)[N])
+{
+    constexpr int kFirst = RUNS && N > 10 ? (N + 1) / 2 : N, kRest = N - kFirst;
+    uint64_t f[kFirst];
+    draw_words<RUNS, kFirst>(z, f);
+#pragma unroll
+    for (int i = 0; i < kFirst; ++i) v[i] = f[i];
+    if constexpr (kRest > 0) {
+        settle(f);
+        uint64_t s[kRest];
+        draw_words<RUNS, kRest>(z, s);
+#pragma unroll
+        for (int i = 0; i < kFirst; ++i) v[i] = f[i];
+#pragma unroll
+        for (int i = 0; i < kRest; ++i) v[kFirst + i] = s[i];
+    }
+}
+
 // The adder drawing its words inline; za = generator state of its first dealer word.
-template <int W, int P>
+template <int W, int P, bool RUNS>
 __device__ __forceinline__ Shares<P> mp_add(uint64_t za, const Shares<P> &X, const Shares<P> &Y)
 {
-    auto gate = [za](int q, uint64_t after) {
-        const uint64_t zq = za + (uint64_t)(q * MpShape<W, P>::kGateWords) * kGamma;
-        const uint64_t z = q == 0 ? zq : not_before(zq, after);
-        return [z](int i) { return mix64(z + (uint64_t)i * kGamma); };
+    constexpr int kWords = MpShape<W, P>::kGateWords;
+    struct Drawn {
+        uint64_t v[kWords];
+        __device__ __forceinline__ uint64_t operator()(int i) const { return v[i]; }
     };
-    return mp_add_gates<W, P, uint64_t>(gate, X, Y);
+    auto gate = [za](int q, uint64_t after) {
+        const uint64_t zq = za + (uint64_t)(q * kWords) * kGamma;
+        uint64_t z = RUNS || q == 0 ? zq : not_before(zq, after);
+        Drawn d;
+        draw_in_two<RUNS, kWords>(z, d.v);
+        return d;
+    };
+    return mp_add_gates<W, P, uint64_t, RUNS>(gate, X, Y);
 }
 
 // XOR shares of (u_0 + ... + u_{P-1}) mod 2^W for one group; add(i, X, Y) is adder i of the tree.
@@ -148,11 +179,11 @@ __device__ __forceinline__ Shares<P, Word> mp_tree(const Word (&u)[P], const Add
 }
 
 // The same drawing its words inline; zg = generator state of the group's first word.
-template <int W, int P>
+template <int W, int P, bool RUNS>
 __device__ __forceinline__ Shares<P> mp_a2b_sum(const uint64_t (&u)[P], uint64_t zg)
 {
     auto add = [zg](int i, const Shares<P> &X, const Shares<P> &Y) {
-        return mp_add<W, P>(zg + (uint64_t)(i * MpShape<W, P>::kAdderWords) * kGamma, X, Y);
+        return mp_add<W, P, RUNS>(zg + (uint64_t)(i * MpShape<W, P>::kAdderWords) * kGamma, X, Y);
     };
     return mp_tree<P, uint64_t>(u, add);
 }
@@ -160,19 +191,28 @@ __device__ __forceinline__ Shares<P> mp_a2b_sum(const uint64_t (&u)[P], uint64_t
 // Everything after the circuit for one element.  t: the opened bit and the dealer's bit.  zA = generator state of the element's first arithmetic word.  MODE: kDrelu or kRelu.
 // As for two parties (b2a_shares): with c_q = ~r^A_q and q = r^A_{P-1} - 1 = c_0 + ... + c_{P-2} + (P - 2) + r,
 //   DReLU_0 = (c_0 ^ m) + 2 (1 - z),  DReLU_q = (c_q ^ m) + (1 - z),  DReLU_{P-1} = ~(q ^ m) + z.
-template <int P, int MODE>
+template <int P, int MODE, bool RUNS>
 __device__ __forceinline__ Shares<P> mp_finish(B2aBits t, const Shares<P> &x, uint64_t zA)
 {
     const uint32_t r = t.r;                                   // known to the dealer only
     const int32_t m = t.m;                                    // -z, the opened bit
     const uint64_t mm = (uint64_t)(int64_t)m;
+    uint64_t w[MODE == kRelu ? 4 * P - 2 : P - 1];
+    draw_in_two<RUNS>(zA, w);
     uint64_t f[P], csum = 0;
 #pragma unroll
     for (int q = 0; q < P - 1; ++q) {
-        const uint64_t c = ~mix64(zA + (uint64_t)q * kGamma);
-        csum += c;
-        f[q] = held(c ^ mm);
+        w[q] = held(~w[q]);
+        f[q] = held(w[q] ^ mm);
     }
+    if constexpr (RUNS) {
+        settle(w);
+#pragma unroll
+        for (int q = 0; q < P - 1; ++q) settle(f[q]);
+        priority<true, kElsewhere>();
+    }
+#pragma unroll
+    for (int q = 0; q < P - 1; ++q) csum += w[q];
     f[P - 1] = held(~((csum + (r + (uint32_t)(P - 2))) ^ mm));
     if (MODE == kDrelu) {
         const uint32_t n = (uint32_t)(m + 1), z = (uint32_t)-m;
@@ -186,36 +226,36 @@ __device__ __forceinline__ Shares<P> mp_finish(B2aBits t, const Shares<P> &x, ui
 #pragma unroll
     for (int q = 1; q < P; ++q) drelu += f[q];
     drelu = held(drelu + (uint32_t)(P + (P - 1) * m));
-    const uint64_t zM = zA + (uint64_t)(P - 1) * kGamma;
+    const uint64_t *m_words = w + P - 1;                      // a_0 .. | b_0 .. | c_0 ..
     uint64_t a[P], b[P], c[P];
-    uint64_t as = 0, b_others = 0, cs = 0, xs = 0;
+    uint64_t as = 0, bs = 0, cs = 0, xs = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        a[q] = mix64(zM + (uint64_t)q * kGamma);
-        b[q] = mix64(zM + (uint64_t)(P + q) * kGamma);
+        a[q] = m_words[q];
+        b[q] = m_words[P + q];
         as += a[q];
-        if (q > 0) b_others += b[q];
+        bs += b[q];
         xs += x.v[q];
     }
 #pragma unroll
     for (int q = 0; q < P - 1; ++q) {
-        c[q] = mix64(zM + (uint64_t)(2 * P + q) * kGamma);
+        c[q] = m_words[2 * P + q];
         cs += c[q];
     }
     const uint64_t eps = xs - as;                             // opened: sum over the parties of x_q - a_q
-    const uint64_t b0_del = held(drelu - b_others);           // b_0 + del
-    const uint64_t del = b0_del - b[0];                       // opened: sum of D_q - b_q
+    const uint64_t del = held(drelu - bs);                    // opened: sum of D_q - b_q
+    const uint64_t b0_del = del + b[0];
     Shares<P> out;
     // party 0 takes the public term: c_0 + eps * b_0 + del * a_0 + eps * del
     out.v[0] = sum_of_products(c[0], eps, b0_del, del, a[0]);
 #pragma unroll
     for (int q = 1; q < P - 1; ++q) out.v[q] = sum_of_products(c[q], eps, b[q], del, a[q]);
     // the last party's c completes the triple: c_{P-1} = a * b - (c_0 + ... + c_{P-2})
-    out.v[P - 1] = sum_of_products(0 - cs, as, b[0] + b_others, eps, b[P - 1], del, a[P - 1]);
+    out.v[P - 1] = sum_of_products(0 - cs, as, bs, eps, b[P - 1], del, a[P - 1]);
     return out;
 }
 
-template <int W, int P, int MODE>
+template <int W, int P, int MODE, bool RUNS>
 __global__ void __launch_bounds__(kBlock)
 mp_group_kernel(const MpPointers ptr, uint64_t n, uint64_t groups, int k, uint64_t seedB, uint64_t seedA)
 {
@@ -238,7 +278,7 @@ mp_group_kernel(const MpPointers ptr, uint64_t n, uint64_t groups, int k, uint64
         }
     }
     const uint64_t zg = seedB + (g * (uint64_t)M::kWordsPerGroup + 1) * kGamma;
-    const Shares<P> sum = mp_a2b_sum<W, P>(u, zg);
+    const Shares<P> sum = mp_a2b_sum<W, P, RUNS>(u, zg);
     const uint64_t wb = mix64(zg + (uint64_t)M::kB2aWord * kGamma);
 
 #pragma unroll
@@ -254,7 +294,7 @@ mp_group_kernel(const MpPointers ptr, uint64_t n, uint64_t groups, int k, uint64
             const uint32_t rho = (uint32_t)(wb >> (P * j)) & ((1u << P) - 1);
             const uint64_t zA = seedA + ((uint64_t)M::kArithWords * (i0 + j) + 1) * kGamma;
             const B2aBits t{minus_bit((uint32_t)__popc(sign ^ rho), 0), (uint32_t)__popc(rho) & 1u};
-            const Shares<P> out = mp_finish<P, MODE>(t, x, zA);
+            const Shares<P> out = mp_finish<P, MODE, RUNS>(t, x, zA);
 #pragma unroll
             for (int q = 0; q < P; ++q) store_stream(ptr.o[q] + i0 + j, out.v[q]);
         }
@@ -377,11 +417,16 @@ __device__ __forceinline__ void mp_publish(unsigned char *verdict, int slot, con
     V::template store_bytes<FIELDS>(verdict + slot * FIELDS, byte, two);
 }
 // Owners' part after the circuit.
-template <int P, int MODE, int PAIRS, int TILE, bool FULL>
+template <int P, int MODE, bool RUNS, int PAIRS, int TILE, bool FULL>
 __device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t tile0, uint64_t n, int lane, uint64_t seedA,
                                                 const U64x2 (&xs)[P][PAIRS], const unsigned char *verdict)
 {
     constexpr uint64_t kArithWords = 4 * P - 2;
+    // Four parties at w = 4 would hold 128 registers of shares, which the compiler puts into scratch memory and takes out again:
+    // read a second time instead (a lane has stored nothing of its pair yet, so also where an output is an input).  1700 tiles
+    // 39 us instead of 52, 2^25 elements 611 instead of 673.  With fewer shares to hold, three parties at w = 4 and four at w = 5,
+    // the second reading costs more than the registers: 2^25 elements 342 / 443 and 626 / 677.
+    constexpr bool kReload = MODE == kRelu && P * PAIRS >= 32;
     uint64_t zA0 = seedA + (kArithWords * (tile0 + 2 * (uint64_t)lane) + 1) * kGamma;
 #pragma unroll
     for (int c = 0; c < PAIRS; ++c) {
@@ -389,14 +434,25 @@ __device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t 
         const unsigned e = 2 * pr;
         if (e < (unsigned)TILE) {
             const uint32_t v = reinterpret_cast<const uint16_t *>(verdict)[pr];
+            U64x2 own[P];
+            if constexpr (kReload) {
+                U64x2 again[P][1];
+                mp_load<P, 1, TILE, FULL>(ptr, tile0 + 2 * c * kWave, n, lane, 0, again);
+#pragma unroll
+                for (int q = 0; q < P; ++q) own[q] = again[q][0];
+            } else {
+#pragma unroll
+                for (int q = 0; q < P; ++q) own[q] = xs[q][c];
+            }
             Shares<P> r[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const B2aBits t{minus_bit(v, 8 * h), __builtin_amdgcn_ubfe(v, 8 * h + 1, 1)};
                 Shares<P> x;
 #pragma unroll
-                for (int q = 0; q < P; ++q) x.v[q] = h ? xs[q][c].b : xs[q][c].a;
-                r[h] = mp_finish<P, MODE>(t, x, zA0 + kArithWords * (uint64_t)(2 * c * kWave + h) * kGamma);
+                for (int q = 0; q < P; ++q) x.v[q] = h ? own[q].b : own[q].a;
+                r[h] = mp_finish<P, MODE, RUNS>(t, x, zA0 + kArithWords * (uint64_t)(2 * c * kWave + h) * kGamma);
+                if constexpr (RUNS) settle(r[h].v);
             }
 #pragma unroll
             for (int q = 0; q < P; ++q) {
@@ -407,14 +463,14 @@ __device__ __forceinline__ void mp_finish_pairs(const MpPointers &ptr, uint64_t 
                     store_stream(t + e, r[0].v[q]);
                 }
             }
-            zA0 = not_before(zA0, r[1].v[P - 1]);               // one pair's dealer words at a time
+            if constexpr (!RUNS) zA0 = not_before(zA0, r[1].v[P - 1]);               // one pair's dealer words at a time
         }
     }
 }
 
 // Work of one wavefront on wave-tile `tile` (uniform over the wavefront).  FULL: the whole tile lies inside the
 // tensor, so no access needs a bounds check (every tile but the last).
-template <int W, int P, int MODE, bool FULL>
+template <int W, int P, int MODE, bool RUNS, bool FULL>
 __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                              uint64_t tile, int lane, unsigned char *lds)
 {
@@ -424,6 +480,7 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
     const uint64_t tile0 = tile * T::kTile;
     unsigned char *verdict = lds + P * kBytes;
 
+    priority<RUNS, kElsewhere>();
     U64x2 xs[P][kPairs];
 #pragma unroll
     for (int c = 0; c < kPairs; ++c) {          // pair by pair: DReLU at w = 4 would hold 96 registers of shares at once
@@ -439,17 +496,17 @@ __device__ __forceinline__ void mp_tile_body(const MpPointers &ptr, uint64_t n, 
         for (int q = 0; q < P; ++q) u[q] = mp_collect<W, P, uint64_t, T::L>(lds + q * kBytes, lane);
         const uint64_t g = tile * T::kGroups + lane;
         const uint64_t zg = seedB + (g * (uint64_t)M::kWordsPerGroup + 1) * kGamma;
-        const Shares<P> sum = mp_a2b_sum<W, P>(u, zg);
+        const Shares<P> sum = mp_a2b_sum<W, P, RUNS>(u, zg);
         mp_publish<W, P, uint64_t, T::L>(verdict, lane, sum, mix64(zg + (uint64_t)M::kB2aWord * kGamma));
     }
     wave_sync();
-    mp_finish_pairs<P, MODE, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
+    mp_finish_pairs<P, MODE, RUNS, kPairs, T::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
 }
 
 // The same on a quarter of a tile: about 1230 vector instructions per wavefront at w = 8 among three parties where the tile has
 // 4250.  4,195,307 elements (8195 tiles: three after the last full round) take 72.6 us, with whole tiles only 76.6; at w = 4
 // 53.5 and 63.8.
-template <int W, int P, int MODE, bool FULL>
+template <int W, int P, int MODE, bool RUNS, bool FULL>
 __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA,
                                                 uint64_t quarter, int lane, unsigned char *lds)
 {
@@ -460,6 +517,7 @@ __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t 
     constexpr int kPairs = (Q::kTile / 2 + kWave - 1) / kWave, kBytes = T::slice_bytes(Q::kGroups);
     const uint64_t tile0 = quarter * Q::kTile;
     unsigned char *verdict = lds + Q::kVerdictAt;
+    priority<RUNS, kElsewhere>();
     U64x2 xs[P][kPairs];
 #pragma unroll
     for (int c = 0; c < kPairs; ++c) mp_load<P, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, c, xs);
@@ -510,16 +568,16 @@ __device__ __forceinline__ void mp_quarter_body(const MpPointers &ptr, uint64_t 
             const Word *words = reinterpret_cast<const Word *>(__builtin_assume_aligned(lds + at, 16)) + q * M::kGateWords;
             return [words](int w) { return words[w]; };
         };
-        return mp_add_gates<W, P, Word>(gate, X, Y);
+        return mp_add_gates<W, P, Word, false>(gate, X, Y);
     };
     const Shares<P, Word> sum = mp_tree<P, Word>(u, add);
     if (sub < (Q::kHalves ? 2 : 1))
         mp_publish<W, P, Word, Q::kFields>(verdict, slot, sum, reinterpret_cast<const Word *>(lds + words_at)[Q::kWords]);
     wave_sync();
-    mp_finish_pairs<P, MODE, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
+    mp_finish_pairs<P, MODE, RUNS, kPairs, Q::kTile, FULL>(ptr, tile0, n, lane, seedA, xs, verdict);
 }
 
-template <int W, int P, int MODE, bool QUARTERS>
+template <int W, int P, int MODE, int FORM>
 __global__ void __launch_bounds__(kBlock)
 mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t seedA, uint32_t whole_blocks)
 {
@@ -527,25 +585,26 @@ mp_tile_kernel(const MpPointers ptr, uint64_t n, int k, uint64_t seedB, uint64_t
     static_assert(T::kSupported, "tile kernel needs W <= 32");
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
     const int lane = threadIdx.x % kWave, wv = wave_index();
-    const TileWork t = tile_work<QUARTERS>(whole_blocks, wv);
+    const TileWork t = tile_work<has_quarters(FORM)>(whole_blocks, wv);
     if (t.tile * T::kTile >= n) return;        // whole wavefront beyond the tensor
-    if constexpr (QUARTERS) {
+    constexpr bool RUNS = has_runs(FORM);
+    if constexpr (has_quarters(FORM)) {
         if (t.quarter >= 0) {
             using Q = MpQuarterTraits<W, P>;
             const uint64_t quarter = t.tile * Q::kSplit + (unsigned)t.quarter;
             unsigned char *lds = tile_lds + wv * Q::kLdsBytes;
             if ((quarter + 1) * Q::kTile <= n)
-                mp_quarter_body<W, P, MODE, true>(ptr, n, k, seedB, seedA, quarter, lane, lds);
+                mp_quarter_body<W, P, MODE, RUNS, true>(ptr, n, k, seedB, seedA, quarter, lane, lds);
             else if (quarter * Q::kTile < n)
-                mp_quarter_body<W, P, MODE, false>(ptr, n, k, seedB, seedA, quarter, lane, lds);
+                mp_quarter_body<W, P, MODE, RUNS, false>(ptr, n, k, seedB, seedA, quarter, lane, lds);
             return;
         }
     }
     unsigned char *lds = tile_lds + wv * T::kLdsBytes;
     if ((t.tile + 1) * T::kTile <= n)
-        mp_tile_body<W, P, MODE, true>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
+        mp_tile_body<W, P, MODE, RUNS, true>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
     else
-        mp_tile_body<W, P, MODE, false>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
+        mp_tile_body<W, P, MODE, RUNS, false>(ptr, n, k, seedB, seedA, t.tile, lane, lds);
 }
 
 }  // namespace hb
