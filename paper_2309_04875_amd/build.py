@@ -1,9 +1,10 @@
-"""Build paper_2309_04875_amd/libhb.so (the library) and libhb_probes.so (bench.py's measurement aids, a separate
-library that the product does not load) from csrc/ with hipcc for gfx950 (cross-compiles without a GPU).
+"""Build paper_2309_04875_amd/libhb.so (the library), _binding.so (the native part of hb.py) and libhb_probes.so (bench.py's
+measurement aids, a separate library that the product does not load) from csrc/ with hipcc for gfx950 (cross-compiles without a
+GPU; the binding is host code).
 
 The group kernels exist once per (mode, slice width); hb_launch_part.hip is compiled once per mode and
 width range so that the parts build in parallel.  Objects go to a temporary directory; only the
-library is left in the tree.  Run as `python -m paper_2309_04875_amd.build`.
+libraries are left in the tree.  Run as `python -m paper_2309_04875_amd.build`.
 """
 import os
 import shutil
@@ -15,6 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIBRARY = os.path.join(HERE, "libhb.so")
 PROBES_LIBRARY = os.path.join(HERE, "libhb_probes.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -48,6 +50,23 @@ def _compile(args):
     return out
 
 
+def _build_binding():
+    """The native part of hb.py: host code against Python, torch and libhb.so beside it."""
+    import sysconfig
+    import torch
+    inside = os.path.dirname(torch.__file__)
+    lib = os.path.join(inside, "lib")
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"]]
+    for path in (os.path.join(inside, "include"), os.path.join(inside, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"):
+        cmd += ["-isystem", path]
+    cmd += [os.path.join(CSRC, "hb_binding.cpp"), "-o", tmp, "-L" + HERE, "-l:" + os.path.basename(LIBRARY), "-L" + lib,
+            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False, jobs: int = 0) -> str:
     jobs = jobs or min(8, os.cpu_count() or 1)
     work = tempfile.mkdtemp(prefix="hb_build_")
@@ -79,6 +98,7 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
             cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", tmp]
             subprocess.run(cmd, check=True)
             os.replace(tmp, library)
+        _build_binding()
     finally:
         shutil.rmtree(work, ignore_errors=True)
     return LIBRARY

@@ -1,14 +1,19 @@
-"""ctypes binding of the C ABI in include/hb.h -- argument marshalling only.
+"""Binding of the C ABI in include/hb.h -- argument marshalling only.
 
 Every function has the name and meaning of its C counterpart; tensors are torch int64 CUDA tensors
 whose `data_ptr()` is handed through, and the stream is torch's current stream unless one is given.
-There is no fallback: if libhb.so has not been built, loading raises.
+There is no fallback: if libhb.so or _binding.so has not been built, loading raises.
+
+Calls on small tensors are bound by the host, so the ordinary forms of a call (plain tensors and ints, outputs given, torch's
+current stream) go through native code, `_binding` (csrc/hb_binding.cpp), which returns NotImplemented for every other form.
+Those go through ctypes here, and so do all that are to raise for their arguments.
 """
 import ctypes
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(HERE, "libhb.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 HB_OK, HB_EINVAL, HB_EALIGN, HB_EHIP, HB_ENOTSUP, HB_ETOOBIG = 0, -1, -2, -3, -4, -5
 HB_PARTY_STATIC_BYTES = 64 << 20
@@ -25,6 +30,19 @@ EXPORTS = ("hb_drelu", "hb_relu", "hb_sign_shares", "hb_open", "hb_relu_batch", 
 _lib = None
 
 
+def _not_loaded(*args):
+    load()
+    return NotImplemented
+
+
+class _Native:
+    """The functions of `_binding`; until the library is loaded each loads it and leaves the call to ctypes."""
+    shares = parties = batch = plan_run = sim_relu = share = reveal = eco_scan = party = staticmethod(_not_loaded)
+
+
+_native = _Native
+
+
 class hb_tensor(ctypes.Structure):
     """Mirror of `struct hb_tensor` in include/hb.h."""
     _fields_ = [("share0", ctypes.c_void_p), ("share1", ctypes.c_void_p), ("out0", ctypes.c_void_p),
@@ -39,13 +57,14 @@ class HbError(RuntimeError):
 
 
 def load():
-    """Load libhb.so (once) and declare the prototypes."""
-    global _lib
+    """Load libhb.so and the native binding (once) and declare the prototypes."""
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIBRARY):
-        raise ImportError("%s is missing: build it with `python -m paper_2309_04875_amd.build` "
-                          "(there is no CPU fallback)" % LIBRARY)
+    for path in (LIBRARY, BINDING):
+        if not os.path.exists(path):
+            raise ImportError("%s is missing: build it with `python -m paper_2309_04875_amd.build` "
+                              "(there is no CPU fallback)" % path)
     lib = ctypes.CDLL(LIBRARY)
     vp, u64, sz, ci = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_int
     u64p = ctypes.POINTER(ctypes.c_uint64)
@@ -117,6 +136,10 @@ def load():
     lib.hb_strerror.argtypes = [ci]
     lib.hb_last_hip_error.restype = ctypes.c_char_p
     lib.hb_last_hip_error.argtypes = []
+    import torch                    # noqa: F401  (the binding's torch symbols)
+    from . import _binding
+    _binding.initialise(_check)
+    _native = _binding
     _lib = lib
     return lib
 
@@ -177,26 +200,46 @@ def _shares_call(name, share0, share1, k, m, seed, out0, out1, stream, dealer=No
 
 def hb_drelu(share0, share1, k, m, seed, out0=None, out1=None, stream=None):
     """Arithmetic shares of DReLU on the slice [k, m); returns (out0, out1, opened_bits)."""
+    if stream is None:
+        done = _native.shares(0, share0, share1, k, m, seed, None, out0, out1)
+        if done is not NotImplemented:
+            return done
     return _shares_call("hb_drelu", share0, share1, k, m, seed, out0, out1, stream)
 
 
 def hb_relu(share0, share1, k, m, seed, out0=None, out1=None, stream=None):
     """Arithmetic shares of x * DReLU; returns (out0, out1, opened_bits)."""
+    if stream is None:
+        done = _native.shares(1, share0, share1, k, m, seed, None, out0, out1)
+        if done is not NotImplemented:
+            return done
     return _shares_call("hb_relu", share0, share1, k, m, seed, out0, out1, stream)
 
 
 def hb_drelu_ex(share0, share1, k, m, seed, dealer, out0=None, out1=None, stream=None):
     """hb_drelu on the dealer layout `dealer` (HB_DEALER_PER_GATE or HB_DEALER_SHARED_MASK)."""
+    if stream is None and dealer is not None:
+        done = _native.shares(0, share0, share1, k, m, seed, dealer, out0, out1)
+        if done is not NotImplemented:
+            return done
     return _shares_call("hb_drelu_ex", share0, share1, k, m, seed, out0, out1, stream, dealer)
 
 
 def hb_relu_ex(share0, share1, k, m, seed, dealer, out0=None, out1=None, stream=None):
     """hb_relu on the dealer layout `dealer`."""
+    if stream is None and dealer is not None:
+        done = _native.shares(1, share0, share1, k, m, seed, dealer, out0, out1)
+        if done is not NotImplemented:
+            return done
     return _shares_call("hb_relu_ex", share0, share1, k, m, seed, out0, out1, stream, dealer)
 
 
 def hb_sign_shares(share0, share1, k, m, seed, out0=None, out1=None, stream=None):
     """XOR shares (0/1) of the sign bit after the adder circuit; returns (out0, out1, opened_bits)."""
+    if stream is None:
+        done = _native.shares(2, share0, share1, k, m, seed, None, out0, out1)
+        if done is not NotImplemented:
+            return done
     return _shares_call("hb_sign_shares", share0, share1, k, m, seed, out0, out1, stream)
 
 
@@ -208,6 +251,10 @@ def _mp_call(name, shares, k, m, seed, outs, stream):
     outs = list(outs)
     if len(outs) != len(shares):
         raise ValueError("one output per party")
+    if stream is None:
+        bits = _native.parties(int(name == "hb_relu_mp"), shares, k, m, seed, outs)
+        if bits is not NotImplemented:
+            return outs, bits
     n = _tensor_args(*shares, *outs) if shares else 0
     p = len(shares)
     tab_in = (ctypes.c_void_p * max(p, 1))(*[s.data_ptr() for s in shares])
@@ -243,6 +290,10 @@ def make_batch(items):
 
 
 def _batch_call(name, batch, stream, dealer=None):
+    if stream is None:
+        bits = _native.batch(int(name.startswith("hb_relu")), batch, dealer)
+        if bits is not NotImplemented:
+            return bits
     if not isinstance(batch, ctypes.Array):
         batch = make_batch(batch)
     bits = ctypes.c_uint64(0)
@@ -283,6 +334,10 @@ class Plan:
 
     def run(self, stream=None):
         """Returns the opened bits of the set."""
+        if stream is None and self._handle is not None:
+            bits = _native.plan_run(self._handle.value)
+            if bits is not NotImplemented:
+                return bits
         st = self._run(self._handle, ctypes.byref(self._bits), _stream_handle(stream))
         if st != HB_OK:
             _check(st)
@@ -324,6 +379,10 @@ def _float_arg(t):
 def hb_share_f32(x, share_seed, share0=None, share1=None, stream=None):
     """Encode to 2^16 fixed point and share additively; returns (share0, share1)."""
     import torch
+    if stream is None:
+        done = _native.share(x, share_seed, share0, share1)
+        if done is not NotImplemented:
+            return done
     n = _float_arg(x)
     if share0 is None:
         share0 = torch.empty(x.shape, dtype=torch.int64, device=x.device)
@@ -339,6 +398,10 @@ def hb_share_f32(x, share_seed, share0=None, share1=None, stream=None):
 def hb_reveal_f32(share0, share1, out=None, stream=None):
     """Open and decode to float32."""
     import torch
+    if stream is None:
+        done = _native.reveal(share0, share1, out)
+        if done is not NotImplemented:
+            return done
     n = _tensor_args(share0, share1)
     if out is None:
         out = torch.empty(share0.shape, dtype=torch.float32, device=share0.device)
@@ -351,6 +414,10 @@ def hb_reveal_f32(share0, share1, out=None, stream=None):
 def hb_sim_relu_f32(x, k, m, seed, share_seed, out=None, stream=None):
     """Approximate ReLU of plaintext floats through the protocol, one kernel."""
     import torch
+    if stream is None:
+        done = _native.sim_relu(x, k, m, seed, share_seed, out)
+        if done is not NotImplemented:
+            return done
     n = _float_arg(x)
     if out is None:
         out = torch.empty_like(x)
@@ -389,6 +456,10 @@ def hb_relu_party_ex(share0, share1, k, m, seed, dealer, out0=None, out1=None, w
     """Party-faithful ReLU on a dealer layout; returns (out0, out1, wire0, wire1, wire_bytes) where wire_p is an
     int64 view of party p's wire inside the workspace (a uint8 CUDA tensor, allocated here unless one is passed)."""
     import torch
+    if stream is None and dealer is not None:
+        done = _native.party(share0, share1, k, m, seed, dealer, out0, out1, workspace)
+        if done is not NotImplemented:
+            return done
     if out0 is None:
         out0 = torch.empty_like(share0)
     if out1 is None:
@@ -415,6 +486,10 @@ def hb_relu_party_ex(share0, share1, k, m, seed, dealer, out0=None, out1=None, w
 def hb_relu_party(share0, share1, k, m, seed, out0=None, out1=None, workspace=None, stream=None):
     """Party-faithful ReLU on the standard dealer layout (through the C entry point hb_relu_party)."""
     import torch
+    if stream is None:
+        done = _native.party(share0, share1, k, m, seed, None, out0, out1, workspace)
+        if done is not NotImplemented:
+            return done
     if out0 is None:
         out0 = torch.empty_like(share0)
     if out1 is None:
@@ -451,6 +526,10 @@ def hb_relu_party_static(share0, share1, k, m, seed, out0, out1, stream=None):
 def hb_eco_scan(share0, share1, counts=None, stream=None):
     """counts[m-1] = elements whose DReLU on [0, m) differs from the full ring; returns the 64-entry device tensor."""
     import torch
+    if stream is None:
+        done = _native.eco_scan(share0, share1, counts)
+        if done is not NotImplemented:
+            return done
     if counts is None:
         counts = torch.empty(64, dtype=torch.int64, device=share0.device)
     n = _tensor_args(share0, share1)
