@@ -552,8 +552,15 @@ uint64_t small_tile_limit(uint64_t usual)
 // tiles, which go by quarters, take as long either way.)
 // Among more parties a kernel's second round counts from its first tile on (76 tiles beyond 1024: w = 8 12.4 / 12.4 and 20.0 / 19.3,
 // w = 32 13.3 / 11.3 and 24.1 / 20.5; 676 tiles 5 to 15 % of any width).
-bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties)
+// Between 100 and 270 MB of shares and results, which stay in the cache before memory in part, DReLU of two parties at w = 10 to 12
+// loses with the form what it gains at other sizes: w = 10, 2, 4, 8, 16 M elements 15.1 / 13.7, 29.3 / 30.3, 56.1 / 54.0, 109 / 102,
+// shared-mask layout at w = 12 17.1 / 15.4, 35.5 / 36.5 (4.5 M), 59.1 / 60.3, 118 / 114.
+bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 {
+    if (op == kDrelu && parties == 2 && w <= 12) {
+        const uint64_t elements = tiles * (uint64_t)tile_elements(w);
+        if (elements > 3200000 && elements <= 8500000) return false;
+    }
     if (split == tiles) return tiles > kQuarterRound && tiles <= kSimds;
     if (tiles <= kSimds) return false;
     if (parties > 2) return w != 4 || tiles - kSimds > kQuarterRound;
@@ -570,7 +577,7 @@ TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
     const uint64_t whole = (tiles - split + kWavesPerBlock - 1) / kWavesPerBlock, blocks = whole + split;
     if (blocks > 0x7fffffffull) return TileGrid{0, 0, false, false};
-    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0, tile_runs(tiles, split, w, parties)};
+    return TileGrid{(uint32_t)whole, (uint32_t)blocks, split != 0, tile_runs(tiles, split, w, parties, op)};
 }
 
 bool group_runs(uint64_t blocks) { return blocks > kSimds / kWavesPerBlock; }

@@ -52,12 +52,12 @@ TileGrid tile_grid(uint64_t tiles, int w, int parties, int op);
 
 // Whether tile kernels have the form with RUNS (mix_words), which long launches then take (tile_runs).  Not where memory bounds long
 // launches, which wavefronts of unequal priority disturb: 2^25 elements, us, without / with: DReLU at w = 6 177 / 183, w = 8 175 /
-// 181, w = 9 216 / 207, w = 10 217 / 200; sign shares at w = 6 172 / 180, w = 12 211 / 204 (8 M elements 57 / 58), w = 16 241 / 221.
+// 181, w = 9 203 / 199 (16 M elements on the shared-mask layout 96.5 / 98.4), w = 10 217 / 200; sign shares at w = 6 172 / 180, w = 12 211 / 204 (8 M elements 57 / 58), w = 16 241 / 221.
 // Among three and four parties DReLU at w = 4 (2^24 elements, three 142 / 146; w = 5 154 / 148).
 constexpr bool runs_supported(int w, int parties, int op)
 {
     if (op == kSign) return w >= 13;
-    if (op == kDrelu) return parties == 2 ? w >= 9 : w >= 5;
+    if (op == kDrelu) return parties == 2 ? w >= 10 : w >= 5;
     return true;
 }
 
