@@ -501,19 +501,25 @@ LauncherTable &launcher_table()
 //             16     8.0 /  9.8   10.5 /  9.9                               16    13.2 / 16.4   17.3 / 16.6
 // (ReLU at w = 4, 1280 tiles: 10.2, as 1024 whole ones and 256 by quarters 11.6.  w = 7 has 72 pairs in a quarter: two passes
 // of the 64 lanes, the second one nearly empty.)
+// These were taken before tile_runs; with the form that it gives to more than one round of quarters ReLU at w = 5 takes 8.1 / 8.6
+// at 800 to 1024 tiles, w = 8 6.8 / 7.1 at 1088 and 7.6 / 7.9 at 1400 tiles (as 1024 whole ones and the rest by quarters; 1536
+// 8.3 / 8.0), the simulator at w = 8 6.2 / 6.3 at 800 to 1000; w = 6 and 9 are as fast either way up to 1024.
 constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
 constexpr int quarter_rounds(int w, int parties, int op)
 {
     if (parties > 2) return w == 4 ? 4 : w == 5 || w == 8 || (parties == 3 && (w == 6 || w == 10)) ? 3 : 2;
     if (w > 12) return w <= 21 ? 2 : 1;
-    if (op == kSimulator) return w == 4 ? 4 : w == 7 ? 1 : w == 6 || w >= 11 ? 2 : 3;
+    if (op == kSimulator) return w == 4 || w == 8 ? 4 : w == 7 ? 1 : w == 6 || w >= 11 ? 2 : 3;
     if (op == kSign) return w <= 6 || w == 8 ? 4 : 3;
     if (op == kDrelu) return w <= 5 ? 4 : 3;
-    return w == 4 ? 5 : w == 8 ? 4 : w == 7 ? 2 : 3;
+    return w == 4 || w == 8 ? 5 : w == 5 ? 4 : w == 7 ? 2 : 3;      // (w = 8: five and a half, tile_grid)
 }
 // Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
-// w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third would give ReLU at w = 8 (766 left: 8.9 / 10.3) what it takes from DReLU at w = 5
-// (after two full rounds 13.4 / 11.5).  One round only
+// w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third one after up to seven full rounds, of ReLU and the simulator at the widths where it
+// gains (600 left after one, two and four full rounds: ReLU w = 4 13.3 / 15.1, 19.0 / 20.5, 33.0 / 35.5; w = 8 8.4 / 9.5, 12.1 /
+// 12.9, 20.8 / 21.5; w = 9 9.7 / 10.6, 13.3 / 14.5, 21.5 / 22.4; w = 12 9.1 / 9.3, 11.7 / 12.4, 18.2 / 18.8; w = 5 11.9 / 12.5, 17.3 /
+// 17.7, 29.1 / 30.0; w = 6 10.8 / 11.2, 15.5 / 15.0; simulator w = 8 9.1 / 9.4, 12.3 / 13.1, w = 6 11.6 / 11.1, w = 12 9.3 / 8.9); DReLU
+// at w = 5 would lose (after two full rounds 13.4 / 11.5).  One round only
 //   - from w = 22, among more parties from w = 13 on, and of the simulator at w = 7 and from w = 17 on (376 left 9.0 / 8.8),
 //   - of sign shares at w = 5 and 6 after two full rounds (452 left 11.4 / 11.1 and 9.8 / 8.7; after one 6.2 / 6.8, after three
 //     15.9 / 17.2 and 12.9 / 13.9): three rounds of them reside together and wait for memory alone.
@@ -527,6 +533,10 @@ constexpr uint64_t shared_remainder(uint64_t tiles, int w, int parties, int op)
     if (parties > 2 ? w >= 13 : w >= 22) return kQuarterRound;
     if (op == kSimulator && (w == 7 || w >= 17)) return kQuarterRound;
     if (op == kSign && (w == 5 || w == 6) && full == 2) return kQuarterRound;
+    if (parties == 2 && full < 8) {
+        if (op == kRelu && (w == 4 || (w >= 8 && w <= 12) || (w == 5 && full <= 4) || (w == 6 && full == 1))) return 3 * kQuarterRound;
+        if (op == kSimulator && (w == 4 || w == 8)) return 3 * kQuarterRound;
+    }
     return 2 * kQuarterRound;
 }
 
@@ -561,7 +571,7 @@ bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
         const uint64_t elements = tiles * (uint64_t)tile_elements(w);
         if (elements > 3200000 && elements <= 8500000) return false;
     }
-    if (split == tiles) return tiles > kQuarterRound && tiles <= kSimds;
+    if (split == tiles) return tiles > kQuarterRound && (w == 8 || tiles <= kSimds);
     if (tiles <= kSimds) return false;
     if (parties > 2) return w != 4 || tiles - kSimds > kQuarterRound;
     if (w <= 3 || w == 7 || w >= 13) return true;
@@ -571,7 +581,8 @@ bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
 {
     const uint64_t left = tiles % kSimds;
-    const uint64_t limit = small_tile_limit((uint64_t)quarter_rounds(w, parties, op) * kQuarterRound + 1);
+    const bool relu8 = w == 8 && parties == 2 && op == kRelu;
+    const uint64_t limit = small_tile_limit((uint64_t)quarter_rounds(w, parties, op) * kQuarterRound + 1 + (relu8 ? kQuarterRound / 2 : 0));
     uint64_t split = 0;
     if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= shared_remainder(tiles, w, parties, op) ? left : 0;
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
