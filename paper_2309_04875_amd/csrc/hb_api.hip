@@ -502,8 +502,8 @@ LauncherTable &launcher_table()
 // (ReLU at w = 4, 1280 tiles: 10.2, as 1024 whole ones and 256 by quarters 11.6.  w = 7 has 72 pairs in a quarter: two passes
 // of the 64 lanes, the second one nearly empty.)
 // These were taken before tile_runs; with the form that it gives to more than one round of quarters ReLU at w = 5 takes 8.1 / 8.6
-// at 800 to 1024 tiles, w = 8 6.8 / 7.1 at 1088 and 7.6 / 7.9 at 1400 tiles (as 1024 whole ones and the rest by quarters; 1536
-// 8.3 / 8.0), the simulator at w = 8 6.2 / 6.3 at 800 to 1000; w = 6 and 9 are as fast either way up to 1024.
+// at 800 to 1024 tiles, w = 8 6.8 / 7.1 at 1088 tiles (as 1024 whole ones and the rest by quarters; 1536 8.3 / 8.0), the simulator
+// at w = 8 6.2 / 6.3 at 800 to 1000; w = 6 and 9 are as fast either way up to 1024.
 constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
 constexpr int quarter_rounds(int w, int parties, int op)
 {
@@ -512,7 +512,7 @@ constexpr int quarter_rounds(int w, int parties, int op)
     if (op == kSimulator) return w == 4 || w == 8 ? 4 : w == 7 ? 1 : w == 6 || w >= 11 ? 2 : 3;
     if (op == kSign) return w <= 6 || w == 8 ? 4 : 3;
     if (op == kDrelu) return w <= 5 ? 4 : 3;
-    return w == 4 || w == 8 ? 5 : w == 5 ? 4 : w == 7 ? 2 : 3;      // (w = 8: five and a half, tile_grid)
+    return w == 4 || w == 8 ? 5 : w == 5 ? 4 : w == 7 ? 2 : 3;
 }
 // Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
 // w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third one after up to seven full rounds, of ReLU and the simulator at the widths where it
@@ -581,8 +581,7 @@ bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
 {
     const uint64_t left = tiles % kSimds;
-    const bool relu8 = w == 8 && parties == 2 && op == kRelu;
-    const uint64_t limit = small_tile_limit((uint64_t)quarter_rounds(w, parties, op) * kQuarterRound + 1 + (relu8 ? kQuarterRound / 2 : 0));
+    const uint64_t limit = small_tile_limit((uint64_t)quarter_rounds(w, parties, op) * kQuarterRound + 1);
     uint64_t split = 0;
     if (quarters_supported(w) && limit != 0) split = tiles < limit ? tiles : left <= shared_remainder(tiles, w, parties, op) ? left : 0;
     if (tiles < kSimds && split < tiles) split = 0;          // no full round before them
