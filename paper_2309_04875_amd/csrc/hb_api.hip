@@ -790,9 +790,9 @@ int hb_share_f32(const float *x, size_t n, uint64_t share_seed, int64_t *share0,
     if (st != HB_OK) return st;
     const Range rx{(uintptr_t)x, (uintptr_t)x + 4 * n}, r0 = range_of(share0, n), r1 = range_of(share1, n);
     if (!disjoint(r0, r1) || !disjoint(rx, r0) || !disjoint(rx, r1)) return HB_EINVAL;
-    const uint64_t blocks = (((uint64_t)n + 1) / 2 + hb::kBlock - 1) / hb::kBlock;
+    const uint64_t blocks = (((uint64_t)n + 1) / 2 + hb::kShareBlock - 1) / hb::kShareBlock;
     if (blocks > 0x7fffffffull) return HB_EINVAL;
-    hipLaunchKernelGGL(hb::share_f32_kernel, dim3((unsigned)blocks), dim3(hb::kBlock), 0, (hipStream_t)stream, x,
+    hipLaunchKernelGGL(hb::share_f32_kernel, dim3((unsigned)blocks), dim3(hb::kShareBlock), 0, (hipStream_t)stream, x,
                        (uint64_t)n, share_seed, (uint64_t *)share0, (uint64_t *)share1);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? HB_OK : fail_hip(e, "kernel launch");

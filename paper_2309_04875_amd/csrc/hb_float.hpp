@@ -9,14 +9,17 @@ namespace hb {
 // What bounds both: HBM (20 bytes per element), and below a few million elements the latency of a launch.  A lane takes one
 // pair: 16-byte accesses on the shares, 8-byte ones on the floats, which the interface aligns to 4 bytes only.  With the
 // non-temporal hint on the shares 16,777,216 elements are shared in 47 us and revealed in 53 (7.1 and 6.4 TB/s; 59 and 57
-// without it; 69 and 62 with one element a lane), 802,816 in 5.7 and 5.6 (6.2 and 6.1).
+// without it; 69 and 62 with one element a lane), 802,816 in 5.7 and 5.6 (6.2 and 6.1).  Sharing, a draw per element between load
+// and store, starts sooner in smaller workgroups: 128 threads instead of 256, launch after launch, 65,536 elements 2.09 us instead of
+// 2.20, 262,144 2.44 / 2.88, 802,816 3.72 / 4.13, 16,777,216 47.4 / 47.4; revealing takes as long either way.
+constexpr int kShareBlock = 128;
 typedef float f32x2_t __attribute__((ext_vector_type(2), aligned(4)));
 
 // Encode and share: share0[i] = output i of the stream started at seedS, share1[i] = round(2^16 x[i]) - share0[i].
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kShareBlock)
 share_f32_kernel(const float *x, uint64_t n, uint64_t seedS, uint64_t *s0, uint64_t *s1)
 {
-    const uint64_t i = 2 * ((uint64_t)blockIdx.x * kBlock + threadIdx.x);
+    const uint64_t i = 2 * ((uint64_t)blockIdx.x * kShareBlock + threadIdx.x);
     if (i >= n) return;
     const uint64_t z = seedS + (i + 1) * kGamma;
     const uint64_t ra = mix64(z);
