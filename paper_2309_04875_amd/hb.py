@@ -290,11 +290,11 @@ def make_batch(items):
 
 
 def _batch_call(name, batch, stream, dealer=None):
-    if stream is None:
-        bits = _native.batch(int(name.startswith("hb_relu")), batch, dealer)
-        if bits is not NotImplemented:
-            return bits
     if not isinstance(batch, ctypes.Array):
+        if stream is None:
+            bits = _native.batch(int(name.startswith("hb_relu")), batch, dealer)
+            if bits is not NotImplemented:
+                return bits
         batch = make_batch(batch)
     bits = ctypes.c_uint64(0)
     layout = () if dealer is None else (int(dealer),)
