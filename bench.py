@@ -54,7 +54,7 @@ def profile_constants():
 def kernel_name(w, op="relu", batched=False):
     if w <= 32:
         return "hb::%s<%d, %s>" % ("tile_batch_kernel" if batched else "tile_kernel", w, op)
-    return "hb::group_kernel<%d, %s, vec>" % (w, op)
+    return "hb::group_kernel<%d, %s>" % (w, op)
 
 
 def party_path_bytes(n, k, m):
