@@ -291,7 +291,7 @@ def make_batch(items):
 
 def _batch_call(name, batch, stream, dealer=None):
     if not isinstance(batch, ctypes.Array):
-        if stream is None:
+        if stream is None and (dealer is not None or not name.endswith("_ex")):      # an _ex call without its layout raises below
             bits = _native.batch(int(name.startswith("hb_relu")), batch, dealer)
             if bits is not NotImplemented:
                 return bits
