@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../../include/hb.h"
+#include "hb_gil.hpp"
 
 namespace {
 
@@ -64,16 +65,6 @@ bool int_of(PyObject *o, int &v)
 }
 
 void *current_stream() { return c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream(); }
-
-template <class Call>
-int without_gil(const Call &call)
-{
-    int st = HB_OK;
-    Py_BEGIN_ALLOW_THREADS
-    st = call();
-    Py_END_ALLOW_THREADS
-    return st;
-}
 
 // The result of a call, or the exception of its status.
 PyObject *checked(int st, PyObject *result)
