@@ -46,7 +46,7 @@ enum hb_status {
     HB_OK = 0,
     HB_EINVAL = -1, /* null pointer with n > 0, bad (k, m), n too large, forbidden overlap, not device memory */
     HB_EALIGN = -2, /* a pointer is not 8-byte aligned */
-    HB_EHIP = -3,   /* the HIP runtime refused the launch; hb_last_hip_error() names the reason */
+    HB_EHIP = -3,   /* the HIP runtime refused the launch, or host memory ran out; hb_last_hip_error() names the reason */
     HB_ENOTSUP = -4, /* this entry point has no kernel for the requested slice width (no entry point returns it today) */
     HB_ETOOBIG = -5  /* hb_relu_party_static: the call needs more workspace than the library's static array holds */
 };

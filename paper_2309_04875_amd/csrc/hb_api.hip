@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <utility>
 #include <vector>
@@ -28,6 +29,17 @@ int fail_hip(hipError_t e, const char *what)
     std::snprintf(g_hip_error, sizeof(g_hip_error), "%s: %s", what, hipGetErrorString(e));
     (void)hipGetLastError();
     return HB_EHIP;
+}
+
+// No C++ exception leaves an entry point: what can throw here is the host memory of a set's launches.
+template <class Body>
+int no_throw(const Body &body)
+{
+    try {
+        return body();
+    } catch (const std::exception &) {
+        return fail_hip(hipErrorOutOfMemory, "host memory");
+    }
 }
 
 bool valid_slice(int k, int m) { return k >= 0 && m > k && m <= 64; }
@@ -382,7 +394,7 @@ int run_batch(int mode, const hb_tensor *tensors, size_t count, uint64_t *opened
     int st = validate_set(mode, tensors, count, &bits);
     if (st != HB_OK) return st;
     std::vector<LaunchItem> items;
-    st = plan_launches(mode, tensors, count, items);
+    st = no_throw([&] { return plan_launches(mode, tensors, count, items); });
     if (st != HB_OK) return st;
     for (const LaunchItem &it : items) {
         const hipError_t e = enqueue(it, (hipStream_t)stream);
@@ -678,7 +690,7 @@ int hb_plan_create(const hb_tensor *tensors, size_t count, int relu, int dealer,
     if (st != HB_OK) return st;
     hb_plan *p = new (std::nothrow) hb_plan;
     if (p == nullptr) return HB_EINVAL;
-    st = plan_launches(mode, tensors, count, p->items);
+    st = no_throw([&] { return plan_launches(mode, tensors, count, p->items); });
     if (st != HB_OK) {
         delete p;
         return st;

@@ -9,6 +9,8 @@ import pytest
 
 from paper_2309_04875_amd import build, hb
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
 
 class _Everything:
     """Short cuts that would serve whatever they are given."""
@@ -54,3 +56,50 @@ def test_the_interpreter_lock_is_held_where_an_exception_is_caught(tmp_path):
                     "-o", str(tmp_path / "throwing.so")], check=True)
     child = subprocess.run([sys.executable, "-c", "import throwing; assert throwing.held_after_throw() == 1"], cwd=tmp_path, timeout=60)
     assert child.returncode == 0
+
+
+# Allocations of just the armed size fail: 4093 descriptors make plan_launches ask for 4093 bytes.
+FAILING = r"""
+#include <cstdlib>
+#include <new>
+static volatile size_t refused = 0;
+extern "C" void refuse(size_t bytes) { refused = bytes; }
+void *operator new(size_t bytes)
+{
+    void *p = bytes != 0 && bytes == refused ? nullptr : std::malloc(bytes ? bytes : 1);
+    if (p == nullptr) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+"""
+
+NO_MEMORY = r"""
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[2], ctypes.RTLD_GLOBAL)          # first, so that the library's operator new is this one
+lib = ctypes.CDLL(sys.argv[1])
+class Tensor(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("s0", "s1", "o0", "o1")] + [("n", ctypes.c_size_t), ("k", ctypes.c_int), ("m", ctypes.c_int), ("seed", ctypes.c_uint64)]
+count = ctypes.c_size_t(4093)
+set_ = (Tensor * 4093)(*[Tensor(k=12, m=20) for _ in range(4093)])
+bits, plan = ctypes.c_uint64(99), ctypes.c_void_p(99)
+stub.refuse(ctypes.c_size_t(4093))
+batch = lib.hb_relu_batch(set_, count, ctypes.byref(bits), None)
+made = lib.hb_plan_create(set_, count, 1, 0, ctypes.byref(plan))
+stub.refuse(ctypes.c_size_t(0))
+lib.hb_last_hip_error.restype = ctypes.c_char_p
+assert (batch, made) == (-3, -3), (batch, made)
+assert bits.value == 99 and plan.value is None and b"memory" in lib.hb_last_hip_error()
+assert lib.hb_relu_batch(set_, count, ctypes.byref(bits), None) == 0 and bits.value == 0
+"""
+
+
+def test_no_exception_leaves_the_c_interface(tmp_path):
+    if not os.path.exists(hb.LIBRARY) or shutil.which("g++") is None:
+        pytest.skip("needs g++ and a built library")
+    (tmp_path / "failing.cpp").write_text(FAILING)
+    stub = str(tmp_path / "failing.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", str(tmp_path / "failing.cpp"), "-o", stub], check=True)
+    child = subprocess.run([sys.executable, "-c", NO_MEMORY, hb.LIBRARY, stub], cwd=tmp_path, timeout=120,
+                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert child.returncode == 0, child.stdout
