@@ -14,6 +14,7 @@
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <vector>
 
@@ -77,13 +78,14 @@ PyObject *checked(int st, PyObject *result)
 }
 
 // Runs `body`, which returns what the function returns; C++ exceptions (tensors without memory of their own) are left to the
-// Python function.
+// Python function.  They come from before the C call, which throws none, and nothing after it does.
 template <class Body>
 PyObject *guarded(const Body &body)
 {
     try {
         return body();
     } catch (const std::exception &) {
+        PyErr_Clear();                    // where the exception came out of Python code (a dispatch mode of torch)
         return not_known();
     }
 }
@@ -287,19 +289,21 @@ PyObject *party(PyObject *, PyObject *const *a, Py_ssize_t count)
         const at::Tensor *workspace = tensor_of(a[8], at::kByte);
         if (!t.ok || workspace == nullptr || workspace->dim() != 1) return not_known();
         const size_t n = (size_t)t.n, workspace_bytes = (size_t)workspace->numel();
+        // The views of the wires are made before the launch: what throws here has not been enqueued and may be left to the Python
+        // function, which would enqueue it a second time otherwise.
+        const int64_t words = (int64_t)(has_dealer ? hb_party_wire_words_ex(n, k, m, dealer) : hb_party_wire_words(n, k, m));
+        THPObjectPtr wires[2];
+        for (int p = 0; p < 2; ++p) {
+            const int64_t at = (int64_t)(has_dealer ? hb_party_wire_offset_ex(n, k, m, dealer, p) : hb_party_wire_offset(n, k, m, p));
+            wires[p] = THPVariable_Wrap(workspace->slice(0, at, at + 8 * words).view(at::kLong));
+        }
         void *to = workspace->data_ptr(), *stream = current_stream();
         const int st = without_gil([&] {
             return has_dealer ? hb_relu_party_ex(s0, s1, n, k, m, seed, dealer, o0, o1, to, workspace_bytes, &bytes, stream)
                               : hb_relu_party(s0, s1, n, k, m, seed, o0, o1, to, workspace_bytes, &bytes, stream);
         });
         if (st != HB_OK) return checked(st, nullptr);
-        const int64_t words = (int64_t)(has_dealer ? hb_party_wire_words_ex(n, k, m, dealer) : hb_party_wire_words(n, k, m));
-        PyObject *wires[2] = {};
-        for (int p = 0; p < 2; ++p) {
-            const int64_t at = (int64_t)(has_dealer ? hb_party_wire_offset_ex(n, k, m, dealer, p) : hb_party_wire_offset(n, k, m, p));
-            wires[p] = THPVariable_Wrap(workspace->slice(0, at, at + 8 * words).view(at::kLong));
-        }
-        return Py_BuildValue("OONNK", a[6], a[7], wires[0], wires[1], (unsigned long long)bytes);
+        return Py_BuildValue("OOOOK", a[6], a[7], wires[0].get(), wires[1].get(), (unsigned long long)bytes);
     });
 }
 

@@ -155,3 +155,24 @@ def test_errors_of_the_library(k, m):
     assert raised[0] == raised[1]
     with pytest.raises(hb.HbError):
         hb.hb_relu(*s, K, M, SEED, o[0], o[0])                     # outputs overlap
+
+
+def test_nothing_is_enqueued_before_a_call_is_left_to_the_general_path():
+    from torch.utils._python_dispatch import TorchDispatchMode
+    s, o = _shares(), _outs()
+    workspace = torch.zeros(hb.hb_party_workspace_bytes(N, K, M), dtype=torch.uint8, device=DEV)
+    hb.load()
+    hb.hb_relu_party(*s, K, M, SEED, *_outs(), workspace)            # the native code is loaded by the first call of all
+
+    class Refuses(TorchDispatchMode):
+        written = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            if "view" in str(func):
+                self.written.append(bool(torch.count_nonzero(o[0])))
+                raise RuntimeError("no views")
+            return func(*args, **(kwargs or {}))
+    with pytest.raises(RuntimeError, match="no views"):
+        with Refuses():
+            hb.hb_relu_party(*s, K, M, SEED, *o, workspace)
+    assert Refuses.written == [False, True]                         # the short cut's try, then the general path's, after its launch
