@@ -1,6 +1,6 @@
-"""Build paper_2309_04875_amd/libhb.so (the library), _binding.so (the native part of hb.py) and libhb_probes.so (bench.py's
+"""Build paper_2309_04875_amd/libhb.so (the library), the _binding module (the native part of hb.py) and libhb_probes.so (bench.py's
 measurement aids, a separate library that the product does not load) from csrc/ with hipcc for gfx950 (cross-compiles without a
-GPU; the binding is host code).
+GPU; the binding is host code, left out where torch or Python's headers are missing).
 
 The group kernels exist once per (mode, slice width); hb_launch_part.hip is compiled once per mode and
 width range so that the parts build in parallel.  Objects go to a temporary directory; only the
@@ -9,6 +9,7 @@ libraries are left in the tree.  Run as `python -m paper_2309_04875_amd.build`.
 import os
 import shutil
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -16,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIBRARY = os.path.join(HERE, "libhb.so")
 PROBES_LIBRARY = os.path.join(HERE, "libhb_probes.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))     # the name says which Python it is for
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -51,14 +52,23 @@ def _compile(args):
 
 
 def _build_binding():
-    """The native part of hb.py: host code against Python, torch and libhb.so beside it."""
-    import sysconfig
-    import torch
+    """The native part of hb.py: host code against Python, torch and libhb.so beside it.  Without torch or Python's headers there is
+    none, and hb.py does without."""
+    headers = sysconfig.get_paths()["include"]
+    try:
+        import torch
+    except ImportError:
+        torch = None
+    if torch is None or not os.path.exists(os.path.join(headers, "Python.h")):
+        print("no _binding: %s" % ("torch cannot be imported" if torch is None else "Python.h is missing"))
+        if os.path.exists(BINDING):
+            os.remove(BINDING)                  # an older one would go on with the new library
+        return
     inside = os.path.dirname(torch.__file__)
     lib = os.path.join(inside, "lib")
     tmp = BINDING + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"]]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DHB_TORCH_VERSION="%s"' % torch.__version__, "-I" + headers]
     for path in (os.path.join(inside, "include"), os.path.join(inside, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"):
         cmd += ["-isystem", path]
     cmd += [os.path.join(CSRC, "hb_binding.cpp"), "-o", tmp, "-L" + HERE, "-l:" + os.path.basename(LIBRARY), "-L" + lib,

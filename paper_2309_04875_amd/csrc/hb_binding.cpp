@@ -333,4 +333,9 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_binding", "argument marshalling
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&g_module); }
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject *module = PyModule_Create(&g_module);
+    if (module != nullptr && PyModule_AddStringConstant(module, "torch_version", HB_TORCH_VERSION) != 0) Py_CLEAR(module);
+    return module;
+}

@@ -2,18 +2,23 @@
 
 Every function has the name and meaning of its C counterpart; tensors are torch int64 CUDA tensors
 whose `data_ptr()` is handed through, and the stream is torch's current stream unless one is given.
-There is no fallback: if libhb.so or _binding.so has not been built, loading raises.
+There is no fallback: if libhb.so has not been built, loading raises.
 
 Calls on small tensors are bound by the host, so the ordinary forms of a call (plain tensors and ints, outputs given, torch's
 current stream) go through native code, `_binding` (csrc/hb_binding.cpp), which returns NotImplemented for every other form.
-Those go through ctypes here, and so do all that are to raise for their arguments.
+Those go through ctypes here, and so do all that are to raise for their arguments, and every call where `_binding` could not be
+built (no Python headers) or was built for another Python or torch: the same entry points and kernels, a few us later.  Functions
+of numbers alone need neither it nor torch.
 """
 import ctypes
 import os
+import sys
+import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(HERE, "libhb.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 HB_OK, HB_EINVAL, HB_EALIGN, HB_EHIP, HB_ENOTSUP, HB_ETOOBIG = 0, -1, -2, -3, -4, -5
 HB_PARTY_STATIC_BYTES = 64 << 20
@@ -31,16 +36,25 @@ _lib = None
 
 
 def _not_loaded(*args):
-    load()
+    _load_native()
     return NotImplemented
 
 
-class _Native:
-    """The functions of `_binding`; until the library is loaded each loads it and leaves the call to ctypes."""
+def _left(*args):
+    return NotImplemented
+
+
+class _NotLoaded:
+    """The functions of `_binding`; until it is loaded each loads it and leaves the call to ctypes."""
     shares = parties = batch = plan_run = sim_relu = share = reveal = eco_scan = party = staticmethod(_not_loaded)
 
 
-_native = _Native
+class _NotThere:
+    """The same where there is no `_binding`: every call is left to ctypes."""
+    shares = parties = batch = plan_run = sim_relu = share = reveal = eco_scan = party = staticmethod(_left)
+
+
+_native = _NotLoaded
 
 
 class hb_tensor(ctypes.Structure):
@@ -57,14 +71,13 @@ class HbError(RuntimeError):
 
 
 def load():
-    """Load libhb.so and the native binding (once) and declare the prototypes."""
-    global _lib, _native
+    """Load libhb.so (once) and declare the prototypes; where torch is loaded already, load the native binding too."""
+    global _lib
     if _lib is not None:
         return _lib
-    for path in (LIBRARY, BINDING):
-        if not os.path.exists(path):
-            raise ImportError("%s is missing: build it with `python -m paper_2309_04875_amd.build` "
-                              "(there is no CPU fallback)" % path)
+    if not os.path.exists(LIBRARY):
+        raise ImportError("%s is missing: build it with `python -m paper_2309_04875_amd.build` "
+                          "(there is no CPU fallback)" % LIBRARY)
     lib = ctypes.CDLL(LIBRARY)
     vp, u64, sz, ci = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_int
     u64p = ctypes.POINTER(ctypes.c_uint64)
@@ -136,12 +149,29 @@ def load():
     lib.hb_strerror.argtypes = [ci]
     lib.hb_last_hip_error.restype = ctypes.c_char_p
     lib.hb_last_hip_error.argtypes = []
-    import torch                    # noqa: F401  (the binding's torch symbols)
-    from . import _binding
-    _binding.initialise(_check)
-    _native = _binding
     _lib = lib
+    if sys.modules.get("torch") is not None and _native is _NotLoaded:
+        _load_native()
     return lib
+
+
+def _load_native():
+    """Load `_binding`, which calls the same libhb.so.  Without it ctypes serves every call."""
+    global _native
+    load()
+    if _native is not _NotLoaded:                       # load() came here itself
+        return
+    try:
+        import torch                                    # the binding's torch symbols
+        from . import _binding
+        if _binding.torch_version != torch.__version__:
+            raise ImportError("it was built for torch %s" % _binding.torch_version)
+        _binding.initialise(_check)
+        _native = _binding
+    except ImportError as e:
+        warnings.warn("paper_2309_04875_amd: calls go through ctypes, a few us slower each (%s); "
+                      "`python -m paper_2309_04875_amd.build` builds the native binding" % e)
+        _native = _NotThere
 
 
 def strerror(status):

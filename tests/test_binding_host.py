@@ -103,3 +103,30 @@ def test_no_exception_leaves_the_c_interface(tmp_path):
     child = subprocess.run([sys.executable, "-c", NO_MEMORY, hb.LIBRARY, stub], cwd=tmp_path, timeout=120,
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert child.returncode == 0, child.stdout
+
+
+def test_functions_of_numbers_need_no_torch():
+    child = subprocess.run([sys.executable, "-W", "error", "-c", "import sys; sys.modules['torch'] = None\nfrom paper_2309_04875_amd import hb\n"
+                            "print(hb.hb_tensor_seed(1, 2), hb.hb_opened_bits(1, 12, 20, 1000), hb.hb_party_workspace_bytes(100, 12, 20))"],
+                           cwd=ROOT, timeout=120, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert child.returncode == 0, child.stdout
+    assert child.stdout.split() == [str(v) for v in (hb.hb_tensor_seed(1, 2), hb.hb_opened_bits(1, 12, 20, 1000), hb.hb_party_workspace_bytes(100, 12, 20))]
+
+
+def test_calls_go_through_ctypes_without_the_native_binding(monkeypatch):
+    hb.load()
+    name = hb.__package__ + "._binding"
+    monkeypatch.delattr(sys.modules[hb.__package__], "_binding", raising=False)
+    monkeypatch.setitem(sys.modules, name, None)                       # cannot be imported
+    monkeypatch.setattr(hb, "_native", hb._NotLoaded)
+    with pytest.warns(UserWarning, match="ctypes"):
+        assert hb._native.shares(1, None, None, 12, 20, 1, None, None, None) is NotImplemented
+    assert hb._native is hb._NotThere and hb._native.batch(1, [], None) is NotImplemented
+
+
+def test_build_without_python_headers(monkeypatch, tmp_path, capsys):
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "_binding.so"))
+    (tmp_path / "_binding.so").write_text("of an older build")
+    build._build_binding()
+    assert "Python.h" in capsys.readouterr().out and not (tmp_path / "_binding.so").exists()
