@@ -53,7 +53,7 @@ def _compile(args):
 
 def _build_binding():
     """The native part of hb.py: host code against Python, torch and libhb.so beside it.  Without torch or Python's headers there is
-    none, and hb.py does without."""
+    none, and hb.py does without.  (DT_RPATH: the libhb.so beside it, whatever LD_LIBRARY_PATH says, for hb.py loads that one.)"""
     headers = sysconfig.get_paths()["include"]
     try:
         import torch
@@ -72,7 +72,7 @@ def _build_binding():
     for path in (os.path.join(inside, "include"), os.path.join(inside, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include"):
         cmd += ["-isystem", path]
     cmd += [os.path.join(CSRC, "hb_binding.cpp"), "-o", tmp, "-L" + HERE, "-l:" + os.path.basename(LIBRARY), "-L" + lib,
-            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
+            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-Wl,--disable-new-dtags,-rpath,$ORIGIN"]
     subprocess.run(cmd, check=True)
     os.replace(tmp, BINDING)
 

@@ -130,3 +130,17 @@ def test_build_without_python_headers(monkeypatch, tmp_path, capsys):
     (tmp_path / "_binding.so").write_text("of an older build")
     build._build_binding()
     assert "Python.h" in capsys.readouterr().out and not (tmp_path / "_binding.so").exists()
+
+
+def test_the_binding_calls_the_library_beside_it(tmp_path):
+    """Another libhb.so in LD_LIBRARY_PATH, here one without functions, is not what `_binding` takes."""
+    if not os.path.exists(hb.BINDING) or shutil.which("gcc") is None:
+        pytest.skip("needs gcc and a built binding")
+    (tmp_path / "empty.c").write_text("int nothing;\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", str(tmp_path / "empty.c"), "-o", str(tmp_path / "libhb.so")], check=True)
+    path = str(tmp_path) + os.pathsep + os.environ.get("LD_LIBRARY_PATH", "")
+    child = subprocess.run([sys.executable, "-W", "error", "-c", "import torch; from paper_2309_04875_amd import hb; hb.load()\n"
+                            "assert hb._native.__name__.endswith('_binding')\n"
+                            "with open('/proc/self/maps') as maps: print({l.split()[-1] for l in maps if l.rstrip().endswith('libhb.so')})"],
+                           cwd=ROOT, env=dict(os.environ, LD_LIBRARY_PATH=path), timeout=120, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert child.returncode == 0 and child.stdout.strip() == str({os.path.realpath(hb.LIBRARY)}), child.stdout
