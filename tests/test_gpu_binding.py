@@ -102,11 +102,14 @@ def test_same_as_general_path(name, monkeypatch):
             assert g == r
 
 
-def test_plan_run():
+def test_plan_run(monkeypatch):
+    counted = _Counted(monkeypatch, "plan_run")
     s = _shares()
     o, p = _outs(), _outs()
     plan, other = hb.hb_plan_create([(*s, *o, K, M, SEED)]), hb.hb_plan_create([(*s, *p, K, M, SEED)])
-    assert hb.hb_plan_run(plan) == hb.hb_plan_run(other, torch.cuda.current_stream())
+    bits = hb.hb_plan_run(plan)
+    assert counted.served == 1
+    assert bits == hb.hb_plan_run(other, torch.cuda.current_stream()) and counted.served == 1
     assert torch.equal(o[0], p[0]) and torch.equal(o[1], p[1])
     plan.close()
     for st in (None, torch.cuda.current_stream()):
@@ -155,6 +158,82 @@ def test_errors_of_the_library(k, m):
     assert raised[0] == raised[1]
     with pytest.raises(hb.HbError):
         hb.hb_relu(*s, K, M, SEED, o[0], o[0])                     # outputs overlap
+
+
+# A call with every argument given, as (short cut, function, arguments); a list of tensors is an argument of one call among parties.
+def _full_calls():
+    s, x, y = _shares(4), torch.randn(N, device=DEV), torch.zeros(N, device=DEV)
+    workspace = [torch.zeros(hb.hb_party_workspace_bytes_ex(N, K, M, d), dtype=torch.uint8, device=DEV) for d in (0, 1)]
+    counts = torch.zeros(64, dtype=torch.int64, device=DEV)
+    return {
+        "relu": ("shares", hb.hb_relu, [s[0], s[1], K, M, SEED, *_outs()]),
+        "drelu": ("shares", hb.hb_drelu, [s[0], s[1], K, M, SEED, *_outs()]),
+        "sign": ("shares", hb.hb_sign_shares, [s[0], s[1], K, M, SEED, *_outs()]),
+        "relu_ex": ("shares", hb.hb_relu_ex, [s[0], s[1], K, M, SEED, 1, *_outs()]),
+        "drelu_ex": ("shares", hb.hb_drelu_ex, [s[0], s[1], K, M, SEED, 1, *_outs()]),
+        "relu_mp": ("parties", lambda a, b, c, *rest, **kw: hb.hb_relu_mp([a, b, c], *rest[:3], list(rest[3:]), **kw), [*s[:3], K, M, SEED, *_outs(3)]),
+        "drelu_mp": ("parties", lambda a, b, c, *rest, **kw: hb.hb_drelu_mp([a, b, c], *rest[:3], list(rest[3:]), **kw), [*s[:3], K, M, SEED, *_outs(3)]),
+        "batch": ("batch", lambda a, b, k, m, seed, c, d, **kw: hb.hb_relu_batch([(a, b, c, d, k, m, seed)], **kw), [s[0], s[1], K, M, SEED, *_outs()]),
+        "drelu_batch_ex": ("batch", lambda a, b, k, m, seed, c, d, **kw: hb.hb_drelu_batch_ex([(a, b, c, d, k, m, seed)], 1, **kw), [s[0], s[1], K, M, SEED, *_outs()]),
+        "sim": ("sim_relu", hb.hb_sim_relu_f32, [x, K, M, SEED, 3, y]),
+        "share": ("share", hb.hb_share_f32, [x, 3, *_outs()]),
+        "reveal": ("reveal", hb.hb_reveal_f32, [s[0], s[1], y]),
+        "eco": ("eco_scan", hb.hb_eco_scan, [s[0], s[1], counts]),
+        "party": ("party", hb.hb_relu_party, [s[0], s[1], K, M, SEED, *_outs(), workspace[0]]),
+        "party_ex": ("party", hb.hb_relu_party_ex, [s[0], s[1], K, M, SEED, 1, *_outs(), workspace[1]]),
+    }
+
+
+CHANGES = {
+    "type": lambda t: t.to(torch.float64 if t.dtype == torch.float32 else torch.int8 if t.dtype == torch.uint8 else torch.int32),
+    "host": lambda t: t.cpu(),
+    "strided": lambda t: t.repeat_interleave(2)[::2],
+    "short": lambda t: t[:-1],
+}
+
+
+@pytest.mark.parametrize("change", sorted(CHANGES))
+@pytest.mark.parametrize("name", sorted(("relu", "drelu", "sign", "relu_ex", "drelu_ex", "relu_mp", "drelu_mp", "batch", "drelu_batch_ex",
+                                         "sim", "share", "reveal", "eco", "party", "party_ex")))
+def test_every_tensor_of_every_call_is_checked(name, change, monkeypatch):
+    cut, call, args = _full_calls()[name]
+    counted = _Counted(monkeypatch, cut)
+    call(*args)
+    assert counted.served == 1
+    for i, arg in enumerate(args):
+        if not isinstance(arg, torch.Tensor):
+            continue
+        given = args[:i] + [CHANGES[change](arg)] + args[i + 1:]
+        raised = []
+        for kw in ({}, {"stream": torch.cuda.current_stream()}):
+            with pytest.raises((TypeError, ValueError, hb.HbError)) as e:
+                call(*given, **kw)
+            raised.append((type(e.value), str(e.value)))
+        assert raised[0] == raised[1] and counted.served == 1, (i, raised)
+
+
+def test_forms_of_sets_and_parties(monkeypatch):
+    counted = _Counted(monkeypatch, "batch")
+    s = _shares(4)
+    assert hb.hb_relu_batch([]) == hb.hb_relu_batch([], torch.cuda.current_stream()) == 0
+    served = counted.served
+    item = (*s[:2], *_outs(), K, M, SEED)
+    assert hb.hb_relu_batch([list(item)]) == hb.hb_relu_batch([item], torch.cuda.current_stream())    # a list for a tuple: as before
+    for wrong in ([item[:6]], [item + (1,)]):
+        with pytest.raises(ValueError):
+            hb.hb_relu_batch(wrong)
+    with pytest.raises(TypeError):
+        hb.hb_relu_batch_ex([item], None)
+    assert counted.served == served
+    for count in (1, 5, 9):                                        # 9: more than the short cut takes
+        raised = []
+        for kw in ({}, {"stream": torch.cuda.current_stream()}):
+            with pytest.raises(hb.HbError) as e:
+                hb.hb_relu_mp(_shares(count), K, M, SEED, _outs(count), **kw)
+            raised.append(str(e.value))
+        assert raised[0] == raised[1]
+    with pytest.raises(ValueError):
+        hb.hb_relu_mp(s[:3], K, M, SEED, _outs(2))
 
 
 def test_nothing_is_enqueued_before_a_call_is_left_to_the_general_path():
