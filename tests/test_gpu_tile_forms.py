@@ -1,6 +1,8 @@
 """Every width from 1 to 32 in every form of a tile launch, all operations, bit for bit against the oracle: whole tiles only
 (HB_SMALL_TILE_LIMIT=0), quarters only (a limit above every size), and the rule's own choice where a launch is mixed (three
-tiles after a full round of 1024) or whole (700 tiles after one).  The variable is read once, so each runs in a child process."""
+tiles after a full round of 1024; 700, where a third round of quarters is shared out) or whole (900 after one, more than any width
+shares out, so that every width's whole tiles run with dealer words in step where they have that form).  The variable is read
+once, so each runs in a child process."""
 import os
 import subprocess
 import sys
@@ -29,7 +31,7 @@ for w in range(1, 33):
     for parties in ((2,) if part == "two" else (3, 4)):
         L = min(64 // w, 32) if parties == 2 else min(64 // w, 64 // parties)
         per = (64 if w >= 4 else 32) * L
-        sizes = (1, L + 1, 16 * L + 1, per - 1, per, 5 * per + 17) if rule == "given" else (1027 * per + 5, 1724 * per + 5)
+        sizes = (1, L + 1, 16 * L + 1, per - 1, per, 5 * per + 17) if rule == "given" else (1027 * per + 5, 1724 * per + 5, 1924 * per - 5)
         for n in sizes:
             k = int(rng.integers(0, 64 - w + 1)); m = k + w
             off = n % 2                                        # odd sizes on buffers that are only 8-byte aligned
