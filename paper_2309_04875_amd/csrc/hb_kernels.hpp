@@ -773,7 +773,7 @@ __device__ __forceinline__ int wave_index()
 }
 
 // Which part of a launch a wavefront takes: workgroups 0 .. whole_blocks - 1 take four tiles each, the others one tile each.
-// Every tile kernel exists twice.  The one with QUARTERS holds both forms, and with them the larger one's registers and LDS
+// Every tile kernel of the widths that have quarters exists with them and without.  The one with QUARTERS holds both forms, and with them the larger one's registers and LDS
 // for every workgroup (ReLU at w = 24: 72 registers and 28 KiB; whole tiles alone 60 and 5 KiB, eight wavefronts per SIMD instead
 // of five), so launches without shared-out tiles take the one without: w = 24 on the shared-mask layout, 640 tiles 4.43 us instead
 // of 4.88, 1536 tiles 6.57 instead of 7.01; three parties at w = 4, DReLU, 4 M elements 37 instead of 41.

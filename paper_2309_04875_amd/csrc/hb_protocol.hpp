@@ -253,60 +253,12 @@ __device__ __forceinline__ WordPair<Word> beaver_and_words(const GateWords<Word>
     return Z;
 }
 
-// The same gate drawing its words inline: zq is the generator state of the gate's first dealer word; the five
-// words a_0 a_1 b_0 b_1 c_0 are consecutive outputs.
-__device__ __forceinline__ Pair beaver_and(uint64_t zq, uint64_t Ux, uint64_t Vx, uint64_t keep, Pair acc)
-{
-    GateWords<uint64_t> t;
-    t.a0 = mix64(zq);
-    t.a1 = mix64(zq + 1 * kGamma);
-    t.b0 = mix64(zq + 2 * kGamma);
-    t.b1 = mix64(zq + 3 * kGamma);
-    t.c0 = mix64(zq + 4 * kGamma);
-    return beaver_and_words(t, Ux, Vx, keep, acc);
-}
-
-// The two Beaver ANDs of a prefix round when one mask serves their common first operand U: T = U & V, Q = U & Y.
-// zr is the generator state of the round's first word; the eight words a_0 a_1 | b_0 b_1 c_0 (for V) |
-// b_0 b_1 c_0 (for Y) are consecutive outputs.  d = U ^ a is opened once.  Operands and `keep` as in beaver_and;
-// T comes back XORed onto accT.  With kSecond false only the first gate is evaluated and its three last words are
-// never drawn.
-template <bool kSecond>
-__device__ __forceinline__ void beaver_and_shared(uint64_t zr, uint64_t Ux, uint64_t Vx, uint64_t Yx, uint64_t keep,
-                                                  Pair accT, Pair &T, Pair &Q)
-{
-    const uint64_t a0 = mix64(zr);
-    const uint64_t a1 = mix64(zr + 1 * kGamma);
-    const uint64_t a = a0 ^ a1;
-    const uint64_t d = Ux ^ a;
-    {
-        const uint64_t b0 = mix64(zr + 2 * kGamma);
-        const uint64_t b1 = mix64(zr + 3 * kGamma);
-        const uint64_t c0 = mix64(zr + 4 * kGamma);
-        const uint64_t b = b0 ^ b1;
-        const uint64_t e = bitop3<kTtXorAnd>(b, Vx, keep);
-        T.p0 = bitop3<kTtXor3>(accT.p0, bitop3<kTtXorAnd>(c0, e, a0), bitop3<kTtAndXor>(d, b0, e));
-        const uint64_t c1 = bitop3<kTtXorAnd>(c0, a, b);
-        T.p1 = bitop3<kTtXorAnd>(bitop3<kTtXorAnd>(accT.p1 ^ c1, d, b1), e, a1);
-    }
-    if (kSecond) {
-        const uint64_t b0 = mix64(zr + 5 * kGamma);
-        const uint64_t b1 = mix64(zr + 6 * kGamma);
-        const uint64_t c0 = mix64(zr + 7 * kGamma);
-        const uint64_t b = b0 ^ b1;
-        const uint64_t e = bitop3<kTtXorAnd>(b, Yx, keep);
-        Q.p0 = bitop3<kTtXorAnd>(c0, e, a0) ^ bitop3<kTtAndXor>(d, b0, e);
-        const uint64_t c1 = bitop3<kTtXorAnd>(c0, a, b);
-        Q.p1 = bitop3<kTtXorAnd>(bitop3<kTtXorAnd>(c1, d, b1), e, a1);
-    }
-}
-
 // A2B + sign for one group.  u0/u1: the L sliced shares of party 0 / party 1 packed as fields.
 // z: generator state of the group's first dealer word.  Returns XOR shares of the sum word
 // S ^ (G << 1); the sign of field j is bit jW + W - 1.  The last round's P-update gate is not
 // evaluated: nothing reads its result (its dealer words are simply never drawn).  SHARED selects the
-// dealer layout in which the two gates of a round share the mask of P (words a_0 a_1 | b_0 b_1 c_0 of the G-update |
-// b_0 b_1 c_0 of the P-update).  B2A: the group's B2A word is drawn with the last gate's and left in `b2a`.
+// dealer layout in which the two gates of a round share the mask of P: eight words a_0 a_1 | b_0 b_1 c_0 of the G-update |
+// b_0 b_1 c_0 of the P-update, of which the last round leaves three undrawn.  B2A: the group's B2A word is drawn with the last gate's and left in `b2a`.
 // A gate's words are used up before the next are drawn.  (Ten words in step, those of a round, take 16 registers more, which
 // costs a wavefront per SIMD at most widths: w = 8 and 10 as fast, w = 16 6 % slower.)
 template <int W, bool SHARED, bool B2A, bool RUNS>
