@@ -53,7 +53,8 @@ hipError_t launch_batch(const hb::BatchArgs &args, hipStream_t stream)
                                stream, args);
             return hipGetLastError();
         };
-        return hb::with_form<W, hb::runs_supported(W, 2, hb::op_of(MODE))>(grid, go);
+        // (no entry point takes a set for its sign shares: that launcher is there for the table's sake, in the fewest forms)
+        return hb::with_form<W, hb::op_of(MODE) != hb::kSign && hb::runs_supported(W, 2, hb::op_of(MODE))>(grid, go);
     } else {
         return hipErrorInvalidDeviceFunction;
     }
