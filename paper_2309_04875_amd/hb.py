@@ -164,8 +164,9 @@ def _load_native():
     try:
         import torch                                    # the binding's torch symbols
         from . import _binding
-        if _binding.torch_version != torch.__version__:
-            raise ImportError("it was built for torch %s" % _binding.torch_version)
+        built_for = getattr(_binding, "torch_version", None)         # a module of an older build says nothing
+        if built_for != torch.__version__:
+            raise ImportError("it was built for torch %s" % built_for)
         _binding.initialise(_check)
         _native = _binding
     except ImportError as e:
