@@ -69,3 +69,9 @@ def test_scratch(kernels):
     # Four-party ReLU at w = 4 keeps its shares there (its loop over eight pairs is not unrolled).
     known = {("mp_tile_kernel", (4, 4, RELU, 0)), ("mp_tile_kernel", (4, 4, RELU, 1))}
     assert {k for k, (_, scratch) in kernels.items() if scratch} <= known
+
+
+# Forms that are slower, or that nothing launches, are not in the library.
+@pytest.mark.parametrize("kernel,arguments", [("mp_tile_kernel", (1, 4, RELU, 2))] + [("tile_batch_kernel", (w, SIGN, form)) for w in (13, 32) for form in (2, 3)])
+def test_forms_left_out(kernels, kernel, arguments):
+    assert (kernel, arguments[:-1] + (arguments[-1] & 1,)) in kernels and (kernel, arguments) not in kernels
