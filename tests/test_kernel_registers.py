@@ -1,7 +1,8 @@
 """What the code objects of the built library say of their kernels: registers and LDS decide how many wavefronts a SIMD holds.
 
 Kernels of whole tiles do not pay for the quarter form, whose registers and rows of dealer words would take wavefronts from
-every long launch, and no kernel keeps anything in scratch memory except the one that is known to."""
+every long launch, those that draw dealer words in step hold what they were measured with, and no kernel keeps anything in scratch
+memory."""
 import os
 import re
 import shutil
@@ -65,10 +66,56 @@ def test_whole_tiles_of_more_parties(kernels, parties, w, mode, wavefronts):
     assert _wavefronts(registers) >= wavefronts, registers
 
 
+# Wavefronts per SIMD of the kernels that draw dealer words in step, whole tiles and with quarters (forms 2 and 3): what long
+# launches run.  Template arguments before the form; widths and wavefronts.
+IN_STEP = [
+    ("tile_kernel", (RELU,), 2, ((1, 7, 4), (8, 9, 5), (10, 12, 6), (13, 21, 7), (22, 32, 8))),
+    ("tile_kernel", (RELU_SHARED,), 2, ((1, 7, 4), (8, 9, 5), (10, 12, 6), (13, 21, 7), (22, 32, 8))),
+    ("tile_kernel", (RELU,), 3, ((4, 7, 4), (8, 12, 5), (13, 16, 7), (17, 21, 5), (22, 32, 7))),
+    ("tile_kernel", (RELU_SHARED,), 3, ((4, 7, 4), (8, 12, 5), (13, 16, 7), (17, 21, 5), (22, 32, 7))),
+    ("tile_kernel", (DRELU,), 2, ((10, 32, 8),)),
+    ("tile_kernel", (DRELU_SHARED,), 2, ((10, 32, 8),)),
+    ("tile_kernel", (DRELU,), 3, ((10, 31, 8), (32, 32, 7))),
+    ("tile_kernel", (DRELU_SHARED,), 3, ((10, 32, 8),)),
+    ("tile_kernel", (SIGN,), 2, ((13, 32, 8),)),
+    ("tile_kernel", (SIGN,), 3, ((13, 32, 8),)),
+    ("tile_sim_kernel", (), 2, ((1, 2, 4), (3, 3, 6), (4, 4, 4), (5, 5, 6), (6, 9, 7), (10, 32, 8))),
+    ("tile_sim_kernel", (), 3, ((4, 4, 4), (5, 7, 5), (8, 8, 8), (9, 12, 5), (13, 16, 7), (17, 21, 5), (22, 32, 6))),
+    ("mp_tile_kernel", (3, RELU), 2, ((1, 1, 4), (2, 5, 3), (6, 9, 4), (10, 12, 5), (13, 21, 6), (22, 32, 7))),
+    ("mp_tile_kernel", (3, RELU), 3, ((4, 5, 3), (6, 9, 4), (10, 21, 5), (22, 32, 7))),
+    ("mp_tile_kernel", (3, DRELU), 2, ((5, 5, 7), (6, 32, 8))),
+    ("mp_tile_kernel", (3, DRELU), 3, ((5, 21, 7), (22, 32, 8))),
+    ("mp_tile_kernel", (4, RELU), 2, ((2, 4, 4), (5, 7, 3), (8, 12, 4), (13, 21, 5), (22, 32, 6))),
+    ("mp_tile_kernel", (4, RELU), 3, ((4, 4, 4), (5, 6, 3), (7, 7, 2), (8, 12, 3), (13, 16, 4), (17, 21, 3), (22, 32, 4))),
+    ("mp_tile_kernel", (4, DRELU), 2, ((5, 8, 6), (9, 32, 8))),
+    ("mp_tile_kernel", (4, DRELU), 3, ((5, 6, 5), (7, 21, 3), (22, 32, 5))),
+]
+BATCHED = [("tile_batch_kernel",) + row[1:] for row in IN_STEP if row[0] == "tile_kernel" and row[1] != (SIGN,)]
+
+
+@pytest.mark.parametrize("kernel,arguments,form,least", IN_STEP + BATCHED)
+def test_words_in_step(kernels, kernel, arguments, form, least):
+    seen = {a[0] for name, a in kernels if name == kernel and a[1:] == arguments + (form,)}
+    assert seen == {w for lo, hi, _ in least for w in range(lo, hi + 1)}
+    for lo, hi, wavefronts in least:
+        for w in range(lo, hi + 1):
+            registers, _ = kernels[kernel, (w,) + arguments + (form,)]
+            assert _wavefronts(registers) >= wavefronts, (w, registers)
+
+
+# The same of one thread per group (w > 32), without words in step and with.
+@pytest.mark.parametrize("kernel,arguments,wavefronts", [("group_kernel", (mode,), (8, 7)) for mode in range(5)]
+                         + [("wide_sim_kernel", (), (8, 8)), ("mp_group_kernel", (3, DRELU), (8, 8)), ("mp_group_kernel", (3, RELU), (6, 8)),
+                            ("mp_group_kernel", (4, DRELU), (5, 6)), ("mp_group_kernel", (4, RELU), (4, 7))])
+def test_one_thread_per_group(kernels, kernel, arguments, wavefronts):
+    for w in range(33, 65):
+        for runs in (0, 1):
+            registers, _ = kernels[kernel, (w,) + arguments + (runs,)]
+            assert _wavefronts(registers) >= wavefronts[runs], (w, runs, registers)
+
+
 def test_scratch(kernels):
-    # Four-party ReLU at w = 4 keeps its shares there (its loop over eight pairs is not unrolled).
-    known = {("mp_tile_kernel", (4, 4, RELU, 0)), ("mp_tile_kernel", (4, 4, RELU, 1))}
-    assert {k for k, (_, scratch) in kernels.items() if scratch} <= known
+    assert {k for k, (_, scratch) in kernels.items() if scratch} == set()
 
 
 # Forms that are slower, or that nothing launches, are not in the library.
