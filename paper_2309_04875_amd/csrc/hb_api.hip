@@ -528,10 +528,19 @@ constexpr int quarter_rounds(int w, int parties, int op)
 }
 // Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
 // w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third one after up to seven full rounds, of ReLU and the simulator at the widths where it
-// gains (600 left after one, two and four full rounds: ReLU w = 4 13.3 / 15.1, 19.0 / 20.5, 33.0 / 35.5; w = 8 8.4 / 9.5, 12.1 /
-// 12.9, 20.8 / 21.5; w = 9 9.7 / 10.6, 13.3 / 14.5, 21.5 / 22.4; w = 12 9.1 / 9.3, 11.7 / 12.4, 18.2 / 18.8; w = 5 11.9 / 12.5, 17.3 /
-// 17.7, 29.1 / 30.0; w = 6 10.8 / 11.2, 15.5 / 15.0; simulator w = 8 9.1 / 9.4, 12.3 / 13.1, w = 6 11.6 / 11.1, w = 12 9.3 / 8.9); DReLU
-// at w = 5 would lose (after two full rounds 13.4 / 11.5).  One round only
+// gains (600 left after one to seven full rounds, shared out / in whole tiles; the shared-mask layout and 520 to 768 left likewise):
+//   ReLU w = 4   12.2 / 17.7   18.0 / 22.4   24.8 / 28.4   30.7 / 36.6   37.5 / 41.4   43.4 / 48.2   48.5 / 54.5
+//            5   11.6 / 12.5   16.3 / 16.1   20.8 / 20.7   26.8 / 29.1
+//            6   10.7 / 11.1   15.2 / 14.2   18.7 / 17.9
+//            8    8.4 /  9.4   11.6 / 12.2   14.6 / 15.1   17.9 / 19.0   23.1 / 24.3   26.1 / 26.6   29.5 / 30.4
+//            9    9.8 / 10.4   13.1 / 14.0   16.8 / 17.5   20.2 / 20.8   24.0 / 25.8   27.5 / 28.1   31.6 / 32.0
+//           10    8.6 /  8.9   11.6 / 11.6   14.7 / 14.4   17.1 / 17.1   20.3 / 20.1   23.8 / 24.7   26.9 / 27.2
+//           11    8.9 /  9.2   11.7 / 11.9   14.5 / 14.9   17.7 / 17.7   21.0 / 20.5   23.6 / 24.5   26.5 / 26.5
+//           12    9.0 /  9.1   11.9 / 12.0   14.6 / 15.0   17.7 / 17.9   21.0 / 20.6   23.6 / 24.6   26.5 / 26.5
+//   sim.     4   12.9 / 15.0   18.3 / 20.3   23.8 / 25.9   29.9 / 32.2   35.0 / 37.2   40.3 / 42.6   45.6 / 48.4
+//            8    8.8 /  9.4   12.3 / 12.9   15.9 / 16.5   19.5 / 20.1   22.6 / 23.7   26.1 / 27.1   29.5 / 30.7
+//            6   11.3 / 11.2   15.9 / 15.5                     10    9.0 /  8.9   12.1 / 12.1
+// DReLU at w = 5 would lose (after two full rounds 13.4 / 11.5).  One round only
 //   - from w = 22, among more parties from w = 13 on, and of the simulator at w = 7 and from w = 17 on (376 left 9.0 / 8.8),
 //   - of sign shares at w = 5 and 6 after two full rounds (452 left 11.4 / 11.1 and 9.8 / 8.7; after one 6.2 / 6.8, after three
 //     15.9 / 17.2 and 12.9 / 13.9): three rounds of them reside together and wait for memory alone.
@@ -546,7 +555,9 @@ constexpr uint64_t shared_remainder(uint64_t tiles, int w, int parties, int op)
     if (op == kSimulator && (w == 7 || w >= 17)) return kQuarterRound;
     if (op == kSign && (w == 5 || w == 6) && full == 2) return kQuarterRound;
     if (parties == 2 && full < 8) {
-        if (op == kRelu && (w == 4 || (w >= 8 && w <= 12) || (w == 5 && full <= 4) || (w == 6 && full == 1))) return 3 * kQuarterRound;
+        const bool gains = w == 4 || w == 8 || w == 9 || (w == 5 && full <= 4) || (w == 6 && full == 1) || (w == 10 && full <= 2) ||
+                           ((w == 11 || w == 12) && full <= 4) || (w >= 10 && w <= 12 && full == 6);
+        if (op == kRelu && gains) return 3 * kQuarterRound;
         if (op == kSimulator && (w == 4 || w == 8)) return 3 * kQuarterRound;
     }
     return 2 * kQuarterRound;
