@@ -581,10 +581,19 @@ uint64_t small_tile_limit(uint64_t usual)
 //  12   4.8 / 4.8                   6.6 /  6.9              7.0 / 7.3      8.4 /  8.0                          9.9 /  9.3    360 / 333
 //  16   4.5 / 4.4                   5.0 /  5.3              6.4 / 5.9      7.5 /  6.7                          7.9 /  7.5    375 / 352
 //  32                               4.8 /  5.0              6.6 / 5.8      7.1 /  6.5                          7.2 /  6.6   1280 / 1174
-// (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1; at w = 4 1088 to 1280
-// tiles, which go by quarters, take as long either way.)
+// (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1.)  Beyond 1024 tiles the
+// line lies at one round of quarters, 256 tiles, at w = 4 at two.  256, 320 and 376 tiles beyond:
+//   ReLU   w = 5   9.2 /  9.5   11.0 / 10.3   10.9 / 10.4     DReLU w = 10   5.6 / 5.6   6.4 / 6.0   6.3 / 6.0
+//              9   7.9 /  8.3    9.2 /  8.8    9.2 /  8.9             11   5.6 / 5.9   6.5 / 6.1   6.6 / 6.2
+//             10   7.0 /  7.3    8.3 /  7.9    8.3 /  7.9             12   5.6 / 5.8   6.5 / 6.1   6.6 / 6.1
+//             11   7.1 /  7.4    8.5 /  7.9    8.5 /  8.0     (w = 4: 376 and 476 beyond 1.03, 676 0.97 of the time without)
+//             12   7.1 /  7.5    8.5 /  8.0    8.5 /  8.1
+// The simulator, which draws shares besides, has it from the first tile beyond 1024 on (6, 256 and 320 beyond: w = 5 9.5 / 9.2, 9.7 / 9.3,
+// 11.9 / 10.6; w = 6 8.9 / 8.4, 9.1 / 8.5, 11.0 / 9.6; w = 9 7.9 / 7.8, 7.9 / 7.9, 9.7 / 8.9; w = 10 7.2 / 6.9, 7.3 / 7.0, 8.6 / 7.8; w = 12 7.3 /
+// 6.8, 7.3 / 6.9, 8.9 / 7.9) except at w = 4 (9.9 / 10.2, 10.3 / 10.4, 12.2 / 11.4) and 8 (6.9 / 7.0, 7.0 / 7.1, 8.3 / 7.8).
 // Among more parties a kernel's second round counts from its first tile on (76 tiles beyond 1024: w = 8 12.4 / 12.4 and 20.0 / 19.3,
-// w = 32 13.3 / 11.3 and 24.1 / 20.5; 676 tiles 5 to 15 % of any width).
+// w = 32 13.3 / 11.3 and 24.1 / 20.5; 676 tiles 5 to 15 % of any width), but for w = 4 (three parties, 256 and 320 beyond, 16.6 / 16.8 and
+// 19.3 / 18.1; four, 320, 476 and 676 beyond, 29.2 / 30.5, 29.6 / 31.4, 46.0 / 38.6) and DReLU of three at w = 5 (11.2 / 11.8, 13.0 / 12.0).
 // DReLU of two parties at w = 10 to 12 gains least between 100 and 270 MB of shares and results, which stay in the cache before
 // memory in part: 3.7, 5.0, 6.3, 8.0 and 16 M elements w = 10 25.9 / 24.5, 34.3 / 32.9, 42.4 / 41.1, 53.4 / 50.7, 105 / 94.8, w = 11 29.1 /
 // 29.2, 38.0 / 38.7, 47.7 / 48.0, 62.2 / 59.4, 121 / 112, w = 12 29.2 / 28.6, 38.3 / 38.2, 47.3 / 47.4, 61.4 / 59.1, 122 / 113; on the
@@ -595,9 +604,11 @@ bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 {
     if (split == tiles) return tiles > kQuarterRound && (w == 8 || tiles <= kSimds);
     if (tiles <= kSimds) return false;
-    if (parties > 2) return w != 4 || tiles - kSimds > kQuarterRound;
-    if (w <= 3 || w == 7 || w >= 13) return true;
-    return tiles - kSimds > (w == 4 ? 2 * kQuarterRound : 320);
+    uint64_t line = w == 4 ? 2 : 1;                  // rounds of quarters beyond the full one that go without
+    if (parties > 2) line = w == 4 ? (parties == 4 ? 2 : 1) : parties == 3 && w == 5 && op == kDrelu ? 1 : 0;
+    else if (op == kSimulator) line = w == 4 || w == 8 ? 1 : 0;
+    else if (w <= 3 || w == 7 || w >= 13) line = 0;
+    return tiles - kSimds > line * kQuarterRound;
 }
 
 TileGrid tile_grid(uint64_t tiles, int w, int parties, int op)
