@@ -496,35 +496,61 @@ LauncherTable &launcher_table()
 // depends on how much of a quarter is spent on gate logic that its lanes repeat (most where a word has few fields), on idle
 // owners, and on what an operation spends beside the dealer's words.  Launches of up to that many rounds of quarters share every
 // tile out.  Measured, us, quarters / whole tiles:
-//              w     512 tiles     768 tiles     1024 tiles                  w     512           768           1024
-//   ReLU       4     5.6 /  9.1    7.0 / 10.1    8.4 / 10.4      sign        4     4.1 /  5.3    5.0 /  5.8    6.2 /  6.8
-//              6     6.0 /  7.8    7.5 /  7.9    8.9 /  8.1                  6     3.9 /  5.0    4.5 /  5.2    5.1 /  5.5
-//              7     7.5 /  8.4    9.1 /  8.5                                7     4.2 /  5.2    4.9 /  5.4    5.7 /  5.7
-//              8     4.5 /  6.8    5.5 /  6.9    6.6 /  7.1                 10     3.8 /  4.7    4.4 /  4.8    5.1 /  5.0
-//             10     4.8 /  6.5    6.0 /  6.6    7.2 /  6.7                 12     4.2 /  4.9    5.0 /  5.1    5.8 /  5.2
-//             12     5.1 /  6.8    6.6 /  7.0    8.0 /  7.1      simulator   4     5.9 /  9.8    7.7 /  9.9    9.5 / 10.1
-//             16     4.7 /  4.9    5.8 /  5.0                                6     6.5 /  7.8    8.4 /  7.9
-//             24     5.0 /  4.6 (256: 3.8 / 4.5)                             7     7.9 /  7.8 (256: 6.4 / 7.8)
-//   DReLU      4     3.9 /  6.0    5.2 /  6.3    5.9 /  7.2                  8     4.6 /  6.4    5.6 /  6.5    6.8 /  6.7
-//              8     3.7 /  4.7    4.3 /  4.8    5.2 /  5.1                 12     5.3 /  6.3    6.8 /  6.3
-//             12     4.4 /  5.2    5.4 /  5.5    6.4 /  5.6      four        4    12.8 / 26.1   17.6 / 28.4   22.7 / 33.0
-//   three      4     8.7 / 15.5   12.6 / 15.9   15.6 / 16.8                  6    14.6 / 19.8   20.5 / 20.0   25.3 / 20.5
-//              6     9.8 / 12.8   12.4 / 12.9   15.3 / 13.2                  8    12.1 / 17.4   15.4 / 17.6   19.2 / 17.9
-//             16     8.0 /  9.8   10.5 /  9.9                               16    13.2 / 16.4   17.3 / 16.6
-// (ReLU at w = 4, 1280 tiles: 10.2, as 1024 whole ones and 256 by quarters 11.6.  w = 7 has 72 pairs in a quarter: two passes
-// of the 64 lanes, the second one nearly empty.)
-// These were taken before tile_runs; with the form that it gives to more than one round of quarters ReLU at w = 5 takes 8.1 / 8.6
-// at 800 to 1024 tiles, w = 8 6.8 / 7.1 at 1088 tiles (as 1024 whole ones and the rest by quarters; 1536 8.3 / 8.0), the simulator
-// at w = 8 6.2 / 6.3 at 800 to 1000; w = 6 and 9 are as fast either way up to 1024.
+//              w    512 tiles     768 tiles     1024 tiles                 w    512           768           1024
+//   ReLU       4    5.4 / 11.2    6.4 / 11.7    7.5 / 13.3      sign       4    3.7 /  4.9    4.7 /  8.0    5.4 /  9.1
+//              5    5.8 /  9.8    7.0 / 10.0    8.2 / 10.4                 6    3.8 /  6.6    4.4 /  6.2    5.4 /  6.3
+//              6    5.6 /  9.2    6.9 /  8.5    8.1 /  9.2                 7    4.2 /  5.9    4.9 /  6.1    5.8 /  6.1
+//              7    7.2 /  9.2    8.6 /  9.2   10.1 /  9.3                 8    3.8 /  4.9    4.0 /  4.9    4.5 /  5.2
+//              8    4.3 /  7.1    5.2 /  7.6    6.0 /  7.7                 9    4.3 /  5.2    5.2 /  5.4    5.9 /  5.6
+//              9    5.2 /  8.0    6.4 /  7.8    7.6 /  8.0                10    3.9 /  4.6    4.4 /  5.0    5.1 /  5.2
+//             10    4.7 /  6.3    5.7 /  6.9    6.8 /  7.0                11    4.2 /  4.8    5.0 /  4.9    5.8 /  5.1
+//             11    5.0 /  6.6    6.2 /  6.7    7.4 /  7.1                12    4.2 /  4.5    5.0 /  4.7    5.9 /  4.9
+//             12    5.1 /  6.2    6.3 /  6.5    7.5 /  6.7                16    3.8 /  3.9    4.5 /  3.9    5.1 /  4.1
+//             16    4.6 /  5.0    5.5 /  5.2    6.4 /  5.3                17    4.5 /  4.3    5.5 /  4.4    6.4 /  4.5
+//             21    5.3 /  5.4    6.6 /  5.6    7.9 /  5.9                24    4.1 /  4.0    4.9 /  4.0    5.6 /  4.1
+//             24    4.9 /  4.5    5.9 /  4.6    7.0 /  4.7      sim.       4    5.6 / 10.8    7.0 / 11.0    8.4 / 11.0
+//   DReLU      4    3.9 /  6.4    5.0 /  9.4    5.7 / 10.7                 5    6.1 /  9.2    7.7 /  9.2    9.3 /  9.4
+//              6    4.2 /  6.8    5.0 /  6.4    5.9 /  6.6                 6    5.9 /  8.1    7.4 /  8.2    9.1 /  8.3
+//              7    4.6 /  6.6    5.7 /  6.4    6.7 /  6.6                 7    7.6 /  8.3    9.4 /  8.4   11.1 /  8.5
+//              8    3.8 /  5.1    4.3 /  5.0    4.9 /  5.8                 8    4.3 /  7.0    5.3 /  7.1    6.4 /  7.1
+//              9    4.6 /  5.8    5.6 /  5.8    6.6 /  6.2                 9    5.1 /  7.6    6.5 /  7.7    7.9 /  7.6
+//             10    4.1 /  4.9    4.8 /  5.3    5.6 /  5.5                10    4.7 /  6.3    5.8 /  6.4    7.1 /  6.5
+//             11    4.4 /  5.2    5.3 /  5.3    6.3 /  5.5                11    5.0 /  6.3    6.4 /  6.5    7.7 /  6.4
+//             12    4.3 /  4.8    5.3 /  5.1    6.3 /  5.2                12    5.0 /  6.4    6.4 /  6.5    7.7 /  6.5
+//             16    4.0 /  4.0    4.7 /  4.1    5.4 /  4.4                16    4.6 /  5.2    5.7 /  5.2    6.7 /  5.3
+//             17    4.6 /  4.5    5.7 /  4.5    6.8 /  4.6                21    5.3 /  5.7    6.8 /  5.7    8.2 /  5.8
+//             24    4.2 /  4.1    5.0 /  4.1    5.8 /  4.2                24    4.9 /  4.6    6.1 /  4.6    7.3 /  4.6
+//   three      4    8.3 / 18.1   10.4 / 18.9   14.4 / 19.5      four       4   11.9 / 28.6   15.7 / 30.7   19.8 / 32.7
+//              5    9.2 / 15.8   11.4 / 16.5   14.6 / 16.9                 5   13.8 / 22.3   17.8 / 23.2   22.6 / 23.8
+//              6    9.0 / 14.7   11.2 / 14.7   13.6 / 14.8                 6   13.8 / 21.8   17.8 / 22.2   22.7 / 22.1
+//              7   12.0 / 14.6   14.7 / 14.8   17.3 / 15.0                 7   18.6 / 21.6   25.5 / 21.7   30.6 / 22.1
+//              8    7.0 / 12.1    8.7 / 12.4   10.6 / 12.6                 8   11.5 / 18.5   14.4 / 18.9   18.2 / 19.2
+//              9    9.6 / 12.8   12.4 / 14.0   15.1 / 14.2                 9   15.9 / 21.1   20.8 / 22.0   26.5 / 22.5
+//             10    8.1 / 11.7   10.3 / 12.0   12.5 / 12.2                10   13.2 / 19.3   17.0 / 19.6   21.5 / 20.0
+//             11    9.5 / 12.0   12.2 / 12.1   14.7 / 12.1                11   15.7 / 19.4   20.4 / 19.6   26.2 / 20.3
+//             16    7.8 /  9.7   10.1 / 10.1   12.1 / 10.2                16   12.7 / 16.9   16.6 / 17.2   21.1 / 17.2
+//             24    8.8 /  9.6   11.5 /  9.8   14.4 /  9.9                24   15.2 / 17.5   21.8 / 17.7   26.9 / 17.7
+//   its DReLU  4    6.0 / 12.3    7.4 / 12.4    9.3 / 13.5      its DReLU  4    8.8 / 17.1   11.8 / 17.6   14.1 / 18.7
+//              6    6.9 / 11.1    8.3 / 11.1    9.8 / 11.1                 6   10.7 / 16.7   13.8 / 17.0   16.7 / 17.4
+//              7    8.1 / 10.9   10.1 / 11.0   11.9 / 11.1                 7   13.2 / 16.4   17.0 / 16.8   21.3 / 17.2
+//              8    6.0 /  9.4    7.4 /  9.6    8.6 /  9.9                 8    9.6 / 14.7   12.1 / 15.0   14.8 / 15.4
+//              9    8.6 / 10.7   10.9 / 11.2   13.1 / 11.2                 9   14.0 / 17.7   18.7 / 18.0   24.1 / 18.5
+//             10    7.0 /  9.9    8.9 /  9.9   10.6 / 10.1                10   11.8 / 16.5   15.4 / 16.9   19.5 / 17.1
+// (quarters in the form that tile_runs gives them; the shared-mask layout has its ratios within 3 %.)  Five rounds where quarters are
+// faster than 1024 whole tiles and 256 by quarters as well: 1280 tiles of ReLU at w = 4 9.5 / 10.2, w = 8 6.8 / 7.0 (1536 7.7 / 7.8, w = 5
+// 10.6 / 9.3).  Two rounds up to w = 21, one above and of DReLU and sign shares from w = 17 on.  (Sign
+// shares at w = 7: 800 tiles 5.9 / 5.4.)  w = 7 has 72 pairs in a quarter: two passes
+// of the 64 lanes, the second one nearly empty.
 constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
 constexpr int quarter_rounds(int w, int parties, int op)
 {
-    if (parties > 2) return w == 4 ? 4 : w == 5 || w == 8 || (parties == 3 && (w == 6 || w == 10)) ? 3 : 2;
-    if (w > 12) return w <= 21 ? 2 : 1;
-    if (op == kSimulator) return w == 4 || w == 8 ? 4 : w == 7 ? 1 : w == 6 || w >= 11 ? 2 : 3;
-    if (op == kSign) return w <= 6 || w == 8 ? 4 : 3;
-    if (op == kDrelu) return w <= 5 ? 4 : 3;
-    return w == 4 || w == 8 ? 5 : w == 5 ? 4 : w == 7 ? 2 : 3;
+    if (parties == 3) return w <= 6 || w == 8 ? 4 : w == 9 || w == 10 || (w == 7 && op == kDrelu) ? 3 : 2;
+    if (parties == 4) return w == 4 || w == 5 || w == 8 || (w == 6 && op == kDrelu) ? 4 : w == 6 || w == 10 || (w == 9 && op == kRelu) ? 3 : 2;
+    if (w > 12) return w <= 16 || (w <= 21 && op != kDrelu && op != kSign) ? 2 : 1;
+    if (op == kSimulator) return w == 4 || w == 8 ? 4 : w == 7 || w >= 11 ? 2 : 3;
+    if (op == kSign) return w >= 11 ? 2 : w == 7 || w == 9 ? 3 : 4;
+    if (op == kDrelu) return w >= 11 ? 2 : w == 7 || w >= 9 ? 3 : 4;
+    return w == 4 || w == 8 ? 5 : w == 7 || w >= 11 ? 3 : 4;
 }
 // Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
 // w = 8 7.9 / 10.1, w = 16 7.3 / 8.0.  A third one after up to seven full rounds, of ReLU and the simulator at the widths where it
@@ -581,7 +607,8 @@ uint64_t small_tile_limit(uint64_t usual)
 //  12   4.8 / 4.8                   6.6 /  6.9              7.0 / 7.3      8.4 /  8.0                          9.9 /  9.3    360 / 333
 //  16   4.5 / 4.4                   5.0 /  5.3              6.4 / 5.9      7.5 /  6.7                          7.9 /  7.5    375 / 352
 //  32                               4.8 /  5.0              6.6 / 5.8      7.1 /  6.5                          7.2 /  6.6   1280 / 1174
-// (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1.)  Beyond 1024 tiles the
+// (At w = 7 and below 4 the form wins from the first tile beyond 1024: 1088 tiles 10.1 / 9.2, w = 2 14.1 / 13.1;
+// at w = 4 1025 to 1280 tiles, which go by quarters alone, take 4 to 7 % longer with it.)  Beyond 1024 tiles the
 // line lies at one round of quarters, 256 tiles, at w = 4 at two.  256, 320 and 376 tiles beyond:
 //   ReLU   w = 5   9.2 /  9.5   11.0 / 10.3   10.9 / 10.4     DReLU w = 10   5.6 / 5.6   6.4 / 6.0   6.3 / 6.0
 //              9   7.9 /  8.3    9.2 /  8.8    9.2 /  8.9             11   5.6 / 5.9   6.5 / 6.1   6.6 / 6.2
