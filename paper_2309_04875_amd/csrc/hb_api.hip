@@ -538,18 +538,20 @@ LauncherTable &launcher_table()
 //             10    7.0 /  9.9    8.9 /  9.9   10.6 / 10.1                10   11.8 / 16.5   15.4 / 16.9   19.5 / 17.1
 // (quarters in the form that tile_runs gives them; the shared-mask layout has its ratios within 3 %.)  Five rounds where quarters are
 // faster than 1024 whole tiles and 256 by quarters as well: 1280 tiles of ReLU at w = 4 9.5 / 10.2, w = 8 6.8 / 7.0 (1536 7.7 / 7.8, w = 5
-// 10.6 / 9.3).  Two rounds up to w = 21, one above and of DReLU and sign shares from w = 17 on.  (Sign
-// shares at w = 7: 800 tiles 5.9 / 5.4.)  w = 7 has 72 pairs in a quarter: two passes
+// 10.6 / 9.3).  Two rounds up to w = 21, one above.  (Three where the fourth gains
+// at its end and loses at its start, 810 tiles of DReLU at w = 6 6.0 / 5.2, sign shares at w = 7 5.9 / 5.4, DReLU of four parties at w = 6 16.6 /
+// 15.6, or gains on one card and loses on the next, 810 and 1024 tiles of DReLU at w = 8 4.9 / 4.4 and 4.9 / 4.8, sign shares at w = 10 5.1 / 4.4 and
+// 5.2 / 4.9.  DReLU's third at w = 11 and 12 changes sides twice within it.)  w = 7 has 72 pairs in a quarter: two passes
 // of the 64 lanes, the second one nearly empty.
 constexpr uint64_t kSimds = 1024, kQuarterRound = kSimds / 4;
 constexpr int quarter_rounds(int w, int parties, int op)
 {
     if (parties == 3) return w <= 6 || w == 8 ? 4 : w == 9 || w == 10 || (w == 7 && op == kDrelu) ? 3 : 2;
-    if (parties == 4) return w == 4 || w == 5 || w == 8 || (w == 6 && op == kDrelu) ? 4 : w == 6 || w == 10 || (w == 9 && op == kRelu) ? 3 : 2;
-    if (w > 12) return w <= 16 || (w <= 21 && op != kDrelu && op != kSign) ? 2 : 1;
+    if (parties == 4) return w == 4 || w == 5 || w == 8 ? 4 : w == 6 || w == 10 || (w == 9 && op == kRelu) ? 3 : 2;
+    if (w > 12) return w <= 21 ? 2 : 1;
     if (op == kSimulator) return w == 4 || w == 8 ? 4 : w == 7 || w >= 11 ? 2 : 3;
-    if (op == kSign) return w >= 11 ? 2 : w == 7 || w == 9 ? 3 : 4;
-    if (op == kDrelu) return w >= 11 ? 2 : w == 7 || w >= 9 ? 3 : 4;
+    if (op == kSign) return w >= 11 ? 2 : w == 7 || w >= 9 ? 3 : 4;
+    if (op == kDrelu) return w <= 5 ? 4 : 3;
     return w == 4 || w == 8 ? 5 : w == 7 || w >= 11 ? 3 : 4;
 }
 // Of what a longer launch leaves after its last full round, two rounds of quarters are shared out: 376 tiles left, ReLU,
@@ -566,6 +568,8 @@ constexpr int quarter_rounds(int w, int parties, int op)
 //   sim.     4   12.9 / 15.0   18.3 / 20.3   23.8 / 25.9   29.9 / 32.2   35.0 / 37.2   40.3 / 42.6   45.6 / 48.4
 //            8    8.8 /  9.4   12.3 / 12.9   15.9 / 16.5   19.5 / 20.1   22.6 / 23.7   26.1 / 27.1   29.5 / 30.7
 //            6   11.3 / 11.2   15.9 / 15.5                     10    9.0 /  8.9   12.1 / 12.1
+// Where the sides are within 3 %, w = 10 to 12 after three rounds and more, the card decides: on another w = 10 took 18.2 / 18.6 after four and
+// w = 12 20.6 / 21.4 after five.
 // DReLU at w = 5 would lose (after two full rounds 13.4 / 11.5).  One round only
 //   - from w = 22, among more parties from w = 13 on, and of the simulator at w = 7 and from w = 17 on (376 left 9.0 / 8.8),
 //   - of sign shares at w = 5 and 6 after two full rounds (452 left 11.4 / 11.1 and 9.8 / 8.7; after one 6.2 / 6.8, after three
@@ -581,9 +585,7 @@ constexpr uint64_t shared_remainder(uint64_t tiles, int w, int parties, int op)
     if (op == kSimulator && (w == 7 || w >= 17)) return kQuarterRound;
     if (op == kSign && (w == 5 || w == 6) && full == 2) return kQuarterRound;
     if (parties == 2 && full < 8) {
-        const bool gains = w == 4 || w == 8 || w == 9 || (w == 5 && full <= 4) || (w == 6 && full == 1) || (w == 10 && full <= 2) ||
-                           ((w == 11 || w == 12) && full <= 4) || (w >= 10 && w <= 12 && full == 6);
-        if (op == kRelu && gains) return 3 * kQuarterRound;
+        if (op == kRelu && (w == 4 || (w >= 8 && w <= 12) || (w == 5 && full <= 4) || (w == 6 && full == 1))) return 3 * kQuarterRound;
         if (op == kSimulator && (w == 4 || w == 8)) return 3 * kQuarterRound;
     }
     return 2 * kQuarterRound;
@@ -621,6 +623,10 @@ uint64_t small_tile_limit(uint64_t usual)
 // Among more parties a kernel's second round counts from its first tile on (76 tiles beyond 1024: w = 8 12.4 / 12.4 and 20.0 / 19.3,
 // w = 32 13.3 / 11.3 and 24.1 / 20.5; 676 tiles 5 to 15 % of any width), but for w = 4 (three parties, 256 and 320 beyond, 16.6 / 16.8 and
 // 19.3 / 18.1; four, 320, 476 and 676 beyond, 29.2 / 30.5, 29.6 / 31.4, 46.0 / 38.6) and DReLU of three at w = 5 (11.2 / 11.8, 13.0 / 12.0).
+// Their ReLU at w = 1 streams 96 and 128 bytes an element past a circuit of one gate an adder: words in step pay while the launch's
+// wavefronts reside all at once, in the third and fourth round (three parties, 2.5 M elements 30.2 / 28.7; four, 1.3 M 21.3 / 20.8), not before
+// (0.7 M 14.3 / 15.3) and not after (three, 3.6, 5.3 and 8.1 M 42.2 / 44.7, 54.0 / 55.1, 81.7 / 81.3; four, 2.1, 9.2 and 20.5 M 33.2 / 35.6, 112 / 120,
+// 246 / 259).
 // DReLU of two parties at w = 10 to 12 gains least between 100 and 270 MB of shares and results, which stay in the cache before
 // memory in part: 3.7, 5.0, 6.3, 8.0 and 16 M elements w = 10 25.9 / 24.5, 34.3 / 32.9, 42.4 / 41.1, 53.4 / 50.7, 105 / 94.8, w = 11 29.1 /
 // 29.2, 38.0 / 38.7, 47.7 / 48.0, 62.2 / 59.4, 121 / 112, w = 12 29.2 / 28.6, 38.3 / 38.2, 47.3 / 47.4, 61.4 / 59.1, 122 / 113; on the
@@ -631,6 +637,7 @@ bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 {
     if (split == tiles) return tiles > kQuarterRound && (w == 8 || tiles <= kSimds);
     if (tiles <= kSimds) return false;
+    if (parties > 2 && w == 1) return tiles > 2 * kSimds && tiles <= 4 * kSimds;
     uint64_t line = w == 4 ? 2 : 1;                  // rounds of quarters beyond the full one that go without
     if (parties > 2) line = w == 4 ? (parties == 4 ? 2 : 1) : parties == 3 && w == 5 && op == kDrelu ? 1 : 0;
     else if (op == kSimulator) line = w == 4 || w == 8 ? 1 : 0;

@@ -53,9 +53,7 @@ TileGrid tile_grid(uint64_t tiles, int w, int parties, int op);
 // Whether tile kernels have the form with RUNS (mix_words), which long launches then take (tile_runs).  Not where memory bounds long
 // launches, which wavefronts of unequal priority disturb: 2^25 elements, us, without / with: DReLU at w = 6 177 / 183, w = 8 175 /
 // 181, w = 9 203 / 199 (16 M elements on the shared-mask layout 96.5 / 98.4), w = 10 217 / 200; sign shares at w = 6 172 / 180, w = 12 211 / 204 (8 M elements 57 / 58), w = 16 241 / 221.
-// Among three and four parties DReLU at w = 4 (2^24 elements, three 142 / 146; w = 5 154 / 148), and ReLU at w = 1, which
-// streams 96 and 128 bytes an element past a circuit of one gate an adder: four, 3.4 M elements 44.8 / 47.6, 9.2 M 113 / 120, 20.5 M 246 /
-// 259 (1.0 to 1.9 M elements 21.3 / 20.7); three, 2 to 5 % between 3 and 8 M (3.6 M 42.5 / 44.8; 1.4 to 2.2 M 3 to 5 % the other way).
+// Among three and four parties DReLU at w = 4 (2^24 elements, three 142 / 146; w = 5 154 / 148).
 // Where the form's registers cost a wavefront per SIMD it gains all the same: the simulator at w = 1 (104 registers instead of 81,
 // 2.2, 9.2 and 20.5 M elements 21.1 / 18.9, 55.8 / 51.1, 116 / 106) and w = 4 (102 instead of 93; 16.7 / 15.8, 60.3 / 54.0, 126 / 113),
 // ReLU of three parties at w = 2 (130 instead of 121; 1.4, 6.0 and 13.4 M 26.8 / 23.9, 70.2 / 66.8, 154 / 139).
@@ -63,7 +61,6 @@ constexpr bool runs_supported(int w, int parties, int op)
 {
     if (op == kSign) return w >= 13;
     if (op == kDrelu) return parties == 2 ? w >= 10 : w >= 5;
-    if (op == kRelu && parties > 2) return w != 1;
     return true;
 }
 

@@ -36,6 +36,13 @@ def test_quarters_of_a_tile(parties, w):
 
 
 @pytest.mark.parametrize("parties", [3, 4])
+def test_one_bit_in_its_third_and_fourth_round(parties):
+    per = 32 * (64 // parties)
+    for tiles in (2048, 2049, 4096, 4097):
+        _check(parties, 1, tiles * per - 5)
+
+
+@pytest.mark.parametrize("parties", [3, 4])
 @pytest.mark.parametrize("w", [33, 34, 64])
 def test_one_thread_per_group(parties, w):
     for n in (65536, 65537):

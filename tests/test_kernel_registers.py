@@ -81,11 +81,11 @@ IN_STEP = [
     ("tile_kernel", (SIGN,), 3, ((13, 32, 8),)),
     ("tile_sim_kernel", (), 2, ((1, 2, 4), (3, 3, 6), (4, 4, 4), (5, 5, 6), (6, 9, 7), (10, 32, 8))),
     ("tile_sim_kernel", (), 3, ((4, 4, 4), (5, 7, 5), (8, 8, 8), (9, 12, 5), (13, 16, 7), (17, 21, 5), (22, 32, 6))),
-    ("mp_tile_kernel", (3, RELU), 2, ((2, 5, 3), (6, 9, 4), (10, 12, 5), (13, 21, 6), (22, 32, 7))),
+    ("mp_tile_kernel", (3, RELU), 2, ((1, 1, 4), (2, 5, 3), (6, 9, 4), (10, 12, 5), (13, 21, 6), (22, 32, 7))),
     ("mp_tile_kernel", (3, RELU), 3, ((4, 5, 3), (6, 9, 4), (10, 21, 5), (22, 32, 7))),
     ("mp_tile_kernel", (3, DRELU), 2, ((5, 5, 7), (6, 32, 8))),
     ("mp_tile_kernel", (3, DRELU), 3, ((5, 21, 7), (22, 32, 8))),
-    ("mp_tile_kernel", (4, RELU), 2, ((2, 4, 4), (5, 7, 3), (8, 12, 4), (13, 21, 5), (22, 32, 6))),
+    ("mp_tile_kernel", (4, RELU), 2, ((1, 4, 4), (5, 7, 3), (8, 12, 4), (13, 21, 5), (22, 32, 6))),
     ("mp_tile_kernel", (4, RELU), 3, ((4, 4, 4), (5, 6, 3), (7, 7, 2), (8, 12, 3), (13, 16, 4), (17, 21, 3), (22, 32, 4))),
     ("mp_tile_kernel", (4, DRELU), 2, ((5, 8, 6), (9, 32, 8))),
     ("mp_tile_kernel", (4, DRELU), 3, ((5, 6, 5), (7, 21, 3), (22, 32, 5))),
@@ -119,6 +119,7 @@ def test_scratch(kernels):
 
 
 # Forms that are slower, or that nothing launches, are not in the library.
-@pytest.mark.parametrize("kernel,arguments", [("mp_tile_kernel", (1, p, RELU, 2)) for p in (3, 4)] + [("tile_batch_kernel", (w, SIGN, form)) for w in (13, 32) for form in (2, 3)])
+@pytest.mark.parametrize("kernel,arguments", [("tile_batch_kernel", (w, SIGN, form)) for w in (13, 32) for form in (2, 3)]
+                         + [("mp_tile_kernel", (4, p, DRELU, form)) for p in (3, 4) for form in (2, 3)])
 def test_forms_left_out(kernels, kernel, arguments):
     assert (kernel, arguments[:-1] + (arguments[-1] & 1,)) in kernels and (kernel, arguments) not in kernels
