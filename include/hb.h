@@ -22,6 +22,8 @@
  *     call is rejected.
  *   - stream: a hipStream_t passed as void* (NULL = the default stream).  Work is enqueued on that
  *     stream; the call does not synchronise, does not allocate and keeps no state between calls.
+ *     Kernels of long launches raise the priority of their wavefronts inside a compute unit for most of their time, so a
+ *     kernel on another stream that shares compute units with one gets fewer of its instructions issued meanwhile.
  *   - opened_bits: HOST pointer or NULL; receives the number of bits the two parties would open to
  *     each other for this call (closed form, written before the call returns).
  *   - return value: HB_OK or a negative status; on error nothing is enqueued and no output is

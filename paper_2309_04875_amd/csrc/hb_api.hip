@@ -631,8 +631,8 @@ uint64_t small_tile_limit(uint64_t usual)
 // memory in part: 3.7, 5.0, 6.3, 8.0 and 16 M elements w = 10 25.9 / 24.5, 34.3 / 32.9, 42.4 / 41.1, 53.4 / 50.7, 105 / 94.8, w = 11 29.1 /
 // 29.2, 38.0 / 38.7, 47.7 / 48.0, 62.2 / 59.4, 121 / 112, w = 12 29.2 / 28.6, 38.3 / 38.2, 47.3 / 47.4, 61.4 / 59.1, 122 / 113; on the
 // shared-mask layout 24.9 / 23.4, 32.1 / 30.8, 38.5 / 39.5, 49.4 / 48.0, 97.4 / 91.7; 27.5 / 26.1, 35.8 / 36.3, 43.9 / 45.3, 57.2 / 56.3,
-// 112 / 106; 27.4 / 26.0, 35.7 / 36.1, 44.1 / 44.7, 57.0 / 56.0, 112 / 106.  So on three cards; a fourth took w = 10 up to 7 % longer
-// with the form between 3.5 and 7 M, and the rest as these.  A line there would cost more than it gives.
+// 112 / 106; 27.4 / 26.0, 35.7 / 36.1, 44.1 / 44.7, 57.0 / 56.0, 112 / 106.  So on three cards; two others took w = 10 up to
+// 7 % longer with the form between 3.5 and 7 M, and the rest as these.  A line there would cost on one card what it gives on the next.
 bool tile_runs(uint64_t tiles, uint64_t split, int w, int parties, int op)
 {
     if (split == tiles) return tiles > kQuarterRound && (w == 8 || tiles <= kSimds);

@@ -85,6 +85,10 @@ using Pair = WordPair<uint64_t>;
 // SIMD, five or ten words in step: 72 cycles a word without priorities whatever the order of the instructions, 61 and 58
 // with them, 72 with the priorities the other way round.  One wavefront per SIMD has nobody to share with, and the changes of
 // priority cost it 1 to 5 %, so kernels exist with RUNS and without.
+// The lowest priority is also the one that kernels without RUNS, and everyone else's, run at: beside a ReLU on another stream they
+// get fewer issue slots.  Both on one GPU at a time, us a launch, form before / with RUNS: ReLU at w = 8 (2^24 elements) 211 / 203 and a
+// DReLU of as many beside it 133 / 140, a bf16 product of 4096^3 225 / 218, an addition of 2^26 floats 228 / 227; beside ReLU at w = 64 (2^22
+// elements) 240 / 129, 257 / 243, 271 / 252.
 constexpr int kXorRuns = 0, kElsewhere = 1;        // wave priorities
 
 template <bool RUNS, int PRIORITY>
